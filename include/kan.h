@@ -156,9 +156,11 @@ kan_status kan_layer_forward(const kan_grid* grid, kan_dtype dtype, int64_t batc
  * kan_layer_forward_workspace_bytes -- size in bytes of the workspace that
  * kan_layer_forward uses for a layer (eq. kan_forward) of this grid, dtype,
  * batch and shape: the packed weights (kan_layer_packed_bytes, the least
- * kan_layer_forward accepts) and, for batches too small to fill the GPU, the
- * fp32 partial sums of the split contraction from the next 256-byte boundary
- * (kan_layer_forward_packed_workspace_bytes).  With only the packed weights'
+ * kan_layer_forward accepts) and, from the next 256-byte boundary, what the
+ * packed forward can use
+ * (kan_layer_forward_packed_full_workspace_bytes: the fp32 partial sums of the
+ * split contraction for batches too small to fill the GPU, the window kernel's
+ * expanded weights for large layers).  With only the packed weights'
  * size the layer runs unsplit.
  * Writes *bytes.  Returns KAN_OK, KAN_ERR_INVALID_ARG (bytes == NULL, bad grid
  * or sizes, batch < 0) or KAN_ERR_UNSUPPORTED.
@@ -221,7 +223,9 @@ kan_status kan_layer_pack(const kan_grid* grid, kan_dtype dtype, int32_t in_feat
  *           kan_layer_forward_packed_workspace_bytes(...), a 16-byte aligned
  *           workspace overlapping no other argument.  A NULL or smaller
  *           workspace runs the layer unsplit (same result up to the fp32
- *           summation order).
+ *           summation order).  With
+ *           kan_layer_forward_packed_full_workspace_bytes(...) bytes large
+ *           layers run on the window kernel (below).
  *   y       [batch, out_features]   dtype storage, fully overwritten; must not
  *           overlap x or packed.
  *
@@ -245,6 +249,27 @@ kan_status kan_layer_forward_packed_workspace_bytes(const kan_grid* grid, kan_dt
                                                     int64_t batch, int32_t in_features,
                                                     int32_t out_features, const int32_t* shape,
                                                     size_t* bytes);
+
+/*
+ * kan_layer_forward_packed_full_workspace_bytes -- size in bytes of the
+ * workspace with which kan_layer_forward_packed can use every kernel it has
+ * for this layer and batch (with shape NULL): the split's partial sums as
+ * above, or for large layers outside the structured-sparse bf16 ones and
+ * the narrow fp32 ones, of degrees 1 to 3, the window kernel's expanded
+ * weights and partial sums.  That kernel contracts only the k + 1 basis
+ * columns whose support holds each input, on the structured-sparse matrix
+ * instruction; in fp32 every basis value and coefficient is the sum of two
+ * fp16 terms (scaled per output column) and the SiLU column stays in fp32,
+ * with fp32 accumulation: the same result up to the fp32 summation order.
+ * An infinite or NaN coefficient times a basis value of exactly 0 is NaN in
+ * fp32, as without the workspace; in bf16 a coefficient is not read for the
+ * inputs whose window leaves it out.  A smaller workspace runs the layer as
+ * kan_layer_plan reports.
+ * Writes *bytes.  Returns as kan_layer_forward_packed_workspace_bytes.
+ */
+kan_status kan_layer_forward_packed_full_workspace_bytes(const kan_grid* grid, kan_dtype dtype,
+                                                         int64_t batch, int32_t in_features,
+                                                         int32_t out_features, size_t* bytes);
 
 /*
  * kan_layer_plan -- the workgroup shape that kan_layer_forward_packed (and

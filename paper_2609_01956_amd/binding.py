@@ -32,6 +32,7 @@ KAN_BF16 = 1
 EXPORTED_SYMBOLS = ("kan_basis_eval", "kan_basis_eval_cdb", "kan_layer_forward", "kan_layer_forward_workspace_bytes",
                     "kan_layer_packed_bytes", "kan_layer_pack", "kan_layer_forward_packed",
                     "kan_layer_forward_packed_workspace_bytes",
+                    "kan_layer_forward_packed_full_workspace_bytes",
                     "kan_layer_plan", "kan_layer_forward_noalloc", "kan_layer_backward",
                     "kan_layer_backward_workspace_bytes", "kan_layer_forward_span",
                     "kan_layer_forward_span_workspace_bytes", "kan_status_string",
@@ -93,6 +94,9 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                 g, ctypes.c_int, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, _I32P,
                 ctypes.POINTER(ctypes.c_size_t)]
             lib.kan_layer_forward_packed_workspace_bytes.restype = ctypes.c_int
+            lib.kan_layer_forward_packed_full_workspace_bytes.argtypes = \
+                lib.kan_layer_forward_workspace_bytes.argtypes
+            lib.kan_layer_forward_packed_full_workspace_bytes.restype = ctypes.c_int
             lib.kan_layer_plan.argtypes = [g, ctypes.c_int, ctypes.c_int64, ctypes.c_int32,
                                            ctypes.c_int32, _I32P, _I32P]
             lib.kan_layer_plan.restype = ctypes.c_int
@@ -286,6 +290,17 @@ def kan_layer_forward_packed_workspace_bytes(grid: kan_grid, dtype: int, batch: 
     return st, int(n.value)
 
 
+def kan_layer_forward_packed_full_workspace_bytes(grid: kan_grid, dtype: int, batch: int,
+                                                  in_features: int,
+                                                  out_features: int) -> Tuple[int, int]:
+    """Raw call: returns (kan_status, bytes)."""
+    n = ctypes.c_size_t(0)
+    st = int(load_library().kan_layer_forward_packed_full_workspace_bytes(
+        ctypes.byref(grid), int(dtype), int(batch), int(in_features), int(out_features),
+        ctypes.byref(n)))
+    return st, int(n.value)
+
+
 def check(status: int) -> None:
     """Map a kan_status to an exception."""
     if status == KAN_OK:
@@ -412,9 +427,10 @@ def layer_forward_packed(x, packed: PackedLayer, out=None, shape=None, workspace
     """kan_layer_forward_packed: x [B, in] with packed weights -> y [B, out].
     `shape` forces a workgroup shape (rf, wk[, nw[, cs]]) for tests and tuning.
     For batches too small to fill the GPU the contraction is split across
-    workgroups; its partial sums go to `workspace` (a uint8 device tensor)
+    workgroups, and large layers run on weights expanded for the call; the
+    partial sums and expanded weights go to `workspace` (a uint8 device tensor)
     when large enough, else to a fresh one from torch's allocator; split=False
-    runs the layer unsplit."""
+    runs the layer unsplit on the packed weights alone."""
     torch = _torch()
     _require_device(x)
     if x.dim() != 2 or x.shape[1] != packed.n_in:
@@ -432,8 +448,12 @@ def layer_forward_packed(x, packed: PackedLayer, out=None, shape=None, workspace
     dt = _dtype_code(x)
     ws_ptr, ws_bytes = 0, 0
     if split:
-        st, need = kan_layer_forward_packed_workspace_bytes(g, dt, B, packed.n_in, packed.n_out,
-                                                            shape)
+        if shape is None:
+            st, need = kan_layer_forward_packed_full_workspace_bytes(g, dt, B, packed.n_in,
+                                                                     packed.n_out)
+        else:
+            st, need = kan_layer_forward_packed_workspace_bytes(g, dt, B, packed.n_in,
+                                                                packed.n_out, shape)
         check(st)
         if need > 0:
             if workspace is None or workspace.numel() < need or workspace.device != x.device:

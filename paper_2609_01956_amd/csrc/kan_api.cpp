@@ -275,6 +275,36 @@ kan_status kan_layer_forward_packed(const kan_grid* grid, kan_dtype dtype, int64
     st = check_forward_packed(geom, dtype, batch, in_features, out_features, x, packed,
                               packed_bytes, y);
     if (st != KAN_OK) return st;
+    const size_t es = dtype_size(dtype);
+    const uint64_t ub = (uint64_t)batch;
+    // The window kernel where it is planned and the workspace can hold its
+    // expanded weights; any other workspace leaves the layer on the kernels
+    // that read the packed weights.
+    kan::WinGeom wg;
+    if (shape == nullptr &&
+        kan::plan_window(geom, dtype == KAN_BF16, batch, in_features, out_features, &wg) &&
+        workspace != nullptr && workspace_bytes >= wg.bytes && aligned(workspace, 16) &&
+        !overlap(workspace, wg.bytes, x, ub * (size_t)in_features * es) &&
+        !overlap(workspace, wg.bytes, packed, geom.packed_bytes) &&
+        !overlap(workspace, wg.bytes, y, ub * (size_t)out_features * es)) {
+        kan::WinArgs a = {};
+        a.x = x;
+        a.wp = packed;
+        a.y = y;
+        a.ws = workspace;
+        a.batch = batch;
+        a.in = in_features;
+        a.out = out_features;
+        a.nb = gc.nb;
+        a.inv_h = gc.inv_h;
+        a.inv_lo = gc.inv_lo;
+        a.xlim = gc.xlim;
+        a.a_int = gc.a_int;
+        a.a_frac = gc.a_frac;
+        a.kdeg = gc.k;
+        return device_status(kan::launch_window(dtype == KAN_BF16, geom, wg, a,
+                                                static_cast<hipStream_t>(stream)));
+    }
     // The K split of small batches runs when the workspace holds its partial
     // sums; without one the layer runs unsplit (same result up to the fp32
     // summation order).
@@ -282,8 +312,6 @@ kan_status kan_layer_forward_packed(const kan_grid* grid, kan_dtype dtype, int64
     const size_t pbytes = kan::layer_partial_bytes(geom, cfg, batch, out_features);
     if (ks > 1 && (workspace == nullptr || workspace_bytes < pbytes)) ks = 1;
     if (ks > 1) {
-        const size_t es = dtype_size(dtype);
-        const uint64_t ub = (uint64_t)batch;
         if (!aligned(workspace, 16) ||
             overlap(workspace, pbytes, x, ub * (size_t)in_features * es) ||
             overlap(workspace, pbytes, packed, geom.packed_bytes) ||
@@ -308,6 +336,21 @@ kan_status kan_layer_forward_packed_workspace_bytes(const kan_grid* grid, kan_dt
     st = layer_shape(geom, dtype, batch < 1 ? 1 : batch, shape, &cfg);
     if (st != KAN_OK) return st;
     *bytes = batch == 0 ? 0 : kan::layer_partial_bytes(geom, cfg, batch, out_features);
+    return KAN_OK;
+}
+
+kan_status kan_layer_forward_packed_full_workspace_bytes(const kan_grid* grid, kan_dtype dtype,
+                                                         int64_t batch, int32_t in_features,
+                                                         int32_t out_features, size_t* bytes) {
+    const kan_status st = kan_layer_forward_packed_workspace_bytes(
+        grid, dtype, batch, in_features, out_features, nullptr, bytes);
+    if (st != KAN_OK) return st;
+    kan::GridConst gc;
+    kan::LayerGeom geom;
+    kan::WinGeom wg;
+    if (check_layer(grid, dtype, in_features, out_features, &gc, &geom) == KAN_OK &&
+        kan::plan_window(geom, dtype == KAN_BF16, batch, in_features, out_features, &wg))
+        *bytes = wg.bytes;
     return KAN_OK;
 }
 
@@ -343,8 +386,10 @@ kan_status kan_layer_forward_workspace_bytes(const kan_grid* grid, kan_dtype dty
     if (batch < 0 || batch > (int64_t)0x7fffffff * 32) return KAN_ERR_INVALID_ARG;
     // the packed weights, then (small batches) the K split's partial sums
     const kan::LayerCfg cfg = kan::plan_layer(geom, dtype == KAN_BF16, batch < 1 ? 1 : batch);
-    const size_t pbytes =
-        batch == 0 ? 0 : kan::layer_partial_bytes(geom, cfg, batch, out_features);
+    size_t pbytes = batch == 0 ? 0 : kan::layer_partial_bytes(geom, cfg, batch, out_features);
+    kan::WinGeom wg;
+    if (kan::plan_window(geom, dtype == KAN_BF16, batch, in_features, out_features, &wg))
+        pbytes = wg.bytes;
     *bytes = pbytes == 0 ? geom.packed_bytes : align256(geom.packed_bytes) + pbytes;
     return KAN_OK;
 }

@@ -199,6 +199,53 @@ hipError_t launch_layer_f32(const LayerGeom& g, const LayerCfg& c, const LayerAr
 bool narrow_ok(const LayerGeom& g);
 hipError_t launch_narrow(const LayerGeom& g, const LayerArgs& a, hipStream_t s);
 
+// --------------------------------------------- window kernel (kan_window_kernel.h)
+//
+// The fused forward on the structured-sparse matrix instruction for degrees 1 ..
+// 3 and any grid: fp32 as two fp16 terms per operand, bf16 where a feature
+// does not take two blocks of eight columns.  It runs on weights expanded from
+// the packed buffer into the caller's workspace.
+struct WinGeom {
+    int nfw;        // 32-column fragments per wave (64 nfw columns per tile)
+    int bn;         // columns per tile
+    int ntiles;
+    int nbk;        // 16-column blocks per feature
+    int steps;      // contraction steps: npairs nbk
+    int spb;        // steps per stage
+    int stages;     // ceil(steps / spb)
+    int ks, sps;    // K splits, stages per split (a multiple of nbk)
+    int64_t rblocks;  // row blocks of 256
+    size_t off_w, off_cm, off_us, off_flag, off_p, bytes;  // workspace layout
+};
+// 16-byte units of a step's weights in LDS: the terms of both features' 16 columns,
+// in fp32 also the SiLU weights, in whole wave loads.
+__host__ __device__ constexpr int win_step_units(bool bf16, int bn) {
+    return bf16 ? 4 * bn : (8 * bn + bn / 2 + 63) / 64 * 64;
+}
+constexpr int kColGroups = 16;  // fp32: partial column maxima
+// The geometry the planner chooses for a layer and batch; false where the
+// kernels on the packed weights stay the choice.
+bool plan_window(const LayerGeom& g, bool bf16, int64_t batch, int in, int out, WinGeom* w);
+
+struct WinArgs {
+    const void* x;   // [batch, in]
+    const void* wp;  // packed weights
+    void* y;         // [batch, out]
+    void* ws;        // workspace of WinGeom::bytes
+    size_t off_w, off_cm, off_us, off_flag, off_p;
+    int64_t batch;
+    int in, out, nb, npairs, nbk, steps, steps_pad, stages, sps, ks, bn, step_u;
+    int pk_ntile, pk_nblk_pad, pk_nsb;  // the packed buffer's tiles
+    float inv_h, inv_lo, xlim, a_int, a_frac;
+    int kdeg;
+};
+hipError_t launch_window(bool bf16, const LayerGeom& g, const WinGeom& w, WinArgs a, hipStream_t s);
+hipError_t launch_window_f32(const WinGeom& g, const WinArgs& a, hipStream_t s);
+hipError_t launch_window_bf16(const WinGeom& g, const WinArgs& a, hipStream_t s);
+// y = the sum of ks fp32 partial results [split][n] in split order.
+hipError_t launch_split_reduce(bool bf16, const float* P, void* y, int64_t n, int ks,
+                               hipStream_t s);
+
 // ------------------------------------------------------------- backward
 //
 // Gradients of the layer for an upstream gradient dy [batch, out]:

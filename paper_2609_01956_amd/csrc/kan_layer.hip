@@ -344,15 +344,100 @@ hipError_t launch_layer(bool bf16, const LayerGeom& g, const LayerCfg& c, LayerA
     a.P = ks > 1 ? static_cast<float*>(partial) : nullptr;
     hipError_t e = bf16 ? launch_layer_bf16(g, c, a, s) : launch_layer_f32(g, c, a, s);
     if (e != hipSuccess || ks == 1) return e;
-    const int64_t n = a.batch * (int64_t)a.out;
+    return launch_split_reduce(bf16, a.P, a.y, a.batch * (int64_t)a.out, ks, s);
+}
+
+hipError_t launch_split_reduce(bool bf16, const float* P, void* y, int64_t n, int ks,
+                               hipStream_t s) {
     const unsigned blocks = (unsigned)((n + 255) / 256);
     if (bf16)
-        hipLaunchKernelGGL(split_reduce_kernel<uint16_t>, dim3(blocks), dim3(256), 0, s,
-                           a.P, static_cast<uint16_t*>(a.y), n, ks);
+        hipLaunchKernelGGL(split_reduce_kernel<uint16_t>, dim3(blocks), dim3(256), 0, s, P,
+                           static_cast<uint16_t*>(y), n, ks);
     else
-        hipLaunchKernelGGL(split_reduce_kernel<float>, dim3(blocks), dim3(256), 0, s, a.P,
-                           static_cast<float*>(a.y), n, ks);
+        hipLaunchKernelGGL(split_reduce_kernel<float>, dim3(blocks), dim3(256), 0, s, P,
+                           static_cast<float*>(y), n, ks);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------- window kernel
+
+bool plan_window(const LayerGeom& g, bool bf16, int64_t batch, int in, int out, WinGeom* w) {
+    if (g.kdeg > 3 || g.sparse || batch < 1) return false;
+    if (!bf16 && narrow_ok(g) && batch >= 16384) return false;
+    // The expansion (two or three launches and a pass over the weights, 15 to 35
+    // us) has to pay: the line in multiply-adds of the dense contraction over
+    // whole 32-column fragments, per call against the kernels on the packed
+    // weights.  fp32: 1024 x 784 -> 256 G = 10 (2.9e9) 117 -> 61 us, 4096 x 256 ->
+    // 64 (0.94e9) 47 -> 32, 8192 x 784 -> 10 (2.9e9) 116 -> 57, 4096 x 64 -> 64
+    // (0.24e9) 19.5 -> 22; a batch of one row block has too few workgroups: 256 x
+    // 784 -> 256 (0.72e9) 40 -> 55.  bf16 cubic: 8192 x
+    // 128 -> 128 G = 100 (1.4e10) 84 -> 71, 65536 x 256 -> 256 G = 20 (1e11) 216 ->
+    // 195, 4096 x 256 -> 256 G = 20 (6e9) 55 -> 54, 5000 x 33 -> 77 G = 30 (5e8) 19
+    // -> 29; bf16 of degree 1 or 2, whose other kernel evaluates every column by a
+    // run-time degree: 4096 x 64 -> 64 G = 20 (4e8) 50 -> 22.
+    const double madds = (double)batch * in * ((out + 31) / 32 * 32) * (g.nb + 1);
+    if (batch < 1024 || madds < (!bf16 ? 5e8 : g.kdeg == 3 ? 1e10 : 2e8)) return false;
+    w->nfw = out <= 64 ? 1 : out <= 128 ? 2 : 4;
+    w->bn = 64 * w->nfw;
+    w->ntiles = (out + w->bn - 1) / w->bn;
+    w->nbk = (g.nb + 1 + 15) / 16;
+    const int64_t steps = (int64_t)g.npairs * w->nbk;
+    w->spb = bf16 ? 2 : 1;
+    const int64_t step_bytes = (int64_t)win_step_units(bf16, w->bn) * 16;
+    const int64_t stages = (steps + w->spb - 1) / w->spb;
+    if (stages * w->spb * step_bytes >= 0x100000000LL) return false;
+    w->steps = (int)steps;
+    w->stages = (int)stages;
+    w->rblocks = (batch + 255) / 256;
+    if (w->rblocks > 0x7fffffffLL || w->ntiles > 65535) return false;
+    // K splits towards a workgroup per CU, of at least eight stages each
+    const int64_t wgs = w->rblocks * w->ntiles;
+    int64_t ks = std::max<int64_t>(1, std::min<int64_t>(256 / wgs, stages / 8));
+    const int64_t most = ((int64_t)64 << 20) / (batch * (int64_t)out * 4);
+    ks = std::max<int64_t>(1, std::min<int64_t>(ks, most));
+    int64_t sps = (stages + ks - 1) / ks;
+    sps = (sps + w->nbk - 1) / w->nbk * w->nbk;
+    w->sps = (int)std::min<int64_t>(sps, 0x7fffffff);
+    w->ks = (int)((stages + sps - 1) / sps);
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        const size_t at = off;
+        off = (off + n + 255) & ~(size_t)255;
+        return at;
+    };
+    w->off_w = take((size_t)w->ntiles * (size_t)(stages * w->spb * step_bytes));
+    w->off_cm = take(bf16 ? 0 : (size_t)kColGroups * out * 8);
+    w->off_us = take(bf16 ? 0 : (size_t)w->ntiles * w->bn * 4);
+    w->off_flag = take((size_t)w->ntiles * w->steps * 4);
+    w->off_p = take(w->ks > 1 ? (size_t)w->ks * (size_t)batch * out * 4 : 0);
+    w->bytes = off;
+    return true;
+}
+
+hipError_t launch_window(bool bf16, const LayerGeom& g, const WinGeom& w, WinArgs a,
+                         hipStream_t s) {
+    a.off_w = w.off_w;
+    a.off_cm = w.off_cm;
+    a.off_us = w.off_us;
+    a.off_flag = w.off_flag;
+    a.off_p = w.off_p;
+    a.npairs = g.npairs;
+    a.nbk = w.nbk;
+    a.steps = w.steps;
+    a.steps_pad = w.stages * w.spb;
+    a.stages = w.stages;
+    a.sps = w.sps;
+    a.ks = w.ks;
+    a.bn = w.bn;
+    a.step_u = win_step_units(bf16, w.bn);
+    a.pk_ntile = 32 * g.nf;
+    a.pk_nblk_pad = g.nblk_pad;
+    a.pk_nsb = g.nsb;
+    const hipError_t e = bf16 ? launch_window_bf16(w, a, s) : launch_window_f32(w, a, s);
+    if (e != hipSuccess || w.ks == 1) return e;
+    return launch_split_reduce(
+        bf16, reinterpret_cast<const float*>(static_cast<const char*>(a.ws) + w.off_p), a.y,
+        a.batch * (int64_t)a.out, w.ks, s);
 }
 
 }  // namespace kan
