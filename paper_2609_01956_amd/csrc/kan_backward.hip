@@ -7,21 +7,15 @@
 //
 // Both are contractions over a dense operand and run on the matrix cores:
 //
-//   dx:  Gm = dy W^T over the outputs (Gm[b, (i, c)] for every column c of
-//        every feature), then per (row, feature) the dot product of its
-//        columns with (silu'(x), N_0'(x), ..., N_{nb-1}'(x)).  The MFMA puts
-//        the K rows in the A operand (the packed weights, staged in LDS and
-//        shared by the workgroup's eight waves) and the batch rows in the B
-//        operand (a wave's 32 rows of dy, held in registers for the whole
-//        kernel); the A rows are permuted so that each lane's 16 accumulators
-//        are 16 consecutive columns of one feature for one batch row, and the
-//        derivative contraction runs in the lane with no cross-lane step
-//        (features of more than 16 columns add the two lane halves).
-//   dW:  dW^T = A^T dy over the batch, A the forward's basis / SiLU matrix
-//        regenerated in registers (never stored), dy transposed once into
-//        the workspace so that both MFMA operands hold consecutive batch rows
-//        per lane.  The batch is split over workgroups; their fp32 partials
-//        are summed in a fixed order by a reduce kernel (deterministic).
+//   dx:  kan_bwd_dx.hip (layers of at most 16 outputs at large batches: on the
+//        vector ALUs, below).
+//   dW:  kan_bwd_dw.hip for features whose K rows divide 256 (fp32: at large
+//        batches); otherwise dw_kernel here: dW^T = A^T dy over the batch, A the
+//        forward's basis / SiLU matrix regenerated in registers (never stored), dy
+//        transposed once into the workspace so that both MFMA operands hold
+//        consecutive batch rows per lane.  The batch is split over workgroups;
+//        their fp32 partials are summed in a fixed order by a reduce kernel
+//        (deterministic).
 //
 // The derivative of the clamped cubic (eq. truncated with eq. bounded) at
 // v = u - 2 is, with a = min(|v|, 2), w = 2 - a and b = max(1 - a, 0),
@@ -83,12 +77,6 @@ template <> struct B<uint16_t> {
     }
     static constexpr int E = 8;
 };
-
-// Local K row of A-operand row i of a 32-row dx tile: rows with (i / 4) % 2 == h
-// land in lane half h of the accumulators, as local rows 16 h .. 16 h + 15.
-__host__ __device__ constexpr int dx_local_row(int i) {
-    return 16 * ((i / 4) % 2) + 4 * (i / 8) + i % 4;
-}
 
 // -------------------------------------------------------------- transposes
 
@@ -175,398 +163,6 @@ __global__ __launch_bounds__(256) void transpose64_kernel(const T* __restrict__ 
 #pragma unroll
         for (int i = 0; i < V; ++i) e[i] = tile[bl + i][cl];
         *reinterpret_cast<u32x4*>(dst + (int64_t)c * rpad + b) = __builtin_bit_cast(u32x4, e);
-    }
-}
-
-// -------------------------------------------------------------- dx packing
-
-// wtp[t][g][lane][e]: for lane (r, h) of 32-row K tile t and k-step group g,
-// the weights W[o][K row of A row r] of the group's outputs o of the lane half:
-// bf16 o = 16 g + 8 h + e (one 32x32x16 k-step), fp32 o = 8 g + 2 e + h (four
-// 32x32x2 k-steps).  W[o][(f, c)] is Wb[o][f] for c = 0, coef[o][f][c - 1] for
-// 1 <= c <= nb, else 0; rows of features past `in` and outputs past `out` are 0.
-template <typename T>
-__global__ __launch_bounds__(256) void pack_dx_kernel(const T* __restrict__ coef,
-                                                      const T* __restrict__ bw,
-                                                      T* __restrict__ wtp, int in, int out, int nb,
-                                                      int cp, int groups, int64_t units) {
-    constexpr int E = B<T>::E;
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (u >= units) return;
-    const int lane = (int)(u % 64);
-    const int g = (int)((u / 64) % groups);
-    const int64_t t = u / (64LL * groups);
-    const int r = lane & 31, h = lane >> 5;
-    const int64_t R = 32 * t + dx_local_row(r);
-    const int f = (int)(R / cp);
-    const int c = (int)(R % cp);
-    T v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int o = sizeof(T) == 2 ? 16 * g + 8 * h + e : 8 * g + 2 * e + h;
-        T w = T(0);
-        if (o < out && f < in) {
-            const int64_t row = (int64_t)o * in + f;
-            if (c == 0) w = bw[row];
-            else if (c <= nb) w = coef[row * nb + c - 1];
-        }
-        v[e] = w;
-    }
-    T* d = wtp + u * E;
-#pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = v[e];
-}
-
-// ------------------------------------------------------------------ dx
-
-template <typename T>
-struct DxArgs {
-    const T* xt;       // x transposed: [in][bpad]
-    int64_t bpad;
-    const T* dy;
-    const u32x4* wtp;  // packed weights, 16-byte units
-    T* dx;
-    float* dxp;        // per-chunk partials when the outputs take several chunks
-    int64_t batch;
-    int in, out, nb, cp, ntiles, groups, gmax;
-    int tiles_per_split;  // K tiles of a workgroup (blockIdx.z), whole features
-    float inv_h, inv_lo, xlim, a_int, a_frac;
-};
-
-// One workgroup: 8 RF 32 batch rows (eight waves of RF 32-row tiles) against
-// the K tiles of split blockIdx.z, for output chunk blockIdx.y (up to gmax
-// k-step groups, 256 outputs).  SM bounds the groups of a chunk at compile
-// time.  Every A fragment read from LDS feeds RF MFMAs.
-//
-// Pipeline (two LDS stages, two register sets, loop unrolled by two so the
-// sets are compile-time choices): LDS stage t % 2 holds tile t; during tile t
-// the MFMAs and the epilogue run, then the loads of tile t + 2 (weights, and
-// x of the lane's rows for its epilogue) go into register set t % 2 and
-// register set (t + 1) % 2, loaded a whole tile earlier, is stored to stage
-// (t + 1) % 2 before the barrier.
-template <typename T, int SM, int RF, int NW>
-__global__ __launch_bounds__(64 * NW) void dx_kernel(DxArgs<T> a) {
-    constexpr bool BF = sizeof(T) == 2;
-    constexpr int NT = 64 * NW;
-    constexpr int UPT = (SM * 64 + NT - 1) / NT;  // 16-byte units per thread per tile
-    __shared__ u32x4 lds[2][SM * 64];
-    // per wave: a lane's 16 accumulators after 4 zero floats (stride 80 bytes,
-    // so the 16-byte writes of 16 lanes fall in distinct banks; the next
-    // lane's zeros, and 4 after the last lane, follow them), read back at the
-    // four columns the clamped derivative can make nonzero
-    __shared__ u32x4 gat[NW][64 * 5 + 1];
-
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, r = lane & 31, h = lane >> 5;
-    const int64_t row0 = (int64_t)blockIdx.x * (NW * 32 * RF) + wave * (32 * RF) + r;
-    int64_t rowc[RF];
-#pragma unroll
-    for (int rf = 0; rf < RF; ++rf) {
-        const int64_t row = row0 + 32 * rf;
-        rowc[rf] = row < a.batch ? row : a.batch - 1;
-    }
-    const int ch = blockIdx.y;
-    const int g0 = ch * a.gmax;
-    const int S = min(a.gmax, a.groups - g0);
-    const int t_begin = blockIdx.z * a.tiles_per_split;
-    const int t_end = min(t_begin + a.tiles_per_split, a.ntiles);
-
-    // B operands: the lane's batch rows of dy for every k-step group of the chunk
-    u32x4 dyr[RF][SM];
-#pragma unroll
-    for (int rf = 0; rf < RF; ++rf) {
-        const T* dyrow = a.dy + rowc[rf] * a.out;
-#pragma unroll
-        for (int s = 0; s < SM; ++s) {
-            float v[B<T>::E];
-#pragma unroll
-            for (int e = 0; e < B<T>::E; ++e) {
-                const int o = BF ? (g0 + s) * 16 + 8 * h + e : (g0 + s) * 8 + 2 * e + h;
-                v[e] = (s < S && o < a.out) ? B<T>::ld(dyrow + o) : 0.0f;
-            }
-            if constexpr (BF)
-                dyr[rf][s] = u32x4{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]),
-                                   pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7])};
-            else
-                dyr[rf][s] = u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]),
-                                   __float_as_uint(v[2]), __float_as_uint(v[3])};
-        }
-    }
-
-    typedef u32x4 WSet[UPT];
-    typedef T XSet[RF];
-    // Tile t's rows are features f0(t) + h of 16 columns each (cp = 16), or
-    // columns 16 h .. 16 h + 15 of feature f0(t) (cp a multiple of 32):
-    // f0(t) is the same for the whole wave.
-    const bool cp16 = a.cp == 16;
-    auto feat0 = [&](int t) -> int { return cp16 ? 2 * t : (32 * t) / a.cp; };
-    // per-lane offsets fixed for the whole kernel: units of the weight loads,
-    // x rows (in x transposed, relative to feature f0), dx rows
-    int wl[UPT];
-#pragma unroll
-    for (int k = 0; k < UPT; ++k) wl[k] = min(tid + k * NT, S * 64 - 1);
-    int64_t xl[RF], dxo[RF];
-    bool rowok[RF];
-#pragma unroll
-    for (int rf = 0; rf < RF; ++rf) {
-        const int64_t row = row0 + 32 * rf;
-        xl[rf] = rowc[rf] + (cp16 && h ? a.bpad : 0);
-        rowok[rf] = row < a.batch;
-        dxo[rf] = (a.dxp != nullptr ? (int64_t)ch * a.batch + row : row) * a.in;
-    }
-    // Register sets: tile t's loads go to set t % L, issued L tiles before
-    // the tile and stored to LDS one tile before it, so each store waits for
-    // loads issued L - 1 tiles earlier (a tile is short: with one tile of
-    // distance the stores wait on most of a memory round trip).
-    constexpr int L = SM >= 32 ? 2 : 4;  // (32 k-steps of fp32 dy already fill the registers)
-    WSet wq[L];
-    XSet xq[L];
-    // Loads of tile t: unconditional (tiles past the split's last, units past
-    // the chunk's and features past `in` re-read valid addresses; their
-    // values are not used), so the compiler's wait before a register set is
-    // used counts only the loads issued after it.  x comes from its
-    // transpose: a lane half reads 32 consecutive rows of one feature.
-    auto issue = [&](int t, WSet& w, XSet& xs) {
-        const int tc = min(t, t_end - 1);
-        const u32x4* src = a.wtp + ((int64_t)tc * a.groups + g0) * 64;
-#pragma unroll
-        for (int k = 0; k < UPT; ++k) w[k] = src[wl[k]];
-        const T* xb = a.xt + (int64_t)feat0(tc) * a.bpad;  // (the lane half's rows: xl)
-#pragma unroll
-        for (int rf = 0; rf < RF; ++rf) xs[rf] = xb[xl[rf]];
-    };
-    auto put = [&](int buf, const WSet& w) {
-#pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-            const int u = tid + k * NT;
-            if (u < S * 64) lds[buf][u] = w[k];
-        }
-    };
-    auto to_f = [&](T v) -> float {
-        if constexpr (BF) return bf16_to_f32(v);
-        else return v;
-    };
-    auto store_dx = [&](int rf, int f, float v) {
-        if (rowok[rf] && f < a.in) {
-            if (a.dxp != nullptr)
-                a.dxp[dxo[rf] + f] = v;
-            else
-                B<T>::st(a.dx + dxo[rf] + f, v);
-        }
-    };
-
-    const int tpf = a.cp / 32;  // tiles per feature (cp >= 32)
-    float dxacc[RF];
-#pragma unroll
-    for (int rf = 0; rf < RF; ++rf) dxacc[rf] = 0.0f;
-
-    // The MFMAs of the tile in LDS stage `buf`: acc[rf][q] = Gm[row][K row of
-    // the tile's local row q (lane half h)].  Groups past S multiply zeros
-    // (the LDS rows past the chunk's are zero, and so is dyr there), so the
-    // loop has no branch and its LDS reads can run ahead of the MFMAs.
-    auto mma = [&](int buf, floatx16 (&acc)[RF]) {
-#pragma unroll
-        for (int rf = 0; rf < RF; ++rf)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[rf][q] = 0.0f;
-        const u32x4* st = lds[buf];
-        // every A fragment of the tile read before the first MFMA (bf16: the
-        // group barriers below keep them there; left to itself the compiler
-        // keeps two reads in flight and each pair of MFMAs waits on the LDS:
-        // 784 -> 256 dx 596 -> 534 us)
-        u32x4 wv[SM];
-#pragma unroll
-        for (int s = 0; s < SM; ++s) wv[s] = st[s * 64 + lane];
-#pragma unroll
-        for (int s = 0; s < SM; ++s) {
-            const u32x4 w = wv[s];
-#pragma unroll
-            for (int rf = 0; rf < RF; ++rf) {
-                if constexpr (BF) {
-                    acc[rf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, dyr[rf][s]),
-                        acc[rf], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[rf] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                            __uint_as_float(w[j]), __uint_as_float(dyr[rf][s][j]), acc[rf], 0, 0,
-                            0);
-                }
-            }
-        }
-        if constexpr (BF) {
-            __builtin_amdgcn_sched_group_barrier(0x100, SM, 0);       // the LDS reads
-            __builtin_amdgcn_sched_group_barrier(0x008, SM * RF, 0);  // then the MFMAs
-        }
-    };
-
-    // The epilogue of tile t, without stores: acc[rf][q] = Gm[row][feature f,
-    // column c0 + q].  Of the basis columns only the four with |v| < 2 have a
-    // nonzero derivative: with s the coordinate of column 0 of the feature,
-    // tau = s - floor(s) and clo = floor(s) - 1, column clo + k has u = tau +
-    // 3 - k, where the derivative of the cubic (its segment form on the span)
-    // is
-    //   k = 0: -(1 - tau)^2 / 2      k = 1: (3 tau^2 - 4 tau) / 2
-    //   k = 2: (1 + 2 tau - 3 tau^2) / 2   k = 3: tau^2 / 2.
-    // Column 0 carries the SiLU derivative.  The four accumulators are read
-    // back from a wave-private LDS copy (their index differs per lane).  xvs:
-    // the lane's x of the tile's feature, per row tile.  Returns the tile's
-    // contribution to dx per row tile in sum.
-    auto epi_sum = [&](int t, const floatx16 (&acc)[RF], const float (&xvs)[RF],
-                       float (&sum)[RF]) {
-        const int fu = feat0(t);
-        const int f = cp16 ? fu + h : fu;
-        const int c0 = cp16 ? 0 : 32 * t - fu * a.cp + 16 * h;
-        char* gl = reinterpret_cast<char*>(gat[wave]) + lane * 80;
-#pragma unroll
-        for (int rf = 0; rf < RF; ++rf) {
-            const float xv = f < a.in ? xvs[rf] : 0.0f;
-            // coordinate of column c0 (its integer offset folded into the fma),
-            // clamped to keep the window index small for far-out inputs; +-Inf
-            // lands outside every column, NaN is carried by the SiLU term
-            const float sc = __builtin_amdgcn_fmed3f(
-                __builtin_fmaf(xv, a.inv_h, a.a_int + 1.0f - (float)c0) +
-                    coord_lo(xv, a.xlim, a.inv_lo, a.a_frac),
-                -8.0f, 24.0f);
-            const float fl = __builtin_floorf(sc);
-            const float tau = sc - fl;
-            const float t2 = tau * tau;
-            float d[4];
-            d[0] = -0.5f * (1.0f - tau) * (1.0f - tau);
-            d[1] = __builtin_fmaf(1.5f, t2, -2.0f * tau);
-            d[2] = __builtin_fmaf(-1.5f, t2, __builtin_fmaf(tau, 1.0f, 0.5f));
-            d[3] = 0.5f * t2;
-            // the lane's 16 columns after its 4 zeros; the SiLU column (c = 0)
-            // is not a basis column and reads as 0 too
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                *reinterpret_cast<floatx4*>(gl + 16 + 16 * m) =
-                    floatx4{m == 0 && c0 == 0 ? 0.0f : acc[rf][4 * m], acc[rf][4 * m + 1],
-                            acc[rf][4 * m + 2], acc[rf][4 * m + 3]};
-            // window columns q = qlo .. qlo + 3 relative to c0: columns outside
-            // the lane's 16 read the zeros around them (padding columns past
-            // nb hold exact zeros: their weights are 0), and a window wholly
-            // outside is moved onto 4 zeros
-            const int qlo = min(max((int)fl - 1, -4), 16);
-            const float* gw = reinterpret_cast<const float*>(gl + 16 + 4 * qlo);
-            float sb = 0.0f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) sb = __builtin_fmaf(gw[k], d[k], sb);
-            sum[rf] = __builtin_fmaf(c0 == 0 ? acc[rf][0] : 0.0f, silu_deriv(xv), a.inv_h * sb);
-        }
-    };
-    // The tile's stores: dx of its feature, or (features of two tiles) the
-    // running sum, stored at the feature's last tile.
-    auto epi_store = [&](int t, const float (&sum)[RF]) {
-        const int f = cp16 ? feat0(t) + h : feat0(t);
-        if (a.cp == 16) {
-#pragma unroll
-            for (int rf = 0; rf < RF; ++rf) store_dx(rf, f, sum[rf]);
-        } else {
-#pragma unroll
-            for (int rf = 0; rf < RF; ++rf) dxacc[rf] += sum[rf];
-            if ((t + 1) % tpf == 0) {  // the feature's last tile: add the two halves
-#pragma unroll
-                for (int rf = 0; rf < RF; ++rf) {
-                    const float tot = dxacc[rf] + __shfl_xor(dxacc[rf], 32);
-                    if (h == 0) store_dx(rf, f, tot);
-                    dxacc[rf] = 0.0f;
-                }
-            }
-        }
-    };
-    auto xfloat = [&](const XSet& xs, float (&xv)[RF]) {
-#pragma unroll
-        for (int rf = 0; rf < RF; ++rf) xv[rf] = to_f(xs[rf]);
-    };
-
-    // LDS rows of groups past the chunk's are never written by put: zero them
-    // once (the MFMAs of those groups then add exact zeros).  Likewise the
-    // zeros around each lane's gather slot, never written after this.
-    for (int u = S * 64 + tid; u < SM * 64; u += NT) {
-        lds[0][u] = u32x4{0u, 0u, 0u, 0u};
-        lds[1][u] = u32x4{0u, 0u, 0u, 0u};
-    }
-    {
-        char* gw0 = reinterpret_cast<char*>(gat[wave]);
-        *reinterpret_cast<u32x4*>(gw0 + lane * 80) = u32x4{0u, 0u, 0u, 0u};
-        if (lane == 63) *reinterpret_cast<u32x4*>(gw0 + 64 * 80) = u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int j = 0; j < L; ++j) issue(t_begin + j, wq[j], xq[j]);
-    put(0, wq[0]);
-    __syncthreads();
-    if constexpr (BF) {
-        // bf16 (a tile's MFMAs are short next to its epilogue): software
-        // pipelined over two accumulator sets.  The iteration of tile t issues
-        // its MFMAs and computes tile t - 1's epilogue in the same straight-line
-        // code, so that VALU and LDS work overlaps the MFMAs; the stores
-        // follow.  x of tile t is kept as floats (xp) before its register set
-        // is reloaded.  Tile t_begin + i uses LDS stage i % 2, register set
-        // i % L and accumulator set i % 2 (L is even).
-        floatx16 acc[2][RF];
-        float xp[2][RF];
-        float sum[RF];
-        if (t_begin < t_end) {  // the first tile: MFMAs only
-            mma(0, acc[0]);
-            xfloat(xq[0], xp[0]);
-            issue(t_begin + L, wq[0], xq[0]);
-            if (t_begin + 1 < t_end) put(1, wq[1 % L]);
-            __syncthreads();
-        }
-#pragma unroll 1
-        for (int tb = t_begin + 1; tb < t_end; tb += L) {
-            bool done = false;
-            StaticFor<0, L>::run([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                constexpr int i = j + 1;  // t - t_begin, mod L
-                constexpr int p = i & 1;
-                const int t = tb + j;
-                if (done || t >= t_end) {
-                    done = true;
-                    return;
-                }
-                mma(p, acc[p]);
-                epi_sum(t - 1, acc[p ^ 1], xp[p ^ 1], sum);
-                epi_store(t - 1, sum);
-                xfloat(xq[i % L], xp[p]);
-                issue(t + L, wq[i % L], xq[i % L]);
-                if (t + 1 < t_end) put((i + 1) & 1, wq[(i + 1) % L]);
-                __syncthreads();
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        }
-        const int tl = t_end - 1;  // the last tile's epilogue
-        if (tl >= t_begin) {
-            if (((tl - t_begin) & 1) == 0) epi_sum(tl, acc[0], xp[0], sum);
-            else epi_sum(tl, acc[1], xp[1], sum);
-            epi_store(tl, sum);
-        }
-    } else {
-        // tile t = t_begin + L i + j: LDS stage j % 2, register set j
-#pragma unroll 1
-        for (int tb = t_begin; tb < t_end; tb += L) {
-            bool done = false;
-            StaticFor<0, L>::run([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                const int t = tb + j;
-                if (done || t >= t_end) {
-                    done = true;
-                    return;
-                }
-                floatx16 acc[RF];
-                float xv[RF], sum[RF];
-                mma(j & 1, acc);
-                xfloat(xq[j], xv);
-                epi_sum(t, acc, xv, sum);
-                epi_store(t, sum);
-                issue(t + L, wq[j], xq[j]);
-                if (t + 1 < t_end) put((j + 1) & 1, wq[(j + 1) % L]);
-                __syncthreads();
-                __builtin_amdgcn_sched_barrier(0);  // (tiles are not interleaved)
-            });
-        }
     }
 }
 
@@ -874,9 +470,20 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict_
     const int64_t of = u / (nb + 1);  // o * in + f
     const int f = (int)(of % in);
     const int o = (int)(of / in);
+    // (16 loads in flight before their adds, in split order: a small layer's few
+    // workgroups wait on one memory round trip per 16 splits; the +0 that stands in
+    // for a split past the last leaves the sum bitwise unchanged)
+    constexpr int kBatch = 16;
+    const float* p = P + (int64_t)o * kr + (int64_t)f * cp + c;
     float s = 0.0f;
-    for (int k = 0; k < split; ++k)
-        s += P[((int64_t)k * out32 + o) * kr + (int64_t)f * cp + c];
+    for (int k0 = 0; k0 < split; k0 += kBatch) {
+        float t[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            t[i] = k0 + i < split ? p[(int64_t)(k0 + i) * out32 * kr] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) s += t[i];
+    }
     s *= 2.0f;
     if (c == 0)
         B<T>::st(dbw + of, s);
@@ -885,33 +492,6 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict_
 }
 
 // ---------------------------------------------------------------- launches
-
-template <typename T, int SM, int RF, int NW = 8>
-hipError_t launch_dx_sm(const BwdGeom& g, const DxArgs<T>& d, hipStream_t s) {
-    constexpr int BM = NW * 32 * RF;
-    const dim3 grid((unsigned)((d.batch + BM - 1) / BM), (unsigned)g.nchunk,
-                    (unsigned)g.dx_ksplit);
-    hipLaunchKernelGGL((dx_kernel<T, SM, RF, NW>), grid, dim3(64 * NW), 0, s, d);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_dx(const BwdGeom& g, const DxArgs<T>& d, hipStream_t s) {
-    const int sm = min(g.groups, g.gmax);  // groups of the largest chunk
-    // two row tiles per wave while their dy registers stay within 64
-    if (g.dx_rf == 2) {
-        if (sm <= 1) return launch_dx_sm<T, 1, 2>(g, d, s);
-        if (sm <= 2) return launch_dx_sm<T, 2, 2>(g, d, s);
-        if (sm <= 4) return launch_dx_sm<T, 4, 2>(g, d, s);
-        if (sm <= 8) return launch_dx_sm<T, 8, 2>(g, d, s);
-        return hipErrorInvalidValue;
-    }
-    if (sm <= 16) return launch_dx_sm<T, 16, 1>(g, d, s);
-    if constexpr (sizeof(T) == 4) {
-        if (sm <= 32) return launch_dx_sm<T, 32, 1>(g, d, s);
-    }
-    return hipErrorInvalidValue;
-}
 
 template <typename T>
 hipError_t launch_dw(const BwdGeom& g, const DwArgs<T>& d, hipStream_t s) {
@@ -1200,6 +780,10 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
             hipLaunchKernelGGL(transpose64_kernel<T>,
                                dim3((unsigned)((g.bpad + 63) / 64), (unsigned)((drows + 63) / 64)),
                                dim3(256), 0, s, x, xt, a.batch, a.in, g.bpad, drows, vec);
+        } else if (g.dw2 && a.dcoef != nullptr) {
+            e = launch_transpose_max(x, xt, reinterpret_cast<float*>(ws + g.off_xm), a.batch, a.in,
+                                     g.bpad, s);
+            if (e != hipSuccess) return e;
         } else {
             hipLaunchKernelGGL((transpose_kernel<T, false>),
                                dim3((unsigned)(g.bpad / 32), (unsigned)((a.in + 31) / 32)),
@@ -1233,20 +817,17 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
         d.a_frac = a.a_frac;
         if ((e = launch_narrow_dx<T>(g, d, s)) != hipSuccess) return e;
     } else if (a.dx != nullptr && a.batch > 0) {
-        T* wtp = reinterpret_cast<T*>(ws + g.off_wt);
-        const int64_t units = (int64_t)g.ntiles * g.groups * 64;
-        hipLaunchKernelGGL(pack_dx_kernel<T>, dim3((unsigned)((units + 255) / 256)), dim3(256), 0,
-                           s, static_cast<const T*>(a.coef), static_cast<const T*>(a.bw), wtp,
-                           a.in, a.out, g.nb, g.cp, g.groups, units);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        DxArgs<T> d;
+        Dx2Args d;
         d.xt = xt;
-        d.bpad = g.bpad;
-        d.dy = static_cast<const T*>(a.dy);
-        d.wtp = reinterpret_cast<const u32x4*>(wtp);
-        d.dx = static_cast<T*>(a.dx);
+        d.dy = a.dy;
+        d.coef = a.coef;
+        d.bw = a.bw;
+        d.wtp = reinterpret_cast<u32x4*>(ws + g.off_wt);
+        d.wexp = reinterpret_cast<int*>(ws + g.off_we);
+        d.dx = a.dx;
         d.dxp = g.nchunk > 1 ? reinterpret_cast<float*>(ws + g.off_dxp) : nullptr;
         d.batch = a.batch;
+        d.bpad = g.bpad;
         d.in = a.in;
         d.out = a.out;
         d.nb = g.nb;
@@ -1254,17 +835,18 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
         d.ntiles = g.ntiles;
         d.groups = g.groups;
         d.gmax = g.gmax;
+        d.nchunk = g.nchunk;
         d.tiles_per_split = g.dx_tiles_per_split;
         d.inv_h = a.inv_h;
         d.inv_lo = a.inv_lo;
         d.xlim = a.xlim;
         d.a_int = a.a_int;
         d.a_frac = a.a_frac;
-        if ((e = launch_dx<T>(g, d, s)) != hipSuccess) return e;
+        if ((e = launch_dx_split(sizeof(T) == 2, g, d, s)) != hipSuccess) return e;
         if (g.nchunk > 1) {
             const int64_t n = a.batch * a.in;
             hipLaunchKernelGGL(dx_reduce_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256),
-                               0, s, d.dxp, d.dx, n, g.nchunk);
+                               0, s, d.dxp, static_cast<T*>(a.dx), n, g.nchunk);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }
@@ -1280,6 +862,11 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
                                         (unsigned)((g.out32 + 63) / 64)),
                                    dim3(256), 0, s, static_cast<const T*>(a.dy), dyt, a.batch,
                                    a.out, g.bpad, g.out32, vec);
+            } else if (g.dw2) {
+                e = launch_transpose_max(reinterpret_cast<const float*>(a.dy), reinterpret_cast<float*>(dyt),
+                                         reinterpret_cast<float*>(ws + g.off_dm), a.batch, a.out,
+                                         g.bpad, s);
+                if (e != hipSuccess) return e;
             } else {
                 hipLaunchKernelGGL((transpose_kernel<T, true>),
                                    dim3((unsigned)(g.bpad / 32), (unsigned)(g.out32 / 32)),
@@ -1287,6 +874,28 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
                                    a.out, g.bpad);
             }
             if ((e = hipGetLastError()) != hipSuccess) return e;
+            if (g.dw2) {
+                Dw2Args d;
+                d.xt = xt;
+                d.dyt = dyt;
+                d.xmax = reinterpret_cast<const float*>(ws + g.off_xm);
+                d.dymax = reinterpret_cast<const float*>(ws + g.off_dm);
+                d.P = P;
+                d.bpad = g.bpad;
+                d.in = a.in;
+                d.in32 = (a.in + 31) / 32 * 32;
+                d.out32 = g.out32;
+                d.nb = g.nb;
+                d.cp = g.cp;
+                d.kr = g.kr;
+                d.rows_per_split = g.rows_per_split;
+                d.inv_h = a.inv_h;
+                d.inv_lo = a.inv_lo;
+                d.xlim = a.xlim;
+                d.a_int = a.a_int;
+                d.a_frac = a.a_frac;
+                if ((e = launch_dw_split(sizeof(T) == 2, g, d, s)) != hipSuccess) return e;
+            } else {
             DwArgs<T> d;
             d.xt = xt;
             d.dyt = dyt;
@@ -1305,6 +914,7 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
             d.a_int = a.a_int;
             d.a_frac = a.a_frac;
             if ((e = launch_dw<T>(g, d, s)) != hipSuccess) return e;
+            }
             split = g.split;
         }
         const int64_t n = (int64_t)a.out * a.in * (g.nb + 1);
@@ -1328,9 +938,8 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     g->ntiles = (int)ntiles;
     g->kr = (int)(32 * ntiles);
     g->out32 = (out + 31) / 32 * 32;
-    const int go = bf16 ? 16 : 8;
-    g->groups = (out + go - 1) / go;
-    g->gmax = 256 / go;
+    g->groups = (out + 15) / 16;
+    g->gmax = 16;
     g->nchunk = (g->groups + g->gmax - 1) / g->gmax;
     if (g->out32 <= 32) { g->oh = 1; g->nfw = 1; }
     else if (g->out32 <= 64) { g->oh = 2; g->nfw = 1; }
@@ -1338,13 +947,21 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     else { g->oh = 2; g->nfw = 4; }
     g->kt = 256;
     g->ktiles = (g->kr + g->kt - 1) / g->kt;
+    // whole features per 256 K rows: the kernel of kan_bwd_dw.hip, whose fp32 form
+    // takes at most 128 outputs per workgroup (and keeps maxima per 64 rows)
+    // (fp32 from 8192 rows: below, its sums are short and the fp32 instruction's
+    // kernel as exact and, with few workgroups, as fast: 1024 x 2 -> 5 59 us per
+    // training step against 64)
+    g->dw2 = g->cp <= 256 && 256 % g->cp == 0 && (bf16 || batch >= 8192);
+    const int wide = (g->out32 + g->oh * g->nfw * 32 - 1) / (g->oh * g->nfw * 32);
+    if (g->dw2 && !bf16 && g->nfw == 4) g->nfw = 2;
     const int ot = g->oh * g->nfw * 32;
     g->otiles = (g->out32 + ot - 1) / ot;
     if (g->otiles > 65535) return false;
-    // dx: two 32-row tiles per wave while their dy registers stay within 64
-    // (up to 8 k-step groups: 128 outputs bf16, 64 fp32), and the K tiles split over
-    // workgroups (whole features each) until the grid fills the chip
-    g->dx_rf = (g->groups < g->gmax ? g->groups : g->gmax) <= 8 ? 2 : 1;
+    // dx: two 32-row tiles per wave while their dy registers stay within 128 (fp32:
+    // up to 128 outputs), and the K tiles split over workgroups (whole features
+    // each) until the grid fills the chip
+    g->dx_rf = bf16 || std::min(g->groups, g->gmax) <= 8 ? 2 : 1;
     {
         const int tpf = g->cp == 16 ? 1 : g->cp / 32;
         g->dx_bm = 32 * g->dx_rf * 8;  // rows per workgroup (eight waves)
@@ -1360,21 +977,22 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
         g->dx_ksplit = (int)((g->ntiles + tps - 1) / tps);
         if (g->dx_ksplit > 65535 || rblocks > 0x7fffffffLL) return false;
     }
-    g->bpad = (batch + 31) / 32 * 32;
-    const int64_t nck = g->bpad / 32;
+    const int rq = !bf16 && g->dw2 ? 64 : 32;  // row quantum
+    g->bpad = (batch + rq - 1) / rq * rq;
+    const int64_t nck = g->bpad / rq;
     // Batch splits of the weight gradient: towards 256 workgroups, in bf16
     // towards 512 while the splits' fp32 partial sums stay within 16 MB (the
     // 256 -> 10 layer at batch 65536: 30 splits, 121 -> 105 us; the wide
     // layers keep theirs; fp32 256 -> 10 with 30 splits: 3% slower)
-    int64_t split = (bf16 ? 512 : 256) / ((int64_t)g->ktiles * g->otiles);
+    int64_t split = (bf16 ? 512 : 256) / ((int64_t)g->ktiles * wide);
     if (split < 1) split = 1;
-    while (split > 1 && split * g->ktiles * g->otiles > 256 &&
+    while (split > 1 && split * g->ktiles * wide > 256 &&
            split * g->out32 * (int64_t)g->kr * 4 > ((int64_t)16 << 20))
         --split;
     if (split > nck) split = nck > 0 ? nck : 1;
     const int64_t rps_chunks = nck > 0 ? (nck + split - 1) / split : 1;
-    if (rps_chunks * 32 > 0x7fffffffLL) return false;
-    g->rows_per_split = (int)(rps_chunks * 32);
+    if (rps_chunks * rq > 0x7fffffffLL) return false;
+    g->rows_per_split = (int)(rps_chunks * rq);
     g->split = nck > 0 ? (int)((nck + rps_chunks - 1) / rps_chunks) : 0;
     if (g->split > 65535 || (batch + 255) / 256 > 0x7fffffffLL) return false;
     // dx of narrow layers (at most 16 outputs, from 16384 rows) on the vector
@@ -1387,13 +1005,19 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     const size_t es = bf16 ? 2 : 4;
     size_t off = 0;
     g->off_wt = off;
-    size_t wt_bytes = (size_t)g->ntiles * g->groups * 1024;
+    size_t wt_bytes = (size_t)g->ntiles * g->groups * (bf16 ? 1024 : 2048);
     if (g->nx) wt_bytes = std::max(wt_bytes, (size_t)g->nfeat * g->ncw * g->nrs * es);
     off = align256(off + wt_bytes);
+    g->off_we = off;
+    if (!bf16) off = align256(off + (size_t)g->ntiles * g->nchunk * 4);
     g->off_dyt = off;
-    off = align256(off + (size_t)g->out32 * (size_t)g->bpad * es);
+    off = align256(off + (size_t)(g->dw2 ? g->otiles * ot : g->out32) * (size_t)g->bpad * es);
     g->off_xt = off;
     off = align256(off + (size_t)((in + 31) / 32 * 32) * (size_t)g->bpad * es);
+    g->off_xm = off;
+    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)((in + 31) / 32 * 32) * 4);
+    g->off_dm = off;
+    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)g->out32 * 4);
     g->off_p = off;
     off = align256(off + (size_t)(g->split > 0 ? g->split : 1) * g->out32 * (size_t)g->kr * 4);
     g->off_dxp = off;

@@ -1,0 +1,477 @@
+// kan_bwd_dw.hip -- weight gradients of the KAN layer on the matrix cores
+// (eq. kan_forward differentiated):
+//
+//   dC[o, i, j] = sum_b dy[b, o] N_j(x[b, i]),   dWb[o, i] = sum_b dy[b, o] silu(x[b, i])
+//
+// as dW^T = A^T dy over the batch, for layers whose cp K rows per feature divide
+// 256 (cp a power of two: every workgroup's 256 K rows are whole features).
+// bf16: one bf16 operand each.  fp32: both operands as two fp16 terms (what the
+// first leaves, rounded again: 22 bits and a sign), three products (the fourth
+// is below 2^-22 of the first), exact in fp32, fp32 accumulation: 96 cycles per
+// 16 rows of a 32 x 32 tile where the fp32 matrix instruction takes 512 (784 ->
+// 256 at 16384 rows: 794 -> 312 us; relative error against float64 6.2e-7 ->
+// 4.0e-7).  dy is
+// scaled per output and SiLU values per feature by the power of two that brings
+// the largest of the workgroup's rows to 2^12 (from the maxima that the
+// transposition leaves per 64 rows), basis values by 2^12.  An output with a
+// non-finite dy, or a SiLU row with an infinite value, has a non-finite gradient
+// whatever the other rows hold: those are computed apart at the end.
+//
+// Per chunk of 32 batch rows the workgroup stages dy (transposed) and the A
+// operand in LDS, double-buffered.  A is built once per workgroup: a thread owns
+// one (row, feature), writes the four window columns and the SiLU column and
+// clears the four it wrote two chunks before in the same stage; everything else
+// stays 0.  The window is clamped to the feature's columns 1 .. cp - 4: what it
+// then takes in is exactly 0, or a padding row past nb, which nobody reads; so
+// the four K rows are consecutive and one address serves all of them.
+#include "kan_internal.h"
+
+namespace kan {
+
+namespace {
+
+constexpr int kThreads = 512;
+constexpr int kBasisExp = 12;
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ float half_silu_w(float x) {
+    return x * __builtin_amdgcn_rcpf(__builtin_fmaf(__expf(-x), 2.0f, 2.0f));
+}
+
+// Exponent of a maximum (of finite values): scaling by 2^(12 - e) brings it to [2^12, 2^13).
+__device__ __forceinline__ int max_exp(float m) {
+    return (int)((__float_as_uint(m) >> 23) & 0xffu) - 127;
+}
+
+// ------------------------------------------------------- transposition, fp32
+
+// dst[c][b] = src[b][c], zero-padded to ceil(cols / 32) * 32 rows and rpad (a
+// multiple of 64) columns, in tiles of 64 rows by 32 columns; and per tile the
+// largest finite |value| of each column, with the sign bit set if a value is not
+// finite: vmax[b / 64][c], c < ceil(cols / 32) * 32.
+__global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restrict__ src,
+                                                            float* __restrict__ dst,
+                                                            float* __restrict__ vmax,
+                                                            int64_t rows, int cols, int64_t rpad) {
+    __shared__ float tile[64][33];
+    __shared__ float red[8][33];
+    const int64_t b0 = (int64_t)blockIdx.x * 64;
+    const int c0 = blockIdx.y * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    float m = 0.0f;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int64_t b = b0 + ty + 8 * k;
+        const float v = (b < rows && c0 + tx < cols) ? src[b * cols + c0 + tx] : 0.0f;
+        tile[ty + 8 * k][tx] = v;
+        const float av = __builtin_fabsf(v);
+        const bool fin = av < __builtin_inff();
+        m = __builtin_fmaxf(m, fin ? av : 0.0f);
+        bad |= !fin;
+    }
+    red[ty][tx] = bad ? -m : m;
+    if (bad && m == 0.0f) red[ty][tx] = -0.0f;
+    __syncthreads();
+    const int bl = threadIdx.x & 63, cq = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int cl = cq + 4 * k;
+        dst[(int64_t)(c0 + cl) * rpad + b0 + bl] = tile[bl][cl];
+    }
+    if (threadIdx.x < 32) {
+        uint32_t s = 0;
+        float mx = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float v = red[k][threadIdx.x];
+            mx = __builtin_fmaxf(mx, __builtin_fabsf(v));
+            s |= __float_as_uint(v) & 0x80000000u;
+        }
+        vmax[(int64_t)blockIdx.x * (gridDim.y * 32) + c0 + threadIdx.x] =
+            __uint_as_float(__float_as_uint(mx) | s);
+    }
+}
+
+// -------------------------------------------------------------------- kernel
+
+// FULL: cp = 16, so every thread owns a (row, feature) of each chunk.
+template <typename T, int OH, int NFW, bool FULL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void dw_split_kernel(Dw2Args a) {
+    constexpr bool BF = sizeof(T) == 2;
+    constexpr int NT = BF ? 1 : 2;              // terms per operand
+    constexpr int RF = OH, KG = 8 / OH;
+    constexpr int KT = 256;
+    constexpr int OT = OH * NFW * 32;
+    constexpr int AROW = 80;                    // bytes of an A row: 32 values and 16 of padding
+    constexpr int UR = BF ? 4 : 8;              // 16-byte loads of a chunk's 32 dy values
+    constexpr int DU = (OT * UR + kThreads - 1) / kThreads;
+    static_assert(KG * RF * 32 == KT, "K rows");
+    // dy rows of 64 bytes, their 16-byte units permuted by the row so that a
+    // fragment read of 16 rows falls in distinct banks (A rows: by the padding)
+    __shared__ u32x4 dys[2][NT][OT * 4];
+    __shared__ u32x4 as[2][NT][KT * AROW / 16];
+    __shared__ int nanf[16];
+    __shared__ int exd[BF ? 1 : OT], exs[BF ? 1 : 16];  // scale exponents; bit 16: non-finite
+
+    const T* __restrict__ xt = static_cast<const T*>(a.xt);
+    const T* __restrict__ dyt = static_cast<const T*>(a.dyt);
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63, r = lane & 31, h = lane >> 5;
+    const int kg = wave / OH, oh = wave % OH;
+    const int kt0 = blockIdx.x * KT, ot0 = blockIdx.z * OT;
+    const int F0 = kt0 / a.cp, nfeat = FULL ? 16 : KT / a.cp;
+    const int64_t b_begin = (int64_t)blockIdx.y * a.rows_per_split;
+    const int64_t b_end = min(b_begin + a.rows_per_split, a.bpad);
+    const int nchunks = (int)((b_end - b_begin) / 32);
+
+    if (tid < 16) nanf[tid] = 0;
+    for (int i = tid; i < 2 * NT * KT * AROW / 16; i += kThreads)
+        (&as[0][0][0])[i] = u32x4{0u, 0u, 0u, 0u};
+    if constexpr (!BF) {
+        // maxima over the split's rows
+        const int64_t m0 = b_begin / 64, m1 = (b_end + 63) / 64;
+        for (int i = tid; i < OT + 16; i += kThreads) {
+            const bool isx = i >= OT;
+            const int c = isx ? F0 + i - OT : ot0 + i;
+            const int w = isx ? a.in32 : a.out32;
+            const float* src = isx ? a.xmax : a.dymax;
+            float m = 0.0f;
+            uint32_t s = 0;
+            if (c < w)
+                for (int64_t k = m0; k < m1; ++k) {
+                    const float v = src[k * w + c];
+                    m = __builtin_fmaxf(m, __builtin_fabsf(v));
+                    s |= __float_as_uint(v) >> 31;
+                }
+            // (low half: the exponent, biased by 512)
+            const int e = (max_exp(m) + 512) | (int)(s << 16);
+            if (isx) exs[i - OT] = e;
+            else exd[i] = e;
+        }
+    }
+    __syncthreads();
+
+    // the thread's (row, feature) of each chunk, and its LDS place in an A row
+    const int bl = tid & 31, fl = tid >> 5;
+    const bool own = FULL || fl < nfeat;
+    const int fx = min(F0 + min(fl, nfeat - 1), a.in - 1);
+    const bool pad_f = F0 + fl >= a.in;
+    const T* xsrc = xt + (int64_t)fx * a.bpad + b_begin + bl;
+    const uint32_t abase = (uint32_t)(min(fl, nfeat - 1) * a.cp * AROW + bl * 2);
+    const float cmax = (float)(a.cp - 4);
+    int sscale = 0;
+    if constexpr (!BF) sscale = 12 - ((exs[min(fl, nfeat - 1)] & 0xffff) - 512);
+    // dy units of the thread: outputs ol + k kThreads / UR, 16-byte load w of each
+    // output's 32 values (the transposed dy has rows up to the last tile's end:
+    // what those past out32 hold is not used)
+    constexpr int KO = kThreads / UR;
+    static_assert(KO % 16 == 0, "the units' permutation is the same for every k");
+    const int ol0 = tid / UR, w0 = tid % UR;
+    const bool dlast = (OT * UR) % kThreads == 0 || ol0 < OT;  // (OT < KO: some threads idle)
+    const T* dsrc = dyt + (int64_t)(ot0 + (dlast ? ol0 : 0)) * a.bpad + b_begin +
+                    w0 * (16 / (int)sizeof(T));
+    const uint32_t dput = (uint32_t)(ol0 * 64 + (((BF ? w0 : w0 / 2) ^ ((ol0 >> 2) & 3)) * 16) +
+                                     (BF ? 0 : (w0 & 1) * 8));
+    const int64_t dstep = (int64_t)KO * a.bpad;
+
+    // dy of the next chunk: bf16 in two register sets, loaded two chunks ahead;
+    // fp32 in one (its registers are short), loaded when the former was staged
+    constexpr int ND = BF ? 2 : 1;
+    typedef u32x4 DSet[DU];
+    DSet dq[ND];
+    T xq[2];
+    uint32_t prev[2];  // window address written two chunks ago in each stage
+    prev[0] = prev[1] = abase + AROW;
+    bool nanx = false;
+    auto issue_dy = [&](int ck, DSet& d) {
+        const int64_t b0 = 32 * (int64_t)min(ck, nchunks - 1);
+#pragma unroll
+        for (int k = 0; k < DU; ++k)
+            d[k] = *reinterpret_cast<const u32x4*>(dsrc + b0 + k * dstep);
+    };
+    auto issue_x = [&](int ck, T& xs) { xs = xsrc[32 * (int64_t)min(ck, nchunks - 1)]; };
+
+    // Staging of a chunk in parts, placed between the MFMAs of the other stage:
+    // parts 0 .. 3 the A values, parts 4 .. 3 + DU a dy unit each.
+    struct Gen {
+        float x, lo, d, sl, bv[4];
+        uint32_t adr;
+    };
+    Gen gn;
+    auto st16 = [&](int buf, int t, uint32_t adr, uint16_t v) {
+        *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(&as[buf][t][0]) + adr) = v;
+    };
+    auto stage_part = [&](auto part, int buf, const DSet& d, T xs,
+                          uint32_t& pv) __attribute__((always_inline)) {
+        constexpr int P = decltype(part)::value;
+        if constexpr (P >= 4) {
+            constexpr int k = P - 4;
+            if (dlast) {
+                if constexpr (BF) {
+                    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&dys[buf][0][0]) + dput + k * (KO * 64)) =
+                        d[k];
+                } else {
+                    const int ds = 12 + 512 - (exd[ol0 + k * KO] & 0xffff);
+                    f16x4_t t0, t1;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        // (a non-finite dy becomes a finite one: its output is computed apart)
+                        const float v = __builtin_amdgcn_fmed3f(
+                            __builtin_ldexpf(__uint_as_float(d[k][e]), ds), -60000.0f, 60000.0f);
+                        t0[e] = (_Float16)v;
+                        t1[e] = (_Float16)(v - (float)t0[e]);
+                    }
+                    *reinterpret_cast<u32x2_t*>(reinterpret_cast<char*>(&dys[buf][0][0]) + dput + k * (KO * 64)) =
+                        __builtin_bit_cast(u32x2_t, t0);
+                    *reinterpret_cast<u32x2_t*>(reinterpret_cast<char*>(&dys[buf][1][0]) + dput + k * (KO * 64)) =
+                        __builtin_bit_cast(u32x2_t, t1);
+                }
+            }
+        } else if (own) {
+            if constexpr (P == 0) {
+                float x;
+                if constexpr (BF) x = bf16_to_f32(xs);
+                else x = xs;
+                x = pad_f ? 0.0f : x;
+                gn.x = x;
+                nanx |= x != x;
+                gn.lo = coord_lo(x, a.xlim, a.inv_lo, a.a_frac);
+                const float sv = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f) + gn.lo;
+                const float cf = __builtin_amdgcn_fmed3f(__builtin_floorf(sv) - 1.0f, 1.0f, cmax);
+                gn.d = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - cf) + gn.lo;
+                gn.adr = abase + __umul24((uint32_t)(int)cf, (uint32_t)AROW);
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) st16(buf, t, pv + m * AROW, 0);
+                pv = gn.adr;
+            } else if constexpr (P == 1) {
+                gn.sl = half_silu_w(gn.x);
+                gn.bv[0] = half_basis(gn.d);
+                gn.bv[1] = half_basis(gn.d - 1.0f);
+            } else if constexpr (P == 2) {
+                gn.bv[2] = half_basis(gn.d - 2.0f);
+                gn.bv[3] = half_basis(gn.d - 3.0f);
+            } else {
+                if constexpr (BF) {
+                    const uint32_t w01 = __builtin_bit_cast(
+                        uint32_t, bf16x2_t{(__bf16)gn.bv[0], (__bf16)gn.bv[1]});
+                    const uint32_t w23 = __builtin_bit_cast(
+                        uint32_t, bf16x2_t{(__bf16)gn.bv[2], (__bf16)gn.bv[3]});
+                    st16(buf, 0, abase, f32_to_bf16(gn.sl));
+                    st16(buf, 0, gn.adr, (uint16_t)w01);
+                    st16(buf, 0, gn.adr + AROW, (uint16_t)(w01 >> 16));
+                    st16(buf, 0, gn.adr + 2 * AROW, (uint16_t)w23);
+                    st16(buf, 0, gn.adr + 3 * AROW, (uint16_t)(w23 >> 16));
+                } else {
+                    auto two = [&](uint32_t adr, float v) {
+                        const _Float16 t = (_Float16)v;
+                        st16(buf, 0, adr, __builtin_bit_cast(uint16_t, t));
+                        st16(buf, 1, adr, __builtin_bit_cast(uint16_t, (_Float16)(v - (float)t)));
+                    };
+                    two(abase, __builtin_ldexpf(gn.sl, sscale));
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        two(gn.adr + m * AROW, gn.bv[m] * (float)(1 << kBasisExp));
+                }
+            }
+        }
+    };
+
+    // fp32: the products with a second term have accumulators of their own, so that
+    // the main ones round twice per 16 rows (six times, their sums have a larger
+    // error than the fp32 instruction's: 7.9e-7 against 6.7e-7 relative to float64
+    // over 65536 rows); at most 64 registers each, so tiles of up to 128 outputs.
+    static_assert(BF || RF * NFW <= 4, "fp32: two sets of accumulators");
+    floatx16 acc[RF][NFW], acc2[BF ? 1 : RF][BF ? 1 : NFW];
+#pragma unroll
+    for (int rt = 0; rt < RF; ++rt)
+#pragma unroll
+        for (int nf = 0; nf < NFW; ++nf)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                acc[rt][nf][q] = 0.0f;
+                if constexpr (!BF) acc2[rt][nf][q] = 0.0f;
+            }
+
+    // The MFMAs of stage buf, in segments; between them the next chunk is staged
+    // into stage buf ^ 1.
+    constexpr int NPART = 4 + DU, NSEG = 2 * NFW;
+    u32x4 A[RF][NT];
+    auto chunk = [&](int buf, const DSet& d, T xs, uint32_t& pv, auto with) {
+        StaticFor<0, NSEG>::run([&](auto seg) __attribute__((always_inline)) {
+            constexpr int S = decltype(seg)::value, s = S / NFW, nf = S % NFW;
+            if constexpr (nf == 0) {
+#pragma unroll
+                for (int rt = 0; rt < RF; ++rt)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        A[rt][t] = as[buf][t][(32 * (kg * RF + rt) + r) * (AROW / 16) + 2 * s + h];
+            }
+            u32x4 b[NT];
+            const int ol = (oh * NFW + nf) * 32 + r;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[t] = dys[buf][t][ol * 4 + ((2 * s + h) ^ ((ol >> 2) & 3))];
+            if constexpr (decltype(with)::value) {
+                StaticFor<NPART * S / NSEG, NPART*(S + 1) / NSEG>::run(
+                    [&](auto p) __attribute__((always_inline)) { stage_part(p, buf ^ 1, d, xs, pv); });
+            }
+#pragma unroll
+            for (int rt = 0; rt < RF; ++rt) {
+                if constexpr (BF) {
+                    acc[rt][nf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, A[rt][0]), __builtin_bit_cast(bf16x8, b[0]),
+                        acc[rt][nf], 0, 0, 0);
+                } else {
+                    auto mul = [&](int ta, int tb, floatx16& c) __attribute__((always_inline)) {
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                            __builtin_bit_cast(f16x8_t, A[rt][ta]), __builtin_bit_cast(f16x8_t, b[tb]),
+                            c, 0, 0, 0);
+                    };
+                    mul(NT - 1, 0, acc2[BF ? 0 : rt][BF ? 0 : nf]);
+                    mul(0, 0, acc[rt][nf]);
+                    mul(0, NT - 1, acc2[BF ? 0 : rt][BF ? 0 : nf]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    // Stage ck % 2 holds chunk ck, staged during chunk ck - 1.  The loop stages one
+    // chunk past the last (loads clamped to the last; never multiplied).
+    issue_x(0, xq[0]);
+    issue_x(1, xq[1]);
+    issue_dy(0, dq[0]);
+    if constexpr (BF) issue_dy(1, dq[1 % ND]);
+    StaticFor<0, NPART>::run([&](auto p) { stage_part(p, 0, dq[0], xq[0], prev[0]); });
+    if constexpr (!BF) issue_dy(1, dq[0]);
+    __syncthreads();
+    int ck = 0;
+    for (; ck + 1 < nchunks; ck += 2) {
+        issue_x(ck + 2, xq[0]);
+        if constexpr (BF) issue_dy(ck + 2, dq[0]);
+        chunk(0, dq[1 % ND], xq[1], prev[1], std::true_type{});
+        if constexpr (!BF) issue_dy(ck + 2, dq[0]);
+        __syncthreads();
+        issue_x(ck + 3, xq[1]);
+        if constexpr (BF) issue_dy(ck + 3, dq[1 % ND]);
+        chunk(1, dq[0], xq[0], prev[0], std::true_type{});
+        if constexpr (!BF) issue_dy(ck + 3, dq[0]);
+        __syncthreads();
+    }
+    if (ck < nchunks) chunk(0, dq[0], xq[1], prev[1], std::false_type{});
+    if (own && nanx) nanf[fl] = 1;
+    __syncthreads();
+
+    // acc[rt][nf][q] = (scaled dW^T / 2)[K row kt0 + lr][output], lr = 32 (kg RF + rt) +
+    // 8 (q / 4) + 4 h + q % 4.  A feature with a NaN input: its basis gradients
+    // are NaN (N_j(NaN) is NaN; the clamped form gave 0).
+    float* P = a.P + (int64_t)blockIdx.y * a.out32 * a.kr;
+#pragma unroll
+    for (int rt = 0; rt < RF; ++rt) {
+#pragma unroll
+        for (int nf = 0; nf < NFW; ++nf) {
+            const int ol = (oh * NFW + nf) * 32 + r;
+            const int o = ot0 + ol;
+            int ed = 0;
+            if constexpr (!BF) ed = (exd[ol] & 0xffff) - 512 - 12;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int lr = 32 * (kg * RF + rt) + 8 * m + 4 * h;
+                const int f = lr / (FULL ? 16 : a.cp);
+                const int c = lr - f * (FULL ? 16 : a.cp);  // (a multiple of 4)
+                const bool isn = nanf[f] != 0;
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float t = acc[rt][nf][4 * m + e];
+                    if constexpr (!BF) {
+                        t += acc2[BF ? 0 : rt][BF ? 0 : nf][4 * m + e];
+                        const int ea = e == 0 && c == 0 ? (exs[f] & 0xffff) - 512 - 12 : -kBasisExp;
+                        t = __builtin_ldexpf(t, ed + ea);
+                    }
+                    v[e] = isn && (c != 0 || e != 0) ? __builtin_nanf("") : t;
+                }
+                if (o < a.out32 && kt0 + lr < a.kr)
+                    *reinterpret_cast<floatx4*>(P + (int64_t)o * a.kr + kt0 + lr) = v;
+            }
+        }
+    }
+    if constexpr (!BF) {
+        // outputs with a non-finite dy, SiLU rows with a non-finite value: the sum
+        // over the rows that hold one (with the zeros of the basis, whose product
+        // with an infinity is NaN)
+        int any = 0;
+        for (int i = tid; i < OT + 16; i += kThreads) any |= (i < OT ? exd[i] : exs[i - OT]) >> 16;
+        if (__syncthreads_or(any)) {
+            for (int ol = 0; ol < OT; ++ol) {
+                const int o = ot0 + ol;
+                if (o >= a.out32) break;
+                const bool od = (exd[ol] >> 16) != 0;
+                for (int lr = tid; lr < KT && kt0 + lr < a.kr; lr += kThreads) {
+                    const int f = lr / a.cp, c = lr - f * a.cp;
+                    const bool fs = c == 0 && (exs[f] >> 16) != 0;
+                    if ((!od && !fs) || F0 + f >= a.in || (c != 0 && nanf[f])) continue;
+                    float s = 0.0f;
+                    for (int64_t b = b_begin; b < b_end && s == s; ++b) {
+                        const float dv = dyt[(int64_t)o * a.bpad + b];
+                        const float x = xt[(int64_t)(F0 + f) * a.bpad + b];
+                        float v;
+                        if (c == 0) {
+                            v = half_silu_w(x);
+                        } else {
+                            v = half_basis(__builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - (float)c) +
+                                           coord_lo(x, a.xlim, a.inv_lo, a.a_frac));
+                        }
+                        if (!(__builtin_fabsf(dv) < __builtin_inff()) ||
+                            !(__builtin_fabsf(v) < __builtin_inff()))
+                            s += v * dv;
+                    }
+                    if (s != 0.0f) P[(int64_t)o * a.kr + kt0 + lr] = s;
+                }
+            }
+        }
+    }
+}
+
+template <typename T, int OH, int NFW>
+void launch_shape(const Dw2Args& a, dim3 grid, hipStream_t s) {
+    if (a.cp == 16)
+        hipLaunchKernelGGL((dw_split_kernel<T, OH, NFW, true>), grid, dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((dw_split_kernel<T, OH, NFW, false>), grid, dim3(kThreads), 0, s, a);
+}
+
+template <typename T>
+hipError_t launch_t(const BwdGeom& g, const Dw2Args& a, hipStream_t s) {
+    const dim3 grid((unsigned)g.ktiles, (unsigned)g.split, (unsigned)g.otiles);
+    if (g.oh == 1 && g.nfw == 1) launch_shape<T, 1, 1>(a, grid, s);
+    else if (g.oh == 2 && g.nfw == 1) launch_shape<T, 2, 1>(a, grid, s);
+    else if (g.oh == 2 && g.nfw == 2) launch_shape<T, 2, 2>(a, grid, s);
+    else if (sizeof(T) == 2 && g.oh == 2 && g.nfw == 4) launch_shape<uint16_t, 2, 4>(a, grid, s);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_transpose_max(const float* src, float* dst, float* vmax, int64_t rows, int cols,
+                                int64_t rpad, hipStream_t s) {
+    hipLaunchKernelGGL(transpose_max_kernel,
+                       dim3((unsigned)(rpad / 64), (unsigned)((cols + 31) / 32)), dim3(256), 0, s,
+                       src, dst, vmax, rows, cols, rpad);
+    return hipGetLastError();
+}
+
+hipError_t launch_dw_split(bool bf16, const BwdGeom& g, const Dw2Args& a, hipStream_t s) {
+    return bf16 ? launch_t<uint16_t>(g, a, s) : launch_t<float>(g, a, s);
+}
+
+}  // namespace kan

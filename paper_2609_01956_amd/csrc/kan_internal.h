@@ -269,6 +269,7 @@ struct BwdGeom {
     int dx_bm;      // dx: batch rows per workgroup
     int dx_ksplit;  // dx: workgroups splitting the K tiles of a row block
     int dx_tiles_per_split;  // dx: K tiles per such workgroup (whole features)
+    bool dw2;       // dW on the whole-feature kernel (kan_bwd_dw.hip): cp divides 256
     bool nx;        // dx on the vector-ALU kernel of narrow layers (else the MFMA kernel)
     int ncw, nrs;   // nx: columns per feature and floats per column of its weight table
     int nfeat;      // nx: features of the table (in rounded up to 8)
@@ -279,7 +280,7 @@ struct BwdGeom {
     int split;      // dW: batch splits (partials summed by the reduce kernel)
     int rows_per_split;  // multiple of 32
     int64_t bpad;   // batch rounded up to 32 (columns of the transposed dy)
-    size_t off_wt, off_dyt, off_xt, off_p, off_dxp, bytes;  // workspace layout
+    size_t off_wt, off_we, off_dyt, off_xt, off_xm, off_dm, off_p, off_dxp, bytes;  // workspace layout
 };
 
 // Returns false when the sizes do not fit the kernels' index types.
@@ -299,6 +300,38 @@ struct BwdArgs {
     int out;
     float inv_h, inv_lo, xlim, a_int, a_frac;
 };
+
+// Weight gradients on the whole-feature kernel (kan_bwd_dw.hip).
+struct Dw2Args {
+    const void* xt;      // x transposed: [in32][bpad]
+    const void* dyt;     // dy transposed: [out32][bpad]
+    const float* xmax;   // fp32: maxima per 64 rows [bpad / 64][in32] (launch_transpose_max)
+    const float* dymax;  // fp32: [bpad / 64][out32]
+    float* P;            // [split][out32][kr] partial sums of dW^T / 2
+    int64_t bpad;
+    int in, in32, out32, nb, cp, kr, rows_per_split;
+    float inv_h, inv_lo, xlim, a_int, a_frac;
+};
+hipError_t launch_dw_split(bool bf16, const BwdGeom& g, const Dw2Args& a, hipStream_t s);
+hipError_t launch_transpose_max(const float* src, float* dst, float* vmax, int64_t rows, int cols,
+                                int64_t rpad, hipStream_t s);
+
+// Input gradient on the matrix cores (kan_bwd_dx.hip).
+struct Dx2Args {
+    const void* xt;    // x transposed: [in32][bpad]
+    const void* dy;    // [batch][out]
+    const void* coef;
+    const void* bw;
+    u32x4* wtp;        // packed weights [ntiles][groups][terms][64 lanes]
+    int* wexp;         // fp32: scale exponents [ntiles][nchunk]
+    void* dx;
+    float* dxp;        // per-chunk partials when the outputs take several chunks (else null)
+    int64_t batch, bpad;
+    int in, out, nb, cp, ntiles, groups, gmax, nchunk;
+    int tiles_per_split;  // K tiles of a workgroup (blockIdx.z), whole features
+    float inv_h, inv_lo, xlim, a_int, a_frac;
+};
+hipError_t launch_dx_split(bool bf16, const BwdGeom& g, const Dx2Args& a, hipStream_t s);
 
 hipError_t launch_backward(bool bf16, const BwdGeom& g, const BwdArgs& a, hipStream_t s);
 

@@ -371,9 +371,9 @@ void window_kernel(WinArgs a) {
                 xs[q] = __builtin_amdgcn_raw_buffer_load_b16(xrs, vo, 4 * p, 0);
         }
     };
-    // weights of stage st to LDS buffer st % NBS (stages past the last read past
-    // the resource: zeros)
-    auto load_w = [&](int st, int buf) {
+    // weights of stage st to LDS buffer st % NBS (stages past the last re-read it)
+    auto load_w = [&](int stage, int buf) {
+        const int st = min(stage, nst - 1);
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
             const int wl = wave + kWaves * i;
