@@ -476,7 +476,10 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict_
     constexpr int kBatch = 16;
     const float* p = P + (int64_t)o * kr + (int64_t)f * cp + c;
     float s = 0.0f;
-    for (int k0 = 0; k0 < split; k0 += kBatch) {
+    if (split <= 4) {  // (many weights: the adds of missing splits would cost more)
+        for (int k = 0; k < split; ++k) s += p[(int64_t)k * out32 * kr];
+    }
+    for (int k0 = split <= 4 ? split : 0; k0 < split; k0 += kBatch) {
         float t[kBatch];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i)
@@ -958,10 +961,9 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     const int ot = g->oh * g->nfw * 32;
     g->otiles = (g->out32 + ot - 1) / ot;
     if (g->otiles > 65535) return false;
-    // dx: two 32-row tiles per wave while their dy registers stay within 128 (fp32:
-    // up to 128 outputs), and the K tiles split over workgroups (whole features
+    // dx: two 32-row tiles per wave (fp32: up to 64 outputs), and the K tiles split over workgroups (whole features
     // each) until the grid fills the chip
-    g->dx_rf = bf16 || std::min(g->groups, g->gmax) <= 8 ? 2 : 1;
+    g->dx_rf = bf16 || std::min(g->groups, g->gmax) <= 4 ? 2 : 1;
     {
         const int tpf = g->cp == 16 ? 1 : g->cp / 32;
         g->dx_bm = 32 * g->dx_rf * 8;  // rows per workgroup (eight waves)

@@ -37,6 +37,8 @@ constexpr int kThreads = 64 * kNW;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));  // 16 bytes at an element's alignment
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 
 __device__ __forceinline__ float silu_slope(float x) {
     const float s = __builtin_amdgcn_rcpf(1.0f + __expf(-x));
@@ -86,9 +88,29 @@ __global__ __launch_bounds__(256) void pack_dx2_kernel(Dx2Args a) {
     const int R = 32 * t + kl, f = R / a.cp, c = R % a.cp;
     // A row of the local K row (inverse of tile_row)
     const int r = 8 * ((kl % 16) / 4) + 4 * (kl / 16) + kl % 4;
+    // the thread's column of the weights, one load per output (unconditional within
+    // groups of eight, so that they are in flight together)
+    const bool ok = f < a.in && c <= a.nb;
+    const T* col = static_cast<const T*>(a.bw);
+    int64_t stride = 0;
+    if (ok) {
+        col = c == 0 ? col + f : static_cast<const T*>(a.coef) + (int64_t)f * a.nb + c - 1;
+        stride = (int64_t)a.in * (c == 0 ? 1 : a.nb);
+    }
     T v[32];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = i < 2 * S ? weight<T>(a, 16 * g0 + 8 * i + e, f, c) : T(0);
+    for (int ib = 0; ib < 4; ++ib) {
+#pragma unroll
+        for (int i = 8 * ib; i < 8 * ib + 8; ++i) v[i] = T(0);
+        if (4 * ib < S) {
+#pragma unroll
+            for (int i = 8 * ib; i < 8 * ib + 8; ++i)
+                v[i] = col[(int64_t)min(16 * g0 + 8 * i + e, a.out - 1) * stride];
+        }
+#pragma unroll
+        for (int i = 8 * ib; i < 8 * ib + 8; ++i)
+            if (!ok || 16 * g0 + 8 * i + e >= a.out || i >= 2 * S) v[i] = T(0);
+    }
     int ex = 0;
     if constexpr (!BF) {
         float m = 0.0f;
@@ -242,32 +264,53 @@ void dx2_kernel(Dx2Args a) {
         *reinterpret_cast<u32x4*>(gw0 + lane * 80) = u32x4{0u, 0u, 0u, 0u};
         if (lane == 63) *reinterpret_cast<u32x4*>(gw0 + 64 * 80) = u32x4{0u, 0u, 0u, 0u};
     }
-    // B operands: the lane's batch rows of dy for every group of the chunk
+    // B operands: the lane's batch rows of dy for every group of the chunk.  All loads
+    // are 8 elements wide, at any alignment of the row, and go out before the first
+    // use; what they read past the row's outputs is masked, and only a load that
+    // would pass the tensor's end is taken element by element.
     u32x4 dyr[RF][NT][SM];
     int esc[RF];
-    const bool vec = a.out % (16 / (int)sizeof(T)) == 0 &&
-                     reinterpret_cast<uintptr_t>(a.dy) % 16 == 0;
+    const int64_t total = a.batch * (int64_t)a.out;
+    constexpr int NV = 8 * (int)sizeof(T) / 16;  // 16-byte units of eight elements
+    typedef typename std::conditional<BF, u32x4_a2, u32x4_a4>::type u32x4_el;
+    u32x4 raw[RF][SM][NV];
 #pragma unroll
     for (int rf = 0; rf < RF; ++rf) {
-        const T* dyrow = static_cast<const T*>(a.dy) + rowc[rf] * a.out;
+        const int64_t at = rowc[rf] * a.out + g0 * 16 + 8 * h;
+#pragma unroll
+        for (int s = 0; s < SM; ++s) {
+            if (total < 8) continue;
+            const T* p = static_cast<const T*>(a.dy) + min(at + 16 * min(s, S - 1), total - 8);
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                raw[rf][s][k] = reinterpret_cast<const u32x4_el*>(p)[k];
+        }
+    }
+#pragma unroll
+    for (int rf = 0; rf < RF; ++rf) {
+        const int64_t at = rowc[rf] * a.out + g0 * 16 + 8 * h;
         T v[SM][8];
 #pragma unroll
         for (int s = 0; s < SM; ++s) {
             const int o0 = (g0 + s) * 16 + 8 * h;
-            if (vec && s < S && o0 + 8 <= a.out) {
-                constexpr int NV = 8 * (int)sizeof(T) / 16;
+            if ((g0 + s) * 16 + 16 > a.out) {  // (uniform) the last group, or one past it
+                const bool past = at + 16 * s + 8 > total;
 #pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    const u32x4 w = *reinterpret_cast<const u32x4*>(dyrow + o0 + k * (8 / NV));
-#pragma unroll
-                    for (int e = 0; e < 8 / NV; ++e) {
-                        if constexpr (BF) v[s][e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
-                        else v[s][k * 4 + e] = __uint_as_float(w[e]);
+                for (int e = 0; e < 8; ++e) {
+                    T t = T(0);
+                    if (s < S && o0 + e < a.out) {
+                        if (past) t = static_cast<const T*>(a.dy)[at + 16 * s + e];
+                        else if constexpr (BF) t = (uint16_t)(raw[rf][s][0][e / 2] >> (16 * (e & 1)));
+                        else t = __uint_as_float(raw[rf][s][e / 4 < NV ? e / 4 : 0][e % 4]);
                     }
+                    v[s][e] = t;
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[s][e] = s < S && o0 + e < a.out ? dyrow[o0 + e] : T(0);
+                for (int e = 0; e < 8; ++e) {
+                    if constexpr (BF) v[s][e] = (uint16_t)(raw[rf][s][0][e / 2] >> (16 * (e & 1)));
+                    else v[s][e] = __uint_as_float(raw[rf][s][e / 4 < NV ? e / 4 : 0][e % 4]);
+                }
             }
         }
         esc[rf] = 0;
@@ -562,14 +605,12 @@ void dx2_kernel(Dx2Args a) {
 template <typename T, int SM, int RF>
 hipError_t launch_sm(const BwdGeom& g, const Dx2Args& a, hipStream_t s) {
     constexpr int BM = kNW * 32 * RF;
-    // (two K tiles per stage where the LDS and, in fp32 over 128 outputs, the
-    // registers hold them)
+    // (two K tiles per stage where the LDS holds them)
     constexpr int TPB = sizeof(T) == 2 || SM <= 8 ? 2 : 1;
     const dim3 grid((unsigned)((a.batch + BM - 1) / BM), (unsigned)g.nchunk,
                     (unsigned)g.dx_ksplit);
-    constexpr int TPB16 = sizeof(T) == 4 && SM == 8 ? 1 : 2;
     if (a.cp == 16)
-        hipLaunchKernelGGL((dx2_kernel<T, SM, RF, TPB16, true>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((dx2_kernel<T, SM, RF, 2, true>), grid, dim3(kThreads), 0, s, a);
     else
         hipLaunchKernelGGL((dx2_kernel<T, SM, RF, TPB, false>), grid, dim3(kThreads), 0, s, a);
     return hipGetLastError();
@@ -585,11 +626,9 @@ hipError_t launch_t(const BwdGeom& g, const Dx2Args& a, hipStream_t s) {
     if (sm <= 1) return launch_sm<T, 1, 2>(g, a, s);
     if (sm <= 2) return launch_sm<T, 2, 2>(g, a, s);
     if (sm <= 4) return launch_sm<T, 4, 2>(g, a, s);
-    if (sm <= 8) return launch_sm<T, 8, 2>(g, a, s);
-    if (sm <= 16) {
-        if constexpr (sizeof(T) == 2) return launch_sm<T, 16, 2>(g, a, s);
-        else return launch_sm<T, 16, 1>(g, a, s);
-    }
+    constexpr int RF = sizeof(T) == 2 ? 2 : 1;
+    if (sm <= 8) return launch_sm<T, 8, RF>(g, a, s);
+    if (sm <= 16) return launch_sm<T, 16, RF>(g, a, s);
     return hipErrorInvalidValue;
 }
 
