@@ -410,9 +410,11 @@ void window_kernel(WinArgs a) {
             const float sv = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f) + G.lo;
             // first window column, within the blocks and past the SiLU column: a
             // column the clamp takes in is at |v| >= (K + 1) / 2, where the form
-            // is exactly 0 (a NaN coordinate gives column 1 and NaN values)
-            const float cf = __builtin_amdgcn_fmed3f(
-                __builtin_floorf(sv - 0.5f * (float)(K - 1)), 1.0f, cmax);
+            // is exactly 0 (a NaN coordinate gives column 1 and NaN values).  Degrees
+            // 1 and 2 need 2 and 3 of the four columns: the window starts 1 and 1/2
+            // lower, so that the rounding of its position loses no value.
+            constexpr float low = 0.5f * (float)(K - 1) + (K == 1 ? 1.0f : K == 2 ? 0.5f : 0.0f);
+            const float cf = __builtin_amdgcn_fmed3f(__builtin_floorf(sv - low), 1.0f, cmax);
             G.c0 = (int)cf;
             // v of column c0 in one rounding at its own magnitude
             G.d = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - cf) + G.lo;
