@@ -131,7 +131,7 @@ kan_status kan_basis_eval(const kan_grid* grid, kan_dtype dtype, const void* x, 
     if (!aligned(x, es) || !aligned(phi, es)) return KAN_ERR_INVALID_ARG;
     if ((uint64_t)n > (uint64_t)(SIZE_MAX / es / gc.nb)) return KAN_ERR_INVALID_ARG;
     if (overlap(x, (size_t)n * es, phi, (size_t)n * gc.nb * es)) return KAN_ERR_INVALID_ARG;
-    const kan::BasisLaunch L = kan::plan_basis(n, gc.nb, phi);
+    const kan::BasisLaunch L = kan::plan_basis(n, gc.nb, gc.k, (int)es, phi);
     if (L.blocks > 0x7fffffffLL) return KAN_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dtype == KAN_F32)

@@ -110,6 +110,81 @@ __global__ __launch_bounds__(kThreads) void basis_kernel(const T* __restrict__ x
     stream_out<T>(stage, phi + e0 * nb, cnt * nb, vec);
 }
 
+// The same tensor where a run of 256 inputs is short (at most 8 KB) and there are
+// many: with one run per workgroup such a kernel waits on its load of x longer
+// than its stores take (65536 x 784, G = 10, bf16, fresh buffers: 334 us, 4.0 TB/s
+// of writes, where a plain fill takes 193 us), and all nb values per input keep the
+// vector ALUs busy for as long as the writes.  Here a workgroup takes `runs` runs
+// (spaced by the grid, so that the workgroups write one front), loads the inputs of
+// all of them before its first store (a load waited for later would wait for the
+// stores too), and evaluates only the k + 1 consecutive values of an input that can
+// be nonzero (eq. bounded), each by the same closed form; the rest of its two LDS
+// stages is zero: a thread clears the window it wrote two runs before in a stage
+// and writes the new one, in output order and type.  267 us.
+constexpr int kBasisRuns = 8;
+
+template <typename T, int K>
+__global__ __launch_bounds__(kThreads) void basis_runs_kernel(const T* __restrict__ x, int64_t n,
+                                                              T* __restrict__ phi, GridConst g,
+                                                              int runs) {
+    extern __shared__ u32x4 stage4[];
+    constexpr int V = 16 / (int)sizeof(T);
+    // degrees 1 and 2, whose values rise linearly or quadratically from the support's
+    // end: one column more, so that the rounding of the window's position loses none
+    constexpr int NW = K < 3 ? K + 2 : K + 1;
+    const int nb = g.nb;  // at least NW
+    const int tid = threadIdx.x;
+    const int stage_u = kThreads * nb / V;
+    T* stage = reinterpret_cast<T*>(stage4);
+    auto first_of = [&](int run) -> int64_t {
+        return ((int64_t)run * gridDim.x + blockIdx.x) * kThreads;
+    };
+    T xq[kBasisRuns];
+#pragma unroll
+    for (int i = 0; i < kBasisRuns; ++i) {
+        const int64_t e = first_of(i < runs ? i : 0) + tid;
+        xq[i] = x[e < n ? e : n - 1];
+    }
+    for (int i = tid; i < 2 * stage_u; i += kThreads) stage4[i] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    int old[2] = {tid * nb, tid * nb};  // window written two runs ago in each stage
+    bool oldnan[2] = {false, false};
+    StaticFor<0, kBasisRuns>::run([&](auto rr) {
+        constexpr int r = decltype(rr)::value, b = r & 1;
+        const int64_t e0 = first_of(r);
+        if (r >= runs || e0 >= n) return;  // (the same for the workgroup)
+        const int cnt = (int)(n - e0 < kThreads ? n - e0 : kThreads);
+        T* st = stage + b * stage_u * V;
+        const float xv = Storage<T>::load(&xq[r]);
+        const float lo = coord_lo(xv, g.xlim, g.inv_lo, g.a_frac);
+        const float sv = __builtin_fmaf(xv, g.inv_h, g.a_int) + lo;
+        const float jf = __builtin_amdgcn_fmed3f(
+            __builtin_floorf(sv - (0.5f * (K - 1) + (K < 3 ? 0.5f : 0.0f))), 0.0f, (float)(nb - NW));
+#pragma unroll
+        for (int m = 0; m < NW; ++m) st[old[b] + m] = T(0);
+        const int at = tid * nb + (int)jf;
+#pragma unroll
+        for (int m = 0; m < NW; ++m) {
+            const float v = __builtin_fmaf(xv, g.inv_h, g.a_int - (jf + (float)m)) + lo;
+            Storage<T>::store(st + at + m, basis_value<K>(v) * kScale<K>);
+        }
+        old[b] = at;
+        if (xv != xv || oldnan[b]) {  // a NaN input gives NaN in all its values
+            for (int j = 0; j < nb; ++j)
+                if (xv != xv) Storage<T>::store(st + tid * nb + j, xv);
+                else if (j < (int)jf || j >= (int)jf + NW) st[tid * nb + j] = T(0);
+            oldnan[b] = xv != xv;
+        }
+        __syncthreads();
+        T* out = phi + e0 * nb;
+        const int total = cnt * nb;
+        const u32x4* su = reinterpret_cast<const u32x4*>(st);
+        for (int u = tid; u < total / V; u += kThreads)
+            __builtin_nontemporal_store(su[u], reinterpret_cast<u32x4*>(out) + u);
+        for (int e = total / V * V + tid; e < total; e += kThreads) out[e] = st[e];
+    });
+}
+
 // ------------------------------------------------------------ Cox-de Boor
 //
 // The same basis by the recursion of eq. cdb0 / eq. cdbk over every knot
@@ -214,8 +289,23 @@ __global__ __launch_bounds__(64) void basis_cdb_lds_kernel(const T* __restrict__
 
 }  // namespace
 
-BasisLaunch plan_basis(int64_t n, int nb, const void* phi) {
+BasisLaunch plan_basis(int64_t n, int nb, int k, int es, const void* phi) {
     BasisLaunch L;
+    // The many-run kernel: bf16, short runs (at most 16 values per input) and enough
+    // of them for 8192 workgroups of eight runs (65536 x 784, G = 10: 267 us against
+    // 335; 65536 x 256: 72 against 83; 16384 x 256, 16384 runs: 20 against 18.6;
+    // longer runs, 60000 x 300, G = 25: 187 against 172; fp32 runs of the same bytes,
+    // 65536 x 300, G = 5: 115 against 99), with room for the window, and an aligned
+    // output (every run then starts on 16 bytes).
+    L.runs = 0;
+    const int64_t nruns = (n + kThreads - 1) / kThreads;
+    if (es == 2 && nb <= 16 && nb >= k + 2 && nruns >= 8 * 8192 &&
+        reinterpret_cast<uintptr_t>(phi) % 16 == 0) {
+        L.runs = kBasisRuns;
+        L.lds = (size_t)2 * kThreads * nb * es;
+        L.blocks = (nruns + kBasisRuns - 1) / kBasisRuns;
+        return L;
+    }
     // Smallest power-of-two split of each input's nb values over threads that
     // keeps the workgroup's LDS run at or below 32 KiB (at most 64 KiB for the
     // largest grids).  A run whose start is not 16-byte aligned (possible only
@@ -235,6 +325,13 @@ BasisLaunch plan_basis(int64_t n, int nb, const void* phi) {
 template <typename T, int K>
 static hipError_t launch_k(const T* x, int64_t n, T* phi, const GridConst& g,
                            const BasisLaunch& L, hipStream_t s) {
+    if constexpr (sizeof(T) == 2) {
+        if (L.runs > 0) {
+            hipLaunchKernelGGL((basis_runs_kernel<T, K>), dim3((unsigned)L.blocks),
+                               dim3(kThreads), L.lds, s, x, n, phi, g, L.runs);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((basis_kernel<T, K>), dim3((unsigned)L.blocks), dim3(kThreads), L.lds, s,
                        x, n, phi, g, L.tpx, L.jc, L.vec ? 1 : 0);
     return hipGetLastError();

@@ -21,9 +21,10 @@ struct BasisLaunch {
     int64_t blocks; // ceil(n / xb)
     bool vec;       // output pointer is 16-byte aligned: vector stores allowed
                     // (each workgroup still checks its own run)
+    int runs;       // > 0: the many-run kernel, this many runs of 256 inputs per block
 };
 
-BasisLaunch plan_basis(int64_t n, int nb, const void* phi);
+BasisLaunch plan_basis(int64_t n, int nb, int k, int es, const void* phi);
 
 hipError_t launch_basis_f32(const float* x, int64_t n, float* phi, const GridConst& g,
                             const BasisLaunch& L, hipStream_t s);

@@ -144,3 +144,47 @@ def test_basis_full_size_mlp_input_sampled(dtype_name):
     pu = (flat.to(torch.float32).sum(dim=1, dtype=torch.float64) - 1.0).abs().max()
     tol = PU_TOL if dtype == torch.float32 else 4 * 2.0 ** -8
     assert float(pu) <= tol
+
+
+@pytest.mark.parametrize("dtype_name,n,G,k,lo,hi", [
+    # the many-run kernel: bf16, from 65536 runs of 256 inputs on (nb = k + 2, the
+    # smallest, up to 16 values), ragged ends, grids whose 1/h is exact and not; and
+    # fp32 and fewer runs on the one-run kernel
+    ("bf16", 65536 * 256, 13, 3, -1.0, 1.0), ("bf16", 65536 * 256 + 77, 10, 3, -1.0, 1.0),
+    ("f32", 65537 * 256 + 1, 5, 3, -1.0, 1.0), ("bf16", 65536 * 256 + 300, 2, 1, 0.0, 3.0),
+    ("bf16", 70000 * 256 + 5, 9, 2, -3.14, 3.14), ("bf16", 65600 * 256 + 129, 2, 6, -1.0, 1.0),
+    ("bf16", 65536 * 256 - 255, 6, 2, 0.0, 7.0), ("bf16", 65535 * 256, 6, 2, 0.0, 7.0),
+])
+def test_basis_many_runs(dtype_name, n, G, k, lo, hi):
+    dt = torch.float32 if dtype_name == "f32" else torch.bfloat16
+    g = torch.Generator(device=device())
+    g.manual_seed(n % 1000)
+    x = torch.empty(n, device=device()).uniform_(1.5 * lo - 0.2, 1.2 * hi, generator=g).to(dt)
+    # every lane's place in a stage: NaN and infinities two runs apart and not
+    bad = torch.arange(0, n, 1237, device=device())
+    x[bad[::3]], x[bad[1::3]], x[bad[2::3]] = float("nan"), float("inf"), float("-inf")
+    say(f"basis many runs {dtype_name} n={n} G={G} k={k}")
+    phi = torch.full((n + 1, G + k), 7.0, dtype=dt, device=device())
+    kb.basis(x, G, lo, hi, spline_order=k, out=phi[:n])
+    torch.cuda.synchronize()
+    assert bool((phi[n] == 7.0).all())
+    rows = np.unique(np.r_[0:600, n - 600:n, np.random.default_rng(1).integers(0, n, 4000)])
+    xs = x.float().cpu().numpy()[rows]
+    got = phi[torch.from_numpy(rows).to(phi.device)].float().cpu().numpy().astype(np.float64)
+    ref = oracle.basis_tp(xs, G, lo, hi, k=k)
+    assert np.array_equal(np.isnan(got), np.isnan(ref) | np.isnan(xs)[:, None])
+    if dtype_name == "bf16":
+        ref = oracle.round_bf16(ref)
+    ok = np.isfinite(xs)
+    # fp32 1e-6; bf16: its neighbour where the fp32 error crosses a rounding boundary
+    tol = 1e-6 if dtype_name == "f32" else 1e-6 + 2.0 ** -8 * np.abs(ref[ok])
+    assert (np.abs(got[ok] - ref[ok]) <= tol).all()
+    assert (got[np.isinf(xs)] == 0).all()
+    # and everywhere against the one-run kernel (a misaligned output takes it)
+    buf = torch.empty(n * (G + k) + 8, dtype=dt, device=device())
+    other = buf[1:1 + n * (G + k)].view(n, G + k)
+    kb.basis(x, G, lo, hi, spline_order=k, out=other)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(other).eq(torch.isnan(phi[:n])).all())
+    assert float((other.nan_to_num() - phi[:n].nan_to_num()).abs().max()) <= (
+        1e-6 if dtype_name == "f32" else 2.0 ** -8)
