@@ -342,7 +342,33 @@ def _require_device(*ts) -> None:
 
 
 def _stream(device) -> int:
+    """Handle of torch's current stream (read without building a Stream object: 0.1
+    against 1.9 us)."""
+    raw = getattr(_torch()._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None:
+        return raw(device.index)
     return int(_torch().cuda.current_stream(device).cuda_stream)
+
+
+def _call(device, fn, *args) -> int:
+    """fn(*args) with `device` current; a small layer's call is bound by the host, so
+    the device is switched only where it is another one."""
+    cuda = _torch().cuda
+    if cuda.current_device() == device.index:
+        return fn(*args)
+    with cuda.device(device):
+        return fn(*args)
+
+
+def _library() -> ctypes.CDLL:
+    return _lib if _lib is not None else load_library()
+
+
+def _query(fn, grid, *args) -> int:
+    """A size query's bytes."""
+    n = ctypes.c_size_t(0)
+    check(fn(ctypes.byref(grid), *args, ctypes.byref(n)))
+    return n.value
 
 
 def basis(x, grid_size: int, grid_lo: float = -1.0, grid_hi: float = 1.0, out=None,
@@ -361,11 +387,11 @@ def basis(x, grid_size: int, grid_lo: float = -1.0, grid_hi: float = 1.0, out=No
         _require_device(x, out)
         if out.dtype != x.dtype or tuple(out.shape) != tuple(x.shape) + (nb,):
             raise ValueError("out must have shape x.shape + (G + k,) and x's dtype")
-    with torch.cuda.device(x.device):
-        fn = kan_basis_eval if method == "tp" else kan_basis_eval_cdb
-        check(fn(make_grid(grid_size, grid_lo, grid_hi, spline_order), _dtype_code(x),
-                             x.data_ptr(),
-                             x.numel(), out.data_ptr(), _stream(x.device)))
+    lib = _library()
+    g = make_grid(grid_size, grid_lo, grid_hi, spline_order)
+    check(_call(x.device, lib.kan_basis_eval if method == "tp" else lib.kan_basis_eval_cdb,
+                ctypes.byref(g), _dtype_code(x), x.data_ptr(), x.numel(), out.data_ptr(),
+                _stream(x.device)))
     return out
 
 
@@ -404,8 +430,8 @@ def pack_layer(coef, base_w, grid_size: int, grid_lo: float = -1.0, grid_hi: flo
     n_in, n_out = _check_weights(coef, base_w, grid_size, spline_order)
     dt = _dtype_code(coef)
     g = make_grid(grid_size, grid_lo, grid_hi, spline_order)
-    st, nbytes = kan_layer_packed_bytes(g, dt, n_in, n_out)
-    check(st)
+    lib = _library()
+    nbytes = _query(lib.kan_layer_packed_bytes, g, dt, n_in, n_out)
     if out is None:
         buf = torch.empty(nbytes, dtype=torch.uint8, device=coef.device)
         out = PackedLayer(buf, grid_size, grid_lo, grid_hi, n_in, n_out, coef.dtype, spline_order)
@@ -416,9 +442,8 @@ def pack_layer(coef, base_w, grid_size: int, grid_lo: float = -1.0, grid_hi: flo
         out.grid_size, out.grid_lo, out.grid_hi = int(grid_size), float(grid_lo), float(grid_hi)
         out.n_in, out.n_out, out.dtype = int(n_in), int(n_out), coef.dtype
         out.spline_order = int(spline_order)
-    with torch.cuda.device(coef.device):
-        check(kan_layer_pack(g, dt, n_in, n_out, coef.data_ptr(), base_w.data_ptr(),
-                             out.buf.data_ptr(), out.nbytes, _stream(coef.device)))
+    check(_call(coef.device, lib.kan_layer_pack, ctypes.byref(g), dt, n_in, n_out, coef.data_ptr(),
+                base_w.data_ptr(), out.buf.data_ptr(), out.nbytes, _stream(coef.device)))
     return out
 
 
@@ -446,24 +471,23 @@ def layer_forward_packed(x, packed: PackedLayer, out=None, shape=None, workspace
             raise ValueError("out must be [B, out] with x's dtype")
     g = make_grid(packed.grid_size, packed.grid_lo, packed.grid_hi, packed.spline_order)
     dt = _dtype_code(x)
+    lib = _library()
+    shape = _shape_arg(shape)
     ws_ptr, ws_bytes = 0, 0
     if split:
         if shape is None:
-            st, need = kan_layer_forward_packed_full_workspace_bytes(g, dt, B, packed.n_in,
-                                                                     packed.n_out)
+            need = _query(lib.kan_layer_forward_packed_full_workspace_bytes, g, dt, B, packed.n_in,
+                          packed.n_out)
         else:
-            st, need = kan_layer_forward_packed_workspace_bytes(g, dt, B, packed.n_in,
-                                                                packed.n_out, shape)
-        check(st)
+            need = _query(lib.kan_layer_forward_packed_workspace_bytes, g, dt, B, packed.n_in,
+                          packed.n_out, shape)
         if need > 0:
             if workspace is None or workspace.numel() < need or workspace.device != x.device:
                 workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
             ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel()
-    with torch.cuda.device(x.device):
-        check(kan_layer_forward_packed(g, dt, B, packed.n_in, packed.n_out, x.data_ptr(),
-                                       packed.buf.data_ptr(), packed.nbytes, out.data_ptr(),
-                                       _stream(x.device), shape=shape, workspace=ws_ptr,
-                                       workspace_bytes=ws_bytes))
+    check(_call(x.device, lib.kan_layer_forward_packed, ctypes.byref(g), dt, B, packed.n_in,
+                packed.n_out, x.data_ptr(), packed.buf.data_ptr(), packed.nbytes, shape, ws_ptr,
+                ws_bytes, out.data_ptr(), _stream(x.device)))
     return out
 
 
@@ -476,11 +500,22 @@ def layer_forward(x, coef, base_w, grid_size: int, grid_lo: float = -1.0, grid_h
     kan_layer_forward_packed, both on torch's current stream; `shape` forces a
     workgroup shape."""
     _require_device(x)
-    n_in, _ = _check_weights(coef, base_w, grid_size, spline_order)
+    n_in, n_out = _check_weights(coef, base_w, grid_size, spline_order)
     if x.dim() != 2 or x.shape[1] != n_in:
         raise ValueError("x must be [B, in] with coef's in")
     if coef.dtype != x.dtype:
         raise ValueError("x, coef and base_w must share one dtype")
+    if out is None and packed is None and shape is None and x.device == coef.device:
+        # both steps in one call, in one workspace
+        torch, lib = _torch(), _library()
+        g, dt, B = make_grid(grid_size, grid_lo, grid_hi, spline_order), _dtype_code(x), x.shape[0]
+        need = _query(lib.kan_layer_forward_workspace_bytes, g, dt, B, n_in, n_out)
+        ws = torch.empty(need, dtype=torch.uint8, device=x.device)
+        out = torch.empty((B, n_out), dtype=x.dtype, device=x.device)
+        check(_call(x.device, lib.kan_layer_forward, ctypes.byref(g), dt, B, n_in, n_out,
+                    x.data_ptr(), coef.data_ptr(), base_w.data_ptr(), ws.data_ptr(), need,
+                    out.data_ptr(), _stream(x.device)))
+        return out
     p = pack_layer(coef, base_w, grid_size, grid_lo, grid_hi, out=packed,
                    spline_order=spline_order)
     return layer_forward_packed(x, p, out=out, shape=shape)
@@ -521,8 +556,8 @@ def layer_backward(x, coef, base_w, dy, grid_size: int, grid_lo: float = -1.0,
     B = x.shape[0]
     dt = _dtype_code(x)
     g = make_grid(grid_size, grid_lo, grid_hi)
-    st, nbytes = kan_layer_backward_workspace_bytes(g, dt, B, n_in, n_out)
-    check(st)
+    lib = _library()
+    nbytes = _query(lib.kan_layer_backward_workspace_bytes, g, dt, B, n_in, n_out)
     if workspace is None or workspace.numel() < nbytes or workspace.device != x.device:
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x.device)
     if out is not None:
@@ -538,10 +573,9 @@ def layer_backward(x, coef, base_w, dy, grid_size: int, grid_lo: float = -1.0,
         dC = torch.empty_like(coef) if need_dw else None
         dW = torch.empty_like(base_w) if need_dw else None
     ptr = lambda t: 0 if t is None else t.data_ptr()
-    with torch.cuda.device(x.device):
-        check(kan_layer_backward(g, dt, B, n_in, n_out, x.data_ptr(), coef.data_ptr(),
-                                 base_w.data_ptr(), dy.data_ptr(), ptr(dx), ptr(dC), ptr(dW),
-                                 workspace.data_ptr(), workspace.numel(), _stream(x.device)))
+    check(_call(x.device, lib.kan_layer_backward, ctypes.byref(g), dt, B, n_in, n_out,
+                x.data_ptr(), coef.data_ptr(), base_w.data_ptr(), dy.data_ptr(), ptr(dx), ptr(dC),
+                ptr(dW), workspace.data_ptr(), workspace.numel(), _stream(x.device)))
     return dx, dC, dW
 
 
@@ -558,14 +592,13 @@ def layer_forward_span(x, coef, base_w, grid_size: int, grid_lo: float = -1.0,
     B = x.shape[0]
     dt = _dtype_code(x)
     g = make_grid(grid_size, grid_lo, grid_hi, spline_order)
-    st, nbytes = kan_layer_forward_span_workspace_bytes(g, dt, B, n_in, n_out)
-    check(st)
+    lib = _library()
+    nbytes = _query(lib.kan_layer_forward_span_workspace_bytes, g, dt, B, n_in, n_out)
     if workspace is None or workspace.numel() < nbytes or workspace.device != x.device:
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x.device)
     if out is None:
         out = torch.empty((B, n_out), dtype=x.dtype, device=x.device)
-    with torch.cuda.device(x.device):
-        check(kan_layer_forward_span(g, dt, B, n_in, n_out, x.data_ptr(), coef.data_ptr(),
-                                     base_w.data_ptr(), workspace.data_ptr(), workspace.numel(),
-                                     out.data_ptr(), _stream(x.device)))
+    check(_call(x.device, lib.kan_layer_forward_span, ctypes.byref(g), dt, B, n_in, n_out,
+                x.data_ptr(), coef.data_ptr(), base_w.data_ptr(), workspace.data_ptr(),
+                workspace.numel(), out.data_ptr(), _stream(x.device)))
     return out
