@@ -23,7 +23,7 @@
 // the term-by-term derivative of the reflected two-term form 6 N = w^3 - 4 b^3
 // (w = 2 - |v| on the support): exactly 0 off the support, where the clamp
 // holds the coordinate constant.
-#include "kan_internal.h"
+#include "kan_bwd_pack.h"
 
 #include <algorithm>
 
@@ -32,6 +32,7 @@ namespace kan {
 namespace {
 
 constexpr int kThreads = 512;  // eight waves
+constexpr int64_t kPrepBlocks = 1024;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -88,12 +89,12 @@ template <> struct B<uint16_t> {
 // consecutive.  Used for dy (the B operand of dW) and x (read per feature for
 // 32 consecutive batch rows by both backward kernels).
 template <typename T, bool PERM>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ src,
-                                                        T* __restrict__ dst, int64_t rows,
-                                                        int cols, int64_t rpad) {
+__device__ __forceinline__ void transpose_tile(const T* __restrict__ src, T* __restrict__ dst,
+                                               int64_t rows, int cols, int64_t rpad, int bx,
+                                               int by) {
     __shared__ T tile[32][33];
-    const int64_t b0 = (int64_t)blockIdx.x * 32;
-    const int c0 = blockIdx.y * 32;
+    const int64_t b0 = (int64_t)bx * 32;
+    const int c0 = by * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows of 32
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -112,22 +113,27 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ sr
     }
 }
 
+template <typename T, bool PERM>
+__global__ __launch_bounds__(256) void transpose_kernel(const T* src, T* dst, int64_t rows,
+                                                        int cols, int64_t rpad) {
+    transpose_tile<T, PERM>(src, dst, rows, cols, rpad, blockIdx.x, blockIdx.y);
+}
+
 // The same transposition (without PERM) in 64 x 64 tiles with 16-byte
 // accesses, for bf16: four threads read a tile row's 64 elements (a 128-byte
 // run of src) and four write an output row's 64 (a run of dst), each moving
 // 16 elements.  vec: src and cols allow 16-byte loads (else element loads);
 // drows = ceil(cols / 32) * 32 rows of dst are written, columns up to rpad.
 template <typename T>
-__global__ __launch_bounds__(256) void transpose64_kernel(const T* __restrict__ src,
-                                                          T* __restrict__ dst, int64_t rows,
-                                                          int cols, int64_t rpad, int drows,
-                                                          bool vec) {
+__device__ __forceinline__ void transpose64_tile(const T* __restrict__ src, T* __restrict__ dst,
+                                                 int64_t rows, int cols, int64_t rpad, int drows,
+                                                 bool vec, int bx, int by) {
     constexpr int V = 16 / (int)sizeof(T);  // elements per 16-byte access
     constexpr int PER = 16;                 // elements per thread
     constexpr int PAD = V;                  // keeps tile rows 16-byte aligned
     __shared__ __align__(16) T tile[64][64 + PAD];
-    const int64_t b0 = (int64_t)blockIdx.x * 64;
-    const int c0 = blockIdx.y * 64;
+    const int64_t b0 = (int64_t)bx * 64;
+    const int c0 = by * 64;
     const int part = threadIdx.x & 3;
     {
         const int bl = threadIdx.x >> 2;
@@ -163,6 +169,51 @@ __global__ __launch_bounds__(256) void transpose64_kernel(const T* __restrict__ 
 #pragma unroll
         for (int i = 0; i < V; ++i) e[i] = tile[bl + i][cl];
         *reinterpret_cast<u32x4*>(dst + (int64_t)c * rpad + b) = __builtin_bit_cast(u32x4, e);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void transpose64_kernel(const T* src, T* dst, int64_t rows,
+                                                          int cols, int64_t rpad, int drows,
+                                                          bool vec) {
+    transpose64_tile<T>(src, dst, rows, cols, rpad, drows, vec, blockIdx.x, blockIdx.y);
+}
+
+// Small layers: what the gradient kernels read, prepared in one launch instead of
+// three (a launch takes the host some 3 us, more than such a kernel runs):
+// workgroups [0, nw) pack the weights of dx, [nw, nw + nx) transpose x and the
+// last ny dy (bf16 in 64 x 64 tiles, fp32 in 32 x 32 ones, dy of fp32 permuted).
+template <typename T>
+struct PrepArgs {
+    Dx2Args d;
+    const T *x, *dy;
+    T *xt, *dyt;
+    int64_t batch, bpad;
+    int in, out, out32, nw, nx, ny, bx;  // bx: tiles along the batch
+    bool vec_x, vec_dy;
+};
+
+template <typename T>
+__global__ __launch_bounds__(256) void prep_kernel(PrepArgs<T> a) {
+    int b = blockIdx.x;
+    if (b < a.nw) {
+        pack_dx2<T>(a.d, b % a.d.ntiles, b / a.d.ntiles);
+        return;
+    }
+    b -= a.nw;
+    if constexpr (sizeof(T) == 2) {
+        if (b < a.nx)
+            transpose64_tile<T>(a.x, a.xt, a.batch, a.in, a.bpad, (a.in + 31) / 32 * 32, a.vec_x,
+                                b % a.bx, b / a.bx);
+        else
+            transpose64_tile<T>(a.dy, a.dyt, a.batch, a.out, a.bpad, a.out32, a.vec_dy,
+                                (b - a.nx) % a.bx, (b - a.nx) / a.bx);
+    } else {
+        if (b < a.nx)
+            transpose_tile<T, false>(a.x, a.xt, a.batch, a.in, a.bpad, b % a.bx, b / a.bx);
+        else
+            transpose_tile<T, true>(a.dy, a.dyt, a.batch, a.out, a.bpad, (b - a.nx) % a.bx,
+                                    (b - a.nx) / a.bx);
     }
 }
 
@@ -771,7 +822,68 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
     const T* x = static_cast<const T*>(a.x);
     hipError_t e = hipSuccess;
     T* xt = reinterpret_cast<T*>(ws + g.off_xt);
-    if (a.batch > 0) {
+    Dx2Args dxa = {};
+    if (a.dx != nullptr && a.batch > 0 && !g.nx) {
+        dxa.xt = xt;
+        dxa.dy = a.dy;
+        dxa.coef = a.coef;
+        dxa.bw = a.bw;
+        dxa.wtp = reinterpret_cast<u32x4*>(ws + g.off_wt);
+        dxa.wexp = reinterpret_cast<int*>(ws + g.off_we);
+        dxa.dx = a.dx;
+        dxa.dxp = g.nchunk > 1 ? reinterpret_cast<float*>(ws + g.off_dxp) : nullptr;
+        dxa.batch = a.batch;
+        dxa.bpad = g.bpad;
+        dxa.in = a.in;
+        dxa.out = a.out;
+        dxa.nb = g.nb;
+        dxa.cp = g.cp;
+        dxa.ntiles = g.ntiles;
+        dxa.groups = g.groups;
+        dxa.gmax = g.gmax;
+        dxa.nchunk = g.nchunk;
+        dxa.tiles_per_split = g.dx_tiles_per_split;
+        dxa.inv_h = a.inv_h;
+        dxa.inv_lo = a.inv_lo;
+        dxa.xlim = a.xlim;
+        dxa.a_int = a.a_int;
+        dxa.a_frac = a.a_frac;
+    }
+    // Both gradients of a small layer: one launch prepares all three operands (up to
+    // kPrepBlocks workgroups: beyond, the shared launch's LDS costs the transpositions
+    // more than two launches take)
+    bool prepared = false;
+    if (a.dx != nullptr && a.dcoef != nullptr && a.batch > 0 && !g.nx &&
+        (sizeof(T) == 2 || !g.dw2)) {
+        constexpr int TB = sizeof(T) == 2 ? 64 : 32;
+        const int64_t bx = (g.bpad + TB - 1) / TB;
+        const int64_t nx = bx * (((a.in + 31) / 32 * 32 + TB - 1) / TB);
+        const int64_t ny = bx * ((g.out32 + TB - 1) / TB);
+        const int64_t nw = (int64_t)g.ntiles * g.nchunk;
+        if (nx + ny + nw <= kPrepBlocks) {
+            PrepArgs<T> p;
+            p.d = dxa;
+            p.x = x;
+            p.dy = static_cast<const T*>(a.dy);
+            p.xt = xt;
+            p.dyt = reinterpret_cast<T*>(ws + g.off_dyt);
+            p.batch = a.batch;
+            p.bpad = g.bpad;
+            p.in = a.in;
+            p.out = a.out;
+            p.out32 = g.out32;
+            p.nw = (int)nw;
+            p.nx = (int)nx;
+            p.ny = (int)ny;
+            p.bx = (int)bx;
+            p.vec_x = reinterpret_cast<uintptr_t>(x) % 16 == 0 && a.in % 8 == 0;
+            p.vec_dy = reinterpret_cast<uintptr_t>(a.dy) % 16 == 0 && a.out % 8 == 0;
+            hipLaunchKernelGGL(prep_kernel<T>, dim3((unsigned)(nx + ny + nw)), dim3(256), 0, s, p);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            prepared = true;
+        }
+    }
+    if (a.batch > 0 && !prepared) {
         // x transposed for both kernels (natural row order), dy for dW.  bf16
         // x in 64 x 64 tiles with 16-byte accesses (65536 x 784: 50 us against
         // 95 in 32 x 32 tiles of element accesses); fp32 x in 32 x 32 tiles,
@@ -820,36 +932,11 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
         d.a_frac = a.a_frac;
         if ((e = launch_narrow_dx<T>(g, d, s)) != hipSuccess) return e;
     } else if (a.dx != nullptr && a.batch > 0) {
-        Dx2Args d;
-        d.xt = xt;
-        d.dy = a.dy;
-        d.coef = a.coef;
-        d.bw = a.bw;
-        d.wtp = reinterpret_cast<u32x4*>(ws + g.off_wt);
-        d.wexp = reinterpret_cast<int*>(ws + g.off_we);
-        d.dx = a.dx;
-        d.dxp = g.nchunk > 1 ? reinterpret_cast<float*>(ws + g.off_dxp) : nullptr;
-        d.batch = a.batch;
-        d.bpad = g.bpad;
-        d.in = a.in;
-        d.out = a.out;
-        d.nb = g.nb;
-        d.cp = g.cp;
-        d.ntiles = g.ntiles;
-        d.groups = g.groups;
-        d.gmax = g.gmax;
-        d.nchunk = g.nchunk;
-        d.tiles_per_split = g.dx_tiles_per_split;
-        d.inv_h = a.inv_h;
-        d.inv_lo = a.inv_lo;
-        d.xlim = a.xlim;
-        d.a_int = a.a_int;
-        d.a_frac = a.a_frac;
-        if ((e = launch_dx_split(sizeof(T) == 2, g, d, s)) != hipSuccess) return e;
+        if ((e = launch_dx_split(sizeof(T) == 2, g, dxa, prepared, s)) != hipSuccess) return e;
         if (g.nchunk > 1) {
             const int64_t n = a.batch * a.in;
             hipLaunchKernelGGL(dx_reduce_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256),
-                               0, s, d.dxp, static_cast<T*>(a.dx), n, g.nchunk);
+                               0, s, dxa.dxp, static_cast<T*>(a.dx), n, g.nchunk);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }
@@ -858,7 +945,9 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
         int split = 0;
         if (a.batch > 0) {
             T* dyt = reinterpret_cast<T*>(ws + g.off_dyt);
-            if constexpr (sizeof(T) == 2) {
+            if (prepared) {
+                // (dy is transposed already)
+            } else if constexpr (sizeof(T) == 2) {
                 const bool vec = reinterpret_cast<uintptr_t>(a.dy) % 16 == 0 && a.out % 8 == 0;
                 hipLaunchKernelGGL(transpose64_kernel<T>,
                                    dim3((unsigned)((g.bpad + 63) / 64),

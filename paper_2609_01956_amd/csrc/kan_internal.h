@@ -332,7 +332,9 @@ struct Dx2Args {
     int tiles_per_split;  // K tiles of a workgroup (blockIdx.z), whole features
     float inv_h, inv_lo, xlim, a_int, a_frac;
 };
-hipError_t launch_dx_split(bool bf16, const BwdGeom& g, const Dx2Args& a, hipStream_t s);
+// packed: the weights are in the workspace already.
+hipError_t launch_dx_split(bool bf16, const BwdGeom& g, const Dx2Args& a, bool packed,
+                           hipStream_t s);
 
 hipError_t launch_backward(bool bf16, const BwdGeom& g, const BwdArgs& a, hipStream_t s);
 
