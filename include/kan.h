@@ -261,10 +261,9 @@ kan_status kan_layer_forward_packed_workspace_bytes(const kan_grid* grid, kan_dt
  * instruction; in fp32 every basis value and coefficient is the sum of two
  * fp16 terms (scaled per output column) and the SiLU column stays in fp32,
  * with fp32 accumulation: the same result up to the fp32 summation order.
- * An infinite or NaN coefficient times a basis value of exactly 0 is NaN in
- * fp32, as without the workspace; in bf16 a coefficient is not read for the
- * inputs whose window leaves it out.  A smaller workspace runs the layer as
- * kan_layer_plan reports.
+ * An infinite or NaN coefficient times a basis value of exactly 0 is NaN, as
+ * without the workspace.  A smaller workspace runs the layer as kan_layer_plan
+ * reports.
  * Writes *bytes.  Returns as kan_layer_forward_packed_workspace_bytes.
  */
 kan_status kan_layer_forward_packed_full_workspace_bytes(const kan_grid* grid, kan_dtype dtype,
@@ -339,7 +338,10 @@ kan_status kan_layer_plan(const kan_grid* grid, kan_dtype dtype, int64_t batch,
  *              overlapping no other argument; overwritten.
  *
  * Both contractions run on the matrix cores with fp32 accumulation; the
- * basis values are regenerated in registers, never stored.  For layers of at
+ * basis values are regenerated in registers, never stored.  In fp32 the
+ * operands are two fp16 terms each (22 bits, scaled by powers of two), except
+ * the weight gradients of batches below 8192 rows and of grids whose padded
+ * columns do not divide 256, which use the fp32 matrix instruction.  For layers of at
  * most 16 outputs from 16384 rows on (when a feature's G + 7 columns, rounded
  * down to even, times its outputs rounded up to a multiple of 4 stay within
  * 256) dx runs instead on the vector ALUs over the SiLU column and the four
@@ -364,8 +366,8 @@ kan_status kan_layer_backward(const kan_grid* grid, kan_dtype dtype, int64_t bat
 /*
  * kan_layer_backward_workspace_bytes -- size in bytes of the workspace
  * kan_layer_backward needs for this grid, dtype, batch and shape (the packed
- * weights of the dx contraction, dy transposed, and the fp32 partial weight
- * gradients of the batch splits).  Writes *bytes.  Returns KAN_OK,
+ * weights of the dx contraction, x and dy transposed, in fp32 their maxima per
+ * 64 rows, and the fp32 partial weight gradients of the batch splits).  Writes *bytes.  Returns KAN_OK,
  * KAN_ERR_INVALID_ARG (bytes == NULL, bad grid or sizes, batch < 0) or
  * KAN_ERR_UNSUPPORTED.
  */

@@ -1050,8 +1050,10 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     const int ot = g->oh * g->nfw * 32;
     g->otiles = (g->out32 + ot - 1) / ot;
     if (g->otiles > 65535) return false;
-    // dx: two 32-row tiles per wave (fp32: up to 64 outputs), and the K tiles split over workgroups (whole features
-    // each) until the grid fills the chip
+    // dx: two 32-row tiles per wave, each weight fragment read from LDS then feeding
+    // two MFMAs (fp32 only up to 64 outputs: its dy takes two terms, twice the
+    // registers of bf16), and the K tiles split over workgroups (whole features each)
+    // until the grid fills the chip
     g->dx_rf = bf16 || std::min(g->groups, g->gmax) <= 4 ? 2 : 1;
     {
         const int tpf = g->cp == 16 ? 1 : g->cp / 32;

@@ -263,8 +263,8 @@ struct BwdGeom {
     int ntiles;     // 32-row K tiles
     int kr;         // 32 ntiles
     int out32;      // out rounded up to 32 (rows of the transposed dy)
-    int groups;     // dx: k-step groups over all outputs (16 outputs bf16, 8 fp32)
-    int gmax;       // dx: groups per output chunk held in registers (256 outputs)
+    int groups;     // dx: k-step groups of 16 outputs over all outputs
+    int gmax;       // dx: groups per output chunk held in registers (16: 256 outputs)
     int nchunk;     // dx: output chunks (partial dx summed by a reduce when > 1)
     int dx_rf;      // dx: 32-row batch tiles per wave
     int dx_bm;      // dx: batch rows per workgroup

@@ -30,7 +30,9 @@
 // and 316 -> 80 us.  Coefficients are scaled per output column by the power of two
 // that brings the column's largest to [2^12, 2^13) (a column's smallest ones
 // then keep an absolute error of 2^-37 of its largest); basis values by 2^12.
-// A coefficient that is not finite has no such terms: it is taken as 0 and its
+// A coefficient that is not finite has no such terms, and in either dtype would
+// not meet exactly the values that it meets in the dense contraction (0 times
+// infinity is NaN): it is taken as 0, in bf16 also SiLU weights as finite, and the
 // terms are added at the end (fix_nonfinite).
 //
 // window_kernel: 8 waves, 256 rows x 64 NFW columns; the two waves of a 64-row
@@ -94,11 +96,13 @@ template <int NS> struct Elem;
 template <> struct Elem<2> {
     typedef float T;
     static __device__ __forceinline__ float val(uint32_t u) { return __uint_as_float(u); }
+    static __device__ __forceinline__ float val(float v) { return v; }
     static __device__ __forceinline__ void st(float* p, float v) { *p = v; }
 };
 template <> struct Elem<1> {
     typedef uint16_t T;
     static __device__ __forceinline__ float val(uint32_t u) { return __uint_as_float(u << 16); }
+    static __device__ __forceinline__ float val(uint16_t v) { return bf16_to_f32(v); }
     static __device__ __forceinline__ void st(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
@@ -207,6 +211,13 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
                 const T t = packed_at<T>(a, o, pair, f, c);
                 if constexpr (NS == 2) v[e] = t;
                 else v[e] = bf16_to_f32(t);
+                if (!(__builtin_fabsf(v[e]) < __builtin_inff())) {
+                    // (an infinite SiLU weight, which can meet an infinite value: the
+                    // largest finite one of its sign)
+                    const bool silu_inf = NS == 1 && c == 0 && v[e] == v[e];
+                    v[e] = silu_inf ? __builtin_copysignf(__uint_as_float(0x7f7f0000u), v[e]) : 0.0f;
+                    bad = 1;
+                }
             }
         }
         if constexpr (NS == 1) {
@@ -216,12 +227,7 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
             f16x8_t t0, t1;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float r = v[e];
-                if (!(__builtin_fabsf(r) < __builtin_inff())) {
-                    r = 0.0f;
-                    bad = 1;
-                }
-                r = __builtin_ldexpf(r, 12 - ex);
+                const float r = __builtin_ldexpf(v[e], 12 - ex);
                 t0[e] = (_Float16)r;
                 t1[e] = (_Float16)(r - (float)t0[e]);
             }
@@ -238,12 +244,10 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
             }
         }
     }
-    if constexpr (NS == 2) {
-        bad = __syncthreads_or(bad);
-        if (threadIdx.x == 0)
-            reinterpret_cast<int*>(static_cast<char*>(a.ws) + a.off_flag)[tile * a.steps + step] =
-                bad;
-    } else if (step == a.steps - 1) {
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0)
+        reinterpret_cast<int*>(static_cast<char*>(a.ws) + a.off_flag)[tile * a.steps + step] = bad;
+    if (NS == 1 && step == a.steps - 1) {
         // (a last step that fills a stage of two: zero weights)
         const int64_t left = (int64_t)(a.steps_pad - a.steps) * a.step_u;
         u32x4* end = dst0 + a.step_u;
@@ -255,12 +259,15 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
 
 // Adds to the workgroup's tile of outputs (already stored) the terms of the
 // non-finite coefficients (flagged steps), with the values and products the
-// dense contraction has (also 0 times an infinite coefficient, NaN).
-template <int K>
-__device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* dst, int64_t row_beg,
+// dense contraction has (also 0 times an infinite coefficient, NaN).  P: the
+// split's partial sums, or null.
+template <int NS, int K>
+__device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* P, int64_t row_beg,
                                               int col_beg, int bm, int t_beg, int t_end,
                                               const int* flag) {
-    const float* x = static_cast<const float*>(a.x);
+    typedef typename Elem<NS>::T T;
+    const T* x = static_cast<const T*>(a.x);
+    T* y = static_cast<T*>(a.y);
     for (int u = threadIdx.x; u < bm * a.bn; u += kThreads) {
         const int64_t row = row_beg + u / a.bn;
         const int o = col_beg + u % a.bn;
@@ -268,21 +275,25 @@ __device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* dst, int6
         float add = 0.0f;
         for (int t = t_beg; t < t_end && add == add; ++t) {
             if (flag[t] == 0) continue;
-            const int p = t / a.nbk, c_beg = max(16 * (t % a.nbk), 1);
+            // (fp32: the SiLU column, 0, is on its own instruction with its weights as given)
+            const int p = t / a.nbk, c_beg = max(16 * (t % a.nbk), NS == 2 ? 1 : 0);
             const int c_end = min(16 * (t % a.nbk) + 15, a.nb);
             for (int f = 0; f < 2 && 2 * p + f < a.in; ++f) {
-                const float xv = x[row * a.in + 2 * p + f];
+                const float xv = Elem<NS>::val(x[row * a.in + 2 * p + f]);
                 const float lo = coord_lo(xv, a.xlim, a.inv_lo, a.a_frac);
                 for (int c = c_beg; c <= c_end; ++c) {
-                    const float w = packed_at<float>(a, o, p, f, c);
+                    const float w = Elem<NS>::val(packed_at<T>(a, o, p, f, c));
                     if (__builtin_fabsf(w) < __builtin_inff()) continue;
                     const float v =
                         __builtin_fmaf(xv, a.inv_h, a.a_int + 1.0f - (float)c) + lo;
-                    add += half_basis_k<K>(v) * w;
+                    add += (c == 0 ? half_silu(xv) : half_basis_k<K>(v)) * w;
                 }
             }
         }
-        if (add != 0.0f) dst[row * a.out + o] += 2.0f * add;
+        if (add == 0.0f) continue;
+        const int64_t at = row * a.out + o;
+        if (P != nullptr) P[at] += 2.0f * add;
+        else Elem<NS>::st(y + at, Elem<NS>::val(y[at]) + 2.0f * add);
     }
 }
 
@@ -673,15 +684,13 @@ void window_kernel(WinArgs a) {
             }
         }
     }
-    if constexpr (NS == 2) {
-        const int* flag = reinterpret_cast<const int*>(static_cast<const char*>(a.ws) +
-                                                       a.off_flag) + tile * a.steps;
-        int bad = 0;
-        for (int t = t_beg + tid; t < t_beg + nst; t += kThreads) bad |= flag[t];
-        if (__syncthreads_or(bad))
-            fix_nonfinite<K>(a, P != nullptr ? P : reinterpret_cast<float*>(a.y), row_beg, col_beg,
-                             BM, t_beg, t_beg + nst, flag);
-    }
+    const int* flag = reinterpret_cast<const int*>(static_cast<const char*>(a.ws) + a.off_flag) +
+                      tile * a.steps;
+    const int t_end = min((st_beg + nst) * SPB, a.steps);
+    int bad = 0;
+    for (int t = t_beg + tid; t < t_end; t += kThreads) bad |= flag[t];
+    if (__syncthreads_or(bad))
+        fix_nonfinite<NS, K>(a, P, row_beg, col_beg, BM, t_beg, t_end, flag);
 }
 
 template <int NS, int NFW, bool MB>

@@ -51,7 +51,8 @@ CASES = [
     ("f32", 4096, 256, 64, 12, 3), ("f32", 4099, 255, 33, 13, 3), ("f32", 1024, 131, 129, 28, 3),
     ("f32", 1500, 67, 300, 29, 3), ("f32", 90001, 7, 64, 10, 3), ("f32", 12000, 300, 17, 1, 3),
     ("f32", 2000, 101, 257, 14, 1), ("f32", 6003, 64, 100, 9, 2), ("f32", 16500, 40, 65, 5, 3),
-    ("f32", 1024, 41, 200, 200, 3), ("f32", 70000, 3, 256, 10, 3),
+    ("f32", 1024, 41, 200, 200, 3), ("f32", 1025, 41, 190, 200, 1),
+    ("f32", 70000, 3, 256, 10, 3),
     ("bf16", 4099, 65, 75, 20, 2), ("bf16", 1111, 200, 64, 13, 1), ("bf16", 2050, 31, 260, 30, 2),
     ("bf16", 9001, 129, 129, 100, 3), ("bf16", 70001, 64, 256, 13, 3),
     ("bf16", 30001, 256, 64, 28, 3), ("bf16", 70000, 101, 255, 3, 3), ("bf16", 30001, 33, 40, 3, 1),
@@ -90,32 +91,32 @@ def test_window_kernel_weight_scales(ec, eb):
     assert normwise(y[rows], oracle.layer(x[rows], C, Wb, G)) <= F32_LAYER_TOL
 
 
-@pytest.mark.parametrize("dtype_name,n_out,G", [("f32", 64, 10), ("f32", 140, 30), ("bf16", 140, 30)])
-def test_window_kernel_non_finite(dtype_name, n_out, G):
+@pytest.mark.parametrize("dtype_name,n_out,G,k", [
+    ("f32", 64, 10, 3), ("f32", 140, 30, 3), ("bf16", 140, 30, 3), ("bf16", 140, 14, 2),
+    ("bf16", 60, 9, 1)])
+def test_window_kernel_non_finite(dtype_name, n_out, G, k):
     """NaN and infinite inputs, and NaN and infinite weights: NaN where the
     dense kernel gives NaN, the same infinities, and unaffected rows and outputs
     as without them.  (An infinite coefficient times a basis value of exactly 0 is
-    NaN in the dense contraction, and so here in fp32.)"""
+    NaN in the dense contraction, and so here.)"""
     B, n_in = (65536, 64) if dtype_name == "bf16" else (4096, 140)
-    x, C, Wb = _inputs(B, n_in, n_out, G, 3, dtype_name)
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, dtype_name)
     x[5, 3] = np.nan
     x[6, 2] = np.inf
     x[7, 2] = -np.inf
     x[B - 1, n_in - 1] = np.inf
-    cases = [(C, Wb)]
-    if dtype_name == "f32":
-        C2, Wb2 = C.copy(), Wb.copy()
-        C2[3, 1, 4] = np.inf
-        C2[4, 9, 0] = -np.inf
-        C2[5, 20, G + 2] = np.nan
-        Wb2[6, 2] = np.inf
-        Wb2[7, 33] = np.nan
-        cases.append((C2, Wb2))
-    assert _planned(B, n_in, n_out, G, 3, dtype_name)
+    C2, Wb2 = C.copy(), Wb.copy()
+    C2[3, 1, 4] = np.inf
+    C2[4, 9, 0] = -np.inf
+    C2[5, 20, G + k - 1] = np.nan
+    Wb2[6, 2] = np.inf
+    Wb2[7, 33] = np.nan
+    cases = [(C, Wb), (C2, Wb2)]
+    assert _planned(B, n_in, n_out, G, k, dtype_name)
     for c, w in cases:
-        say(f"window non-finite {dtype_name} out={n_out} G={G}")
-        y = _run(x, c, w, G, 3, dtype_name)
-        ref = _run(x, c, w, G, 3, dtype_name, split=False)
+        say(f"window non-finite {dtype_name} out={n_out} G={G} k={k}")
+        y = _run(x, c, w, G, k, dtype_name)
+        ref = _run(x, c, w, G, k, dtype_name, split=False)
         assert np.array_equal(np.isnan(y), np.isnan(ref))
         inf = np.isinf(ref)
         assert np.array_equal(y[inf], ref[inf]) and np.array_equal(inf, np.isinf(y))
