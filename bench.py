@@ -89,7 +89,7 @@ def copy_calibration(nbytes: int) -> None:
 
 
 def layer_roofline(dtype: str, batch: int, n_in: int, n_out: int, nb: int,
-                   narrow: bool = False) -> dict:
+                   narrow: bool = False, window: bool = False) -> dict:
     """Roofline of one fused layer: bound by the matrix cores (dense flops,
     all nb bases plus the SiLU column per input) unless generating its basis
     values (the least VALU work, four nonzero columns per input) takes longer
@@ -97,7 +97,10 @@ def layer_roofline(dtype: str, batch: int, n_in: int, n_out: int, nb: int,
     then it is reported against the VALU.  A layer that runs on the
     vector-ALU kernel of narrow fp32 layers (`narrow`) is reported against the
     VALU with that kernel's least work: the basis generation plus one fma per
-    output for each of the five nonzero columns (SiLU and four bases)."""
+    output for each of the five nonzero columns (SiLU and four bases).  A layer
+    on the window kernel (`window`) uses the 16-bit matrix cores in fp32 too (two
+    fp16 terms per operand): its dense flops, counted once, are reported against
+    their peak."""
     flop = 2.0 * batch * n_out * n_in * (nb + 1)
     valu = VALU_OPS_PER_FEATURE[dtype] * batch * n_in
     if narrow:
@@ -108,8 +111,11 @@ def layer_roofline(dtype: str, batch: int, n_in: int, n_out: int, nb: int,
         k = {"bound": "alu", "unit": "Gop/s", "peak": PEAK_VALU_GOPS,
              "algorithmic": valu / 1e9}  # G lane-ops
     else:
-        k = {"bound": "mfma", "unit": "TFLOP/s", "peak": PEAK_TFLOPS[dtype],
+        k = {"bound": "mfma", "unit": "TFLOP/s",
+             "peak": PEAK_TFLOPS["bf16" if window else dtype],
              "algorithmic": flop / 1e12}  # dense TFLOP
+        if window:
+            k["kernel"] = "window kernel"
     k["valu_gops"] = valu / 1e9
     k["valu_gops_dense"] = (VALU_OPS_PER_VALUE_DENSE * nb + 4.0) * batch * n_in / 1e9
     return k
@@ -125,7 +131,21 @@ def planned_narrow(kb, dtype: str, G: int, lo: float, hi: float, batch: int, n_i
     return plan[0] == 0
 
 
-KERNEL_SOURCES = ["kan_layer_kernel.h", "kan_layer.hip", "kan_internal.h", "kan_device.h"]
+def planned_window(kb, dtype: str, G: int, lo: float, hi: float, batch: int, n_in: int,
+                   n_out: int) -> bool:
+    """Whether the library plans the window kernel for this layer and batch (it then
+    asks for a workspace of its own instead of the split's)."""
+    args = (kb.make_grid(G, lo, hi), kb.KAN_BF16 if dtype == "bf16" else kb.KAN_F32, batch, n_in,
+            n_out)
+    st, full = kb.kan_layer_forward_packed_full_workspace_bytes(*args)
+    kb.check(st)
+    st, split = kb.kan_layer_forward_packed_workspace_bytes(*args)
+    kb.check(st)
+    return full != split
+
+
+KERNEL_SOURCES = ["kan_layer_kernel.h", "kan_window_kernel.h", "kan_layer.hip", "kan_internal.h",
+                  "kan_device.h"]
 
 
 def traffic_record(dtype: str, kernel: str, root: str = ROOT):
@@ -319,7 +339,8 @@ def configs_sweep(dtype: str) -> None:
             lus = _time_us(lambda: kb.layer_forward_packed(h, pk, out=out), 50, 200,
                            CONFIG_WARM_S)
             k = layer_roofline(dtype, B, C.shape[1], C.shape[0], nb,
-                               planned_narrow(kb, dtype, G, lo, hi, B, C.shape[1], C.shape[0]))
+                               planned_narrow(kb, dtype, G, lo, hi, B, C.shape[1], C.shape[0]),
+                               planned_window(kb, dtype, G, lo, hi, B, C.shape[1], C.shape[0]))
             k.pop("valu_gops")
             k.pop("valu_gops_dense")
             k.update(us=lus, samples_per_s=B / lus * 1e6, achieved=k["algorithmic"] / (lus * 1e-6))
@@ -496,7 +517,8 @@ def measure_step(dtype: str, W, steps: int, warmup: int, clock_warmup_s: float =
             "bound": "hbm", "unit": "GB/s", "peak": PEAK_HBM_GBS,
             "algorithmic": (o * i_ * (nb + 1) * es + packs[li].nbytes) / 1e9}
         kern[names[2 + 2 * li]] = layer_roofline(dtype, B, i_, o, nb,
-                                                 planned_narrow(kb, dtype, G, lo, hi, B, i_, o))
+                                                 planned_narrow(kb, dtype, G, lo, hi, B, i_, o),
+                                                 planned_window(kb, dtype, G, lo, hi, B, i_, o))
         # HBM bytes the layer must move: x, the packed weights once, y
         kern[names[2 + 2 * li]]["algorithmic_bytes"] = (B * (i_ + o) * es + packs[li].nbytes)
     for name, ms in zip(names, per_kernel_ms):
@@ -527,7 +549,8 @@ def backward_block(dtype: str, W, r: dict, reps: int = 10) -> dict:
     with HIP events on torch's current stream.  Work: the two contractions
     dx = dy W^T and [dcoef dbase_w] = A^T dy over all G + 4 columns of the
     layer (A: SiLU and basis values of x), 2 B out in (G + 4) dense flops
-    each, against the MFMA peak of the dtype."""
+    each, counted once, against the 16-bit MFMA peak: both dtypes run there at
+    these sizes (fp32 as two fp16 terms per operand)."""
     import torch
 
     from paper_2609_01956_amd import binding as kb
@@ -556,9 +579,9 @@ def backward_block(dtype: str, W, r: dict, reps: int = 10) -> dict:
                       warmup=2, reps=reps)
         flop = 2 * 2.0 * B * n_out * n_in * (nb + 1)
         layers[f"layer{li + 1}_{n_in}x{n_out}"] = {
-            "avg_us": us, "bound": "mfma", "unit": "TFLOP/s", "peak": PEAK_TFLOPS[dtype],
+            "avg_us": us, "bound": "mfma", "unit": "TFLOP/s", "peak": PEAK_TFLOPS["bf16"],
             "achieved": flop / (us * 1e-6) / 1e12,
-            "frac": flop / (us * 1e-6) / 1e12 / PEAK_TFLOPS[dtype]}
+            "frac": flop / (us * 1e-6) / 1e12 / PEAK_TFLOPS["bf16"]}
         total += us
     return {"ms_all_layers": total * 1e-3, "layers": layers,
             "step": "kan_layer_backward (dx, dcoef, dbase_w) per layer"}
@@ -573,7 +596,8 @@ def grid_sweep_block(dtype: str = "f32") -> dict:
     MFMA over all G + 4 columns) and the span-sparse one (kan_layer_forward_span,
     its weight transposition included: only the k + 1 nonzero bases and SiLU
     per input, on the vector ALUs), with the partition-of-unity error of the
-    basis kernel on the same inputs.  Dense work against the MFMA peak; the
+    basis kernel on the same inputs.  Dense work against the 16-bit MFMA peak
+    (the dense entry point runs these layers on the window kernel); the
     span path's multiply-adds (B in out (k + 2)) and its least basis work (38
     lane-ops per input) against the VALU peak."""
     import numpy as np
@@ -610,7 +634,7 @@ def grid_sweep_block(dtype: str = "f32") -> dict:
         lane_ops = B * n_in * (5.0 * n_out + 38.0)
         out[name] = {"grid_size": G, "dense_us": dense, "span_us": span,
                      "samples_per_s": B / (min(dense, span) * 1e-6),
-                     "dense_mfma_frac": flop / (dense * 1e-6) / 1e12 / PEAK_TFLOPS[dtype],
+                     "dense_mfma_frac": flop / (dense * 1e-6) / 1e12 / PEAK_TFLOPS["bf16"],
                      "span_valu_frac": lane_ops / (span * 1e-6) / 1e9 / PEAK_VALU_GOPS,
                      "pu_max_err": float((pu - 1.0).abs().max())}
     return {"dtype": dtype, "grids": out}

@@ -46,6 +46,13 @@ def test_narrow_kernel_layer_roofline():
     assert k["peak"] == pytest.approx(256 * 4 * 32 * 2.4)
 
 
+def test_window_kernel_layer_roofline():
+    # the dense flops, counted once, against the 16-bit matrix cores also in fp32
+    k = bench.layer_roofline("f32", 65536, 784, 256, 13, window=True)
+    assert k["algorithmic"] == pytest.approx(2.0 * 65536 * 256 * 784 * 14 / 1e12)
+    assert k["peak"] == bench.PEAK_TFLOPS["bf16"]
+
+
 def _fake_tree(tmp_path, record_md5):
     csrc = tmp_path / "paper_2609_01956_amd" / "csrc"
     csrc.mkdir(parents=True)
