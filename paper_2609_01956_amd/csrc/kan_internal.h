@@ -348,20 +348,20 @@ struct SpanGeom {
     int otiles;      // output tiles of opt * ng columns
     int outp;        // out padded to whole tiles (columns of the transposed weights)
     int fs, fpf;     // feature splits (partials summed when > 1), features per split
-    int cs;          // LDS stride of one weight column in floats (tile width, padded)
+    int cs;          // fp32: LDS stride of one weight column in floats (tile width, padded)
     int64_t rblocks; // row blocks of 256 nr / ng rows
-    size_t off_w, off_p, bytes;  // workspace: transposed fp32 weights, partial sums
+    size_t off_w, off_p, bytes;  // workspace: transposed weights (four bytes each), partial sums
 };
 bool span_geom(int nb, int64_t batch, int in, int out, SpanGeom* g);
 
 struct SpanArgs {
     const void* x;    // [batch, in]
-    const float* wt;  // transposed weights [in][nb + 1][outp] (set by the launcher)
+    const void* wt;   // transposed weights [in][nb + 1][outp] (set by the launcher)
     void* y;          // [batch, out]
     void* ws;         // workspace of SpanGeom::bytes
     size_t off_p;
     int64_t batch;
-    int in, out, nb, outp, fs, fpf, cs;
+    int in, out, nb, outp, fs, fpf, csu;  // csu: LDS stride of a weight column in 16-byte units
     float inv_h, inv_lo, xlim, a_int, a_frac;
     int kdeg;
     float hw;

@@ -15,9 +15,14 @@
 // is (k + 2) rows of weights instead of G + k + 1.
 //
 // The window differs per row, so the contraction is a gather: each
-// workgroup stages one feature's weights [column][its output tile] (fp32) in
-// LDS, double-buffered, and every thread accumulates its rows' outputs on
-// the vector ALUs from the (k + 2) weight rows its rows select.  Features
+// workgroup stages one feature's weights [column][its output tile] in LDS,
+// double-buffered, and every thread accumulates its rows' outputs in fp32 on
+// the vector ALUs from the (k + 2) weight rows its rows select.  The LDS reads of
+// those rows bound the kernel, so bf16 weights stay bf16 there and are widened
+// (exactly) in registers: half the bytes per multiply-add (8192 x 128 -> 128,
+// G = 200, bf16: 114.2 -> 105.6 us per call, the same outputs; what remains is the
+// vector ALUs' unpacking and waits at two waves per SIMD: one row per thread, for
+// three waves, took 110 us, registers cut for more waves spill).  Features
 // are split over workgroups when the row blocks do not fill the chip; the
 // partial sums are then added in a fixed order by a reduce kernel.
 #include "kan_internal.h"
@@ -32,26 +37,25 @@ constexpr int64_t kSpanTargetWgs = 512;
 
 template <typename T> struct S;
 template <> struct S<float> {
-    static __device__ __forceinline__ float ld(const float* p) { return *p; }
     static __device__ __forceinline__ float val(float v) { return v; }
     static __device__ __forceinline__ void st(float* p, float v) { *p = v; }
 };
 template <> struct S<uint16_t> {
-    static __device__ __forceinline__ float ld(const uint16_t* p) { return bf16_to_f32(*p); }
     static __device__ __forceinline__ float val(uint16_t v) { return bf16_to_f32(v); }
     static __device__ __forceinline__ void st(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
-// Transposed fp32 weights: wt[f][c][o] for o < outp (zero past `out`),
+// Transposed weights, in their own type: wt[f][c][o] for o < outp (zero past `out`),
 // c = 0 the SiLU weight, c = 1 .. nb the spline coefficients.  One workgroup
 // moves a 64 x 64 tile (outputs x columns) of one feature through LDS, so the
 // reads run along a coefficient row and the writes along the outputs.
 template <typename T>
 __global__ __launch_bounds__(256) void span_pack_kernel(const T* __restrict__ coef,
                                                         const T* __restrict__ bw,
-                                                        float* __restrict__ wt, int in, int out,
+                                                        T* __restrict__ wt, int in, int out,
                                                         int nb, int outp) {
-    __shared__ float tile[64][65];
+    // (rows of an odd number of 32-bit words in either type)
+    __shared__ T tile[64][sizeof(T) == 2 ? 66 : 65];
     const int f = blockIdx.x, o0 = blockIdx.y * 64, c0 = blockIdx.z * 64;
     const int ncol = nb + 1;
 #pragma unroll
@@ -59,10 +63,10 @@ __global__ __launch_bounds__(256) void span_pack_kernel(const T* __restrict__ co
         const int idx = threadIdx.x + 256 * i;
         const int ol = idx / 64, cl = idx % 64;
         const int o = o0 + ol, c = c0 + cl;
-        float v = 0.0f;
+        T v = T(0);
         if (o < out && c < ncol) {
             const int64_t row = (int64_t)o * in + f;
-            v = c == 0 ? S<T>::ld(bw + row) : S<T>::ld(coef + row * nb + c - 1);
+            v = c == 0 ? bw[row] : coef[row * nb + c - 1];
         }
         tile[ol][cl] = v;
     }
@@ -85,12 +89,13 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
     constexpr int OT = OPT * NG;
     constexpr int RL = kThreads / NG;  // row lanes
     constexpr int RW = RL * NR;        // rows per workgroup
-    extern __shared__ floatx4 wl4[];    // [2][ncol][cs] floats
-    float* wl = reinterpret_cast<float*>(wl4);
+    constexpr bool BF = sizeof(T) == 2;
+    constexpr int EU = 16 / (int)sizeof(T);  // weights per 16-byte unit
+    extern __shared__ u32x4 wl[];      // [2][ncol][csu] units; bf16: then a column of zeros
     const int ncol = a.nb + 1;
-    const int stage_f = ncol * a.cs;   // LDS floats per stage
-    const int stage_u = ncol * OT / 4; // 16-byte units of the tile per stage
-    const int csu = a.cs / 4;          // column stride in 16-byte units
+    const int csu = a.csu;             // column stride in units
+    const int stage_l = ncol * csu;    // LDS units per stage
+    const int stage_u = ncol * OT / EU; // units of the tile per stage
 
     const int tid = threadIdx.x;
     const int og = tid % NG, rl = tid / NG;
@@ -113,13 +118,15 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
 #pragma unroll
         for (int o = 0; o < OPT; ++o) acc[r][o] = 0.0f;
 
-    // staging of feature f's weight tile: unit u = (c, o / 4) of the tile
-    auto stage_src = [&](int f, int u) -> const floatx4* {
-        const int c = u / (OT / 4), oq = u % (OT / 4);
-        return reinterpret_cast<const floatx4*>(a.wt + ((int64_t)f * ncol + c) * a.outp + ot0) + oq;
+    // staging of feature f's weight tile: unit u = (c, o / EU) of the tile
+    auto stage_src = [&](int f, int u) -> const u32x4* {
+        const int c = u / (OT / EU), oq = u % (OT / EU);
+        return reinterpret_cast<const u32x4*>(static_cast<const T*>(a.wt) +
+                                              ((int64_t)f * ncol + c) * a.outp + ot0) + oq;
     };
-    constexpr int MAXU = kSpanLdsBytes / 2 / 16 / kThreads;  // 16-byte units per thread per stage
-    floatx4 reg[MAXU];
+    // units per thread per stage
+    constexpr int MAXU = kSpanLdsBytes / 2 / 16 / kThreads * (int)sizeof(T) / 4;
+    u32x4 reg[MAXU];
     const int upt = (stage_u + kThreads - 1) / kThreads;
     auto issue = [&](int f) {
         const int fc = min(f, f1 - 1);
@@ -132,7 +139,23 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
         for (int k = 0; k < MAXU; ++k) {
             const int u = tid + k * kThreads;
             if (k < upt && u < stage_u)
-                wl4[buf * (stage_f / 4) + (u / (OT / 4)) * csu + u % (OT / 4)] = reg[k];
+                wl[buf * stage_l + (u / (OT / EU)) * csu + u % (OT / EU)] = reg[k];
+        }
+    };
+    // acc[r] += b times the weights at wp
+    auto add_column = [&](float (&ar)[OPT], float b, const u32x4* wp) {
+#pragma unroll
+        for (int q = 0; q < OPT / EU; ++q) {
+            const u32x4 wv = wp[q];
+#pragma unroll
+            for (int e = 0; e < EU; ++e) {
+                float w;
+                if constexpr (BF)
+                    w = __uint_as_float(e & 1 ? wv[e / 2] & 0xffff0000u : wv[e / 2] << 16);
+                else
+                    w = __uint_as_float(wv[e]);
+                ar[EU * q + e] = __builtin_fmaf(b, w, ar[EU * q + e]);
+            }
         }
     };
 
@@ -147,6 +170,8 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
     };
     issue(f0);
     issue_x(f0);
+    if constexpr (BF)
+        if (tid < OT / EU) wl[2 * stage_l + tid] = u32x4{0u, 0u, 0u, 0u};
     put(0);
     __syncthreads();
     for (int f = f0; f < f1; ++f) {
@@ -158,7 +183,8 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
             issue(f + 1);
             issue_x(f + 1);
         }
-        const float* w = wl + buf * stage_f + og * OPT;
+        const u32x4* w = wl + buf * stage_l + og * (OPT / EU);
+        const u32x4* wzero = wl + 2 * stage_l + og * (OPT / EU);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const float xv = xf[r];
@@ -166,36 +192,21 @@ __global__ __launch_bounds__(kThreads) void span_kernel(SpanArgs a) {
             const float s = __builtin_amdgcn_fmed3f(__builtin_fmaf(xv, a.inv_h, c0) + lot, -16.0f,
                                                    (float)(ncol + 16));
             const int clo = (int)__builtin_floorf(s - a.hw) + 1;
-            // SiLU column
-            {
-                const float sl = silu(xv);
-                const floatx4* wp = reinterpret_cast<const floatx4*>(w);
-#pragma unroll
-                for (int q = 0; q < OPT / 4; ++q) {
-                    const floatx4 wv = wp[q];
-                    acc[r][4 * q] = __builtin_fmaf(sl, wv[0], acc[r][4 * q]);
-                    acc[r][4 * q + 1] = __builtin_fmaf(sl, wv[1], acc[r][4 * q + 1]);
-                    acc[r][4 * q + 2] = __builtin_fmaf(sl, wv[2], acc[r][4 * q + 2]);
-                    acc[r][4 * q + 3] = __builtin_fmaf(sl, wv[3], acc[r][4 * q + 3]);
-                }
-            }
+            add_column(acc[r], silu(xv), w);
             for (int m = 0; m < kw; ++m) {
                 const int c = clo + m;
-                if (c < 1 || c > a.nb) continue;
+                const bool in_grid = c >= 1 && c <= a.nb;
+                // (bf16: a column past the grid's ends reads zeros, so the columns'
+                // reads are in flight together; fp32 has no LDS to spare for them at
+                // the widest grids)
+                if constexpr (!BF)
+                    if (!in_grid) continue;
                 // v of column c in one rounding at its own magnitude
                 const float v = __builtin_fmaf(xv, a.inv_h, c0 - (float)c) + lot;
                 float bv;
                 if constexpr (GD) bv = 2.0f * half_basis_deg(v, a.kdeg, a.hw, a.hc);
                 else bv = 2.0f * half_basis(v);
-                const floatx4* wp = reinterpret_cast<const floatx4*>(w + c * a.cs);
-#pragma unroll
-                for (int q = 0; q < OPT / 4; ++q) {
-                    const floatx4 wv = wp[q];
-                    acc[r][4 * q] = __builtin_fmaf(bv, wv[0], acc[r][4 * q]);
-                    acc[r][4 * q + 1] = __builtin_fmaf(bv, wv[1], acc[r][4 * q + 1]);
-                    acc[r][4 * q + 2] = __builtin_fmaf(bv, wv[2], acc[r][4 * q + 2]);
-                    acc[r][4 * q + 3] = __builtin_fmaf(bv, wv[3], acc[r][4 * q + 3]);
-                }
+                add_column(acc[r], bv, BF && !in_grid ? wzero : w + c * csu);
             }
             // a NaN input: whatever window its clamped coordinate selects,
             // the SiLU term carries the NaN into every output of the row
@@ -233,7 +244,7 @@ __global__ __launch_bounds__(256) void span_reduce_kernel(const float* __restric
 template <typename T, int OPT, int NG, int NR>
 hipError_t launch_span_shape(const SpanGeom& g, const SpanArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)g.rblocks, (unsigned)g.fs, (unsigned)g.otiles);
-    const size_t lds = 2 * (size_t)(a.nb + 1) * a.cs * 4;
+    const size_t lds = (2 * (size_t)(a.nb + 1) + (sizeof(T) == 2)) * a.csu * 16;
     if (a.kdeg == 3)
         hipLaunchKernelGGL((span_kernel<T, OPT, NG, NR, false>), grid, dim3(kThreads), lds, s, a);
     else
@@ -245,7 +256,7 @@ template <typename T>
 hipError_t span_t(const SpanGeom& g, SpanArgs a, const void* coef, const void* bw,
                   hipStream_t s) {
     char* ws = static_cast<char*>(a.ws);
-    float* wt = reinterpret_cast<float*>(ws + g.off_w);
+    T* wt = reinterpret_cast<T*>(ws + g.off_w);
     const dim3 pgrid((unsigned)a.in, (unsigned)((g.outp + 63) / 64),
                      (unsigned)((a.nb + 1 + 63) / 64));
     hipLaunchKernelGGL(span_pack_kernel<T>, pgrid, dim3(256), 0, s, static_cast<const T*>(coef),
@@ -257,7 +268,8 @@ hipError_t span_t(const SpanGeom& g, SpanArgs a, const void* coef, const void* b
     a.fpf = g.fpf;
     a.fs = g.fs;
     a.off_p = g.off_p;
-    a.cs = g.cs;
+    // (bf16: the padding always fits)
+    a.csu = sizeof(T) == 2 ? g.opt * g.ng / 8 + 1 : g.cs / 4;
     if (g.opt == 16 && g.ng == 1 && g.nr == 2) e = launch_span_shape<T, 16, 1, 2>(g, a, s);
     else if (g.opt == 32 && g.ng == 1 && g.nr == 2) e = launch_span_shape<T, 32, 1, 2>(g, a, s);
     else e = hipErrorInvalidValue;

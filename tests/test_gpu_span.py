@@ -183,3 +183,26 @@ def test_span_reuses_workspace():
     torch.cuda.synchronize()
     _check(ya, x1, C1, W1, G, 3, -1.0, 1.0, "f32")
     _check(yb, x2, C2, W2, G, 3, -1.0, 1.0, "f32")
+
+
+@pytest.mark.parametrize("dtype_name", ["f32", "bf16"])
+@pytest.mark.parametrize("n_out", [10, 70])
+def test_span_columns_past_the_grid_are_not_read(n_out, dtype_name):
+    """Inputs whose window reaches past the grid's ends, or lies wholly outside, take
+    no weight from there: infinite first and last coefficients leave the rows whose
+    window does not hold those columns as they are, bit for bit."""
+    G, n_in = 50, 5
+    _, C, Wb = _case(8, n_in, n_out, G, 3, -1.0, 1.0, dtype_name, seed=3)
+    h = 2.0 / G
+    # wholly outside on either side, and on the grid away from the first and last basis
+    x = np.float32([-4.0, -1.0 - 6 * h, -0.5, 0.01, 0.5, 1.0 + 6 * h, 4.0])
+    x = np.repeat(x[:, None], n_in, axis=1)
+    dt = _dt(dtype_name)
+    say(f"span past the grid {dtype_name} out={n_out}")
+    y = kb.layer_forward_span(to_dev(x, dt), to_dev(C, dt), to_dev(Wb, dt), G)
+    Ci = C.copy()
+    Ci[:, :, 0] = np.inf
+    Ci[:, :, -1] = np.inf
+    yi = kb.layer_forward_span(to_dev(x, dt), to_dev(Ci, dt), to_dev(Wb, dt), G)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.equal(y, yi)
