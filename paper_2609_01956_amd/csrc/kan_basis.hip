@@ -114,19 +114,22 @@ __global__ __launch_bounds__(kThreads) void basis_kernel(const T* __restrict__ x
 // many: with one run per workgroup such a kernel waits on its load of x longer
 // than its stores take (65536 x 784, G = 10, bf16, fresh buffers: 334 us, 4.0 TB/s
 // of writes, where a plain fill takes 193 us), and all nb values per input keep the
-// vector ALUs busy for as long as the writes.  Here a workgroup takes `runs` runs
+// vector ALUs busy for as long as the writes.  Here a workgroup takes R runs
 // (spaced by the grid, so that the workgroups write one front), loads the inputs of
 // all of them before its first store (a load waited for later would wait for the
 // stores too), and evaluates only the k + 1 consecutive values of an input that can
 // be nonzero (eq. bounded), each by the same closed form; the rest of its two LDS
 // stages is zero: a thread clears the window it wrote two runs before in a stage
-// and writes the new one, in output order and type.  267 us.
-constexpr int kBasisRuns = 8;
+// and writes the new one, in output order and type.  Four runs, or eight of at most
+// 4 KB (65536 x 784, bf16, fresh buffers / the same ones again, one run per
+// workgroup here 340 / 246-278 us at G = 10, 300 / 214 at G = 5; G = 10: eight runs
+// 263 / 245-251, four 260 / 221-228, two 302 / 222-232; G = 5: eight 176 / 170-176,
+// four 200 / 156-160; 65536 x 256, G = 10: eight 81-84, four 70-71).
+constexpr int basis_runs(int nb) { return nb <= 8 ? 8 : 4; }
 
-template <typename T, int K>
+template <typename T, int K, int R>
 __global__ __launch_bounds__(kThreads) void basis_runs_kernel(const T* __restrict__ x, int64_t n,
-                                                              T* __restrict__ phi, GridConst g,
-                                                              int runs) {
+                                                              T* __restrict__ phi, GridConst g) {
     extern __shared__ u32x4 stage4[];
     constexpr int V = 16 / (int)sizeof(T);
     // degrees 1 and 2, whose values rise linearly or quadratically from the support's
@@ -139,20 +142,20 @@ __global__ __launch_bounds__(kThreads) void basis_runs_kernel(const T* __restric
     auto first_of = [&](int run) -> int64_t {
         return ((int64_t)run * gridDim.x + blockIdx.x) * kThreads;
     };
-    T xq[kBasisRuns];
+    T xq[R];
 #pragma unroll
-    for (int i = 0; i < kBasisRuns; ++i) {
-        const int64_t e = first_of(i < runs ? i : 0) + tid;
+    for (int i = 0; i < R; ++i) {
+        const int64_t e = first_of(i) + tid;
         xq[i] = x[e < n ? e : n - 1];
     }
     for (int i = tid; i < 2 * stage_u; i += kThreads) stage4[i] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
     int old[2] = {tid * nb, tid * nb};  // window written two runs ago in each stage
     bool oldnan[2] = {false, false};
-    StaticFor<0, kBasisRuns>::run([&](auto rr) {
+    StaticFor<0, R>::run([&](auto rr) {
         constexpr int r = decltype(rr)::value, b = r & 1;
         const int64_t e0 = first_of(r);
-        if (r >= runs || e0 >= n) return;  // (the same for the workgroup)
+        if (e0 >= n) return;  // (the same for the workgroup)
         const int cnt = (int)(n - e0 < kThreads ? n - e0 : kThreads);
         T* st = stage + b * stage_u * V;
         const float xv = Storage<T>::load(&xq[r]);
@@ -292,8 +295,8 @@ __global__ __launch_bounds__(64) void basis_cdb_lds_kernel(const T* __restrict__
 BasisLaunch plan_basis(int64_t n, int nb, int k, int es, const void* phi) {
     BasisLaunch L;
     // The many-run kernel: bf16, short runs (at most 16 values per input) and enough
-    // of them for 8192 workgroups of eight runs (65536 x 784, G = 10: 267 us against
-    // 335; 65536 x 256: 72 against 83; 16384 x 256, 16384 runs: 20 against 18.6;
+    // of them (65536 x 784, G = 10: 260 us against 340; 65536 x 256: 70 against 79;
+    // with eight runs 16384 x 256, 16384 runs: 20 against 18.6;
     // longer runs, 60000 x 300, G = 25: 187 against 172; fp32 runs of the same bytes,
     // 65536 x 300, G = 5: 115 against 99), with room for the window, and an aligned
     // output (every run then starts on 16 bytes).
@@ -301,9 +304,9 @@ BasisLaunch plan_basis(int64_t n, int nb, int k, int es, const void* phi) {
     const int64_t nruns = (n + kThreads - 1) / kThreads;
     if (es == 2 && nb <= 16 && nb >= k + 2 && nruns >= 8 * 8192 &&
         reinterpret_cast<uintptr_t>(phi) % 16 == 0) {
-        L.runs = kBasisRuns;
+        L.runs = basis_runs(nb);
         L.lds = (size_t)2 * kThreads * nb * es;
-        L.blocks = (nruns + kBasisRuns - 1) / kBasisRuns;
+        L.blocks = (nruns + L.runs - 1) / L.runs;
         return L;
     }
     // Smallest power-of-two split of each input's nb values over threads that
@@ -327,8 +330,12 @@ static hipError_t launch_k(const T* x, int64_t n, T* phi, const GridConst& g,
                            const BasisLaunch& L, hipStream_t s) {
     if constexpr (sizeof(T) == 2) {
         if (L.runs > 0) {
-            hipLaunchKernelGGL((basis_runs_kernel<T, K>), dim3((unsigned)L.blocks),
-                               dim3(kThreads), L.lds, s, x, n, phi, g, L.runs);
+            if (L.runs == 8)
+                hipLaunchKernelGGL((basis_runs_kernel<T, K, 8>), dim3((unsigned)L.blocks),
+                                   dim3(kThreads), L.lds, s, x, n, phi, g);
+            else
+                hipLaunchKernelGGL((basis_runs_kernel<T, K, 4>), dim3((unsigned)L.blocks),
+                                   dim3(kThreads), L.lds, s, x, n, phi, g);
             return hipGetLastError();
         }
     }
