@@ -258,9 +258,15 @@ kan_status kan_layer_forward_packed_workspace_bytes(const kan_grid* grid, kan_dt
  * the narrow fp32 ones, of degrees 1 to 3, the window kernel's expanded
  * weights and partial sums.  That kernel contracts only the k + 1 basis
  * columns whose support holds each input, on the structured-sparse matrix
- * instruction; in fp32 every basis value and coefficient is the sum of two
- * fp16 terms (scaled per output column) and the SiLU column stays in fp32,
- * with fp32 accumulation: the same result up to the fp32 summation order.
+ * instruction, with fp32 accumulation.  In fp32 every basis value and
+ * coefficient is the sum of two fp16 terms: 22 bits, where the largest of any
+ * k + 1 consecutive coefficients (those that one input meets) is 0 or within
+ * 2^-15 of its output column's largest coefficient and 2^-39 of its largest SiLU
+ * weight; the SiLU column stays in fp32.  Columns outside that range, and sums
+ * that are not finite, are taken with the fp32 instruction on 24-bit operands.
+ * Without the workspace the result differs by these roundings and the summation
+ * order (relative error against float64, 2-norm, 65536 x 784 -> 256, G = 10:
+ * 8.7e-7 with, 1.1e-6 without).
  * An infinite or NaN coefficient times a basis value of exactly 0 is NaN, as
  * without the workspace.  A smaller workspace runs the layer as kan_layer_plan
  * reports.

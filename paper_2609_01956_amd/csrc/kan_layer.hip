@@ -406,7 +406,7 @@ bool plan_window(const LayerGeom& g, bool bf16, int64_t batch, int in, int out, 
         return at;
     };
     w->off_w = take((size_t)w->ntiles * (size_t)(stages * w->spb * step_bytes));
-    w->off_cm = take(bf16 ? 0 : (size_t)kColGroups * out * 8);
+    w->off_cm = take(bf16 ? 0 : (size_t)kColGroups * out * 16);
     w->off_us = take(bf16 ? 0 : (size_t)w->ntiles * w->bn * 4);
     w->off_flag = take((size_t)w->ntiles * w->steps * 4);
     w->off_p = take(w->ks > 1 ? (size_t)w->ks * (size_t)batch * out * 4 : 0);

@@ -28,12 +28,18 @@
 // float64 at 65536 x 784 -> 256, G = 10: 8.7e-7, with the fp32 instruction 1.1e-6;
 // 8192 x 128 -> 128, G = 100: 1.8e-7 both.  Times at these sizes: 3198 -> 634 us
 // and 316 -> 80 us.  Coefficients are scaled per output column by the power of two
-// that brings the column's largest to [2^12, 2^13) (a column's smallest ones
-// then keep an absolute error of 2^-37 of its largest); basis values by 2^12.
-// A coefficient that is not finite has no such terms, and in either dtype would
-// not meet exactly the values that it meets in the dense contraction (0 times
-// infinity is NaN): it is taken as 0, in bf16 also SiLU weights as finite, and the
-// terms are added at the end (fix_nonfinite).
+// that brings the column's largest to [2^12, 2^13), and basis values by 2^12; a
+// column's coefficients then have an absolute error of 2^-37 of its largest.  That
+// is 2^-22 or less of the largest of any k + 1 consecutive coefficients of a
+// feature (what one input meets) where none of these windows but empty ones is
+// 2^15 below the column's scale.  A workgroup with a column that does not meet
+// this (colmax_kernel), or with a sum that is not finite (a coefficient or an input
+// that is not, or a SiLU value that only the scaled weight takes past fp32), takes
+// its sums over all columns on the fp32 instruction (dense_tile) instead.
+// bf16: a weight that is not finite would not meet exactly the values that it
+// meets in the dense contraction (0 times infinity is NaN): it is taken as 0, an
+// infinite SiLU weight as finite, and the terms are added at the end
+// (fix_nonfinite).
 //
 // window_kernel: 8 waves, 256 rows x 64 NFW columns; the two waves of a 64-row
 // group take the two column halves, each generates the A of one of the group's
@@ -118,74 +124,111 @@ __device__ __forceinline__ T packed_at(const WinArgs& a, int o, int pair, int f,
     return static_cast<const T*>(a.wp)[((blk * 2 + f) * a.pk_ntile + n) * KJ + c % KJ];
 }
 
-// Largest finite |coefficient| and |SiLU weight| of each output column over the
-// pairs of group blockIdx.y: colmax[group][output] (16 columns per workgroup).
-static __global__ __launch_bounds__(256) void colmax_kernel(WinArgs a) {
-    __shared__ floatx2 red[16][17];
+// Columns of a window whose largest is 2^kWindowBits below the column's scale lose
+// more than the last two bits of an fp32 value.
+constexpr int kWindowBits = 15;
+
+// Per output column over the pairs of group blockIdx.y (16 columns per workgroup),
+// colmax[group][output] = largest finite |coefficient|, largest finite |SiLU
+// weight|, and the least nonzero maximum of any k + 1 consecutive coefficients of
+// a feature (infinity: there is none; 0: a coefficient is not finite).  A thread
+// takes 8 units of two columns of a feature at a time, and the two before them for
+// the windows that begin there, all ten in flight: its reads bound this kernel.
+static __global__ __launch_bounds__(kThreads) void colmax_kernel(WinArgs a) {
+    __shared__ floatx4 red[kWaves][16];
+    constexpr int SEG = 8, NV = SEG + 2;
     const int cl = threadIdx.x & 15, sub = threadIdx.x >> 4;
     const int o = blockIdx.x * 16 + cl;
     const int per = (a.npairs + kColGroups - 1) / kColGroups;
-    const int p_end = min((int)(blockIdx.y + 1) * per, a.npairs);
-    float mc = 0.0f, mb = 0.0f;
+    const int p_beg = min((int)blockIdx.y * per, a.npairs);
+    const int p_end = min(p_beg + per, a.npairs);
+    const int nseg = (a.pk_nsb + SEG - 1) / SEG;
+    float mc = 0.0f, mb = 0.0f, mw = __builtin_inff();
     if (o < a.out) {
         const int tile = o / a.pk_ntile, n = o % a.pk_ntile;
-        const floatx2* w = static_cast<const floatx2*>(a.wp);
-        // (units of two columns: blocks of a pair, then its features)
-        const int per_pair = 2 * a.pk_nsb;
-        const int u_end = p_end * per_pair;
-        // (four loads in flight: a thread's reads are what bounds this kernel)
-        for (int u0 = blockIdx.y * per * per_pair + sub; u0 < u_end; u0 += 64) {
-            floatx2 v[4];
+        const floatx2* w = static_cast<const floatx2*>(a.wp) +
+                           (int64_t)tile * a.pk_nblk_pad * 2 * a.pk_ntile + n;
+        for (int it = sub; it < (p_end - p_beg) * 2 * nseg; it += kThreads / 16) {
+            const int sg = it % nseg, pf = it / nseg;  // feature pf & 1 of pair p_beg + pf / 2
+            const int64_t blk0 = (int64_t)(p_beg + pf / 2) * a.pk_nsb;
+            const int b0 = sg * SEG - 2;
+            floatx2 v[NV];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int u = min(u0 + 16 * i, u_end - 1);
-                v[i] = w[((int64_t)tile * a.pk_nblk_pad * 2 + u) * a.pk_ntile + n];
+            for (int i = 0; i < NV; ++i) {
+                const int b = min(max(b0 + i, 0), a.pk_nsb - 1);
+                v[i] = w[((blk0 + b) * 2 + (pf & 1)) * a.pk_ntile];
+            }
+            float m[2 * NV];  // |column 2 b0 + i|
+#pragma unroll
+            for (int i = 0; i < 2 * NV; ++i) {
+                const int c = 2 * b0 + i;
+                const float av = __builtin_fabsf(v[i / 2][i % 2]);
+                const bool fin = av < __builtin_inff();
+                m[i] = c >= 1 && c <= a.nb && fin ? av : 0.0f;
+                mc = __builtin_fmaxf(mc, m[i]);
+                if (c == 0) mb = __builtin_fmaxf(mb, fin ? av : 0.0f);
+                if (c >= 1 && c <= a.nb && !fin) mw = 0.0f;
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int u = min(u0 + 16 * i, u_end - 1);
-                const float v0 = __builtin_fabsf(v[i][0]), v1 = __builtin_fabsf(v[i][1]);
-                const bool first = u % per_pair < 2;
-                const float f0 = v0 < __builtin_inff() ? v0 : 0.0f;
-                const float f1 = v1 < __builtin_inff() ? v1 : 0.0f;
-                mc = __builtin_fmaxf(mc, __builtin_fmaxf(first ? 0.0f : f0, f1));
-                mb = __builtin_fmaxf(mb, first ? f0 : 0.0f);
+            for (int i = 4; i < 2 * NV; ++i) {  // the window that ends with column c
+                const int c = 2 * b0 + i;
+                float x = __builtin_fmaxf(m[i], m[i - 1]);
+                if (a.kdeg >= 2) x = __builtin_fmaxf(x, m[i - 2]);
+                if (a.kdeg >= 3) x = __builtin_fmaxf(x, m[i - 3]);
+                if (c > a.kdeg && c <= a.nb && x > 0.0f) mw = __builtin_fminf(mw, x);
             }
         }
     }
-    red[sub][cl] = floatx2{mc, mb};
+#pragma unroll
+    for (int d = 16; d < 64; d *= 2) {
+        mc = __builtin_fmaxf(mc, __shfl_xor(mc, d));
+        mb = __builtin_fmaxf(mb, __shfl_xor(mb, d));
+        mw = __builtin_fminf(mw, __shfl_xor(mw, d));
+    }
+    if ((sub & 3) == 0) red[sub >> 2][cl] = floatx4{mc, mb, mw, 0.0f};
     __syncthreads();
     if (threadIdx.x < 16 && o < a.out) {
-        for (int i = 1; i < 16; ++i) {
-            mc = __builtin_fmaxf(mc, red[i][cl][0]);
-            mb = __builtin_fmaxf(mb, red[i][cl][1]);
+#pragma unroll
+        for (int i = 1; i < kWaves; ++i) {
+            const floatx4 v = red[i][cl];
+            mc = __builtin_fmaxf(mc, v[0]);
+            mb = __builtin_fmaxf(mb, v[1]);
+            mw = __builtin_fminf(mw, v[2]);
         }
-        reinterpret_cast<floatx2*>(static_cast<char*>(a.ws) + a.off_cm)[(int64_t)blockIdx.y * a.out +
-                                                                       o] = floatx2{mc, mb};
+        reinterpret_cast<floatx4*>(static_cast<char*>(a.ws) + a.off_cm)[(int64_t)blockIdx.y * a.out +
+                                                                       o] =
+            floatx4{mc, mb, mw, 0.0f};
     }
 }
 
 // Scale exponent of an output column from its largest values: coefficients are
 // multiplied by 2^(12 - e).  e follows the coefficients, held within 2^24 of the
-// SiLU weights (scaled along with them).
-static __device__ __forceinline__ int scale_exp(const WinArgs& a, int o) {
-    const floatx2* cm = reinterpret_cast<const floatx2*>(static_cast<const char*>(a.ws) + a.off_cm);
-    float mc = 0.0f, mb = 0.0f;
+// SiLU weights (scaled along with them).  wide: the scale does not serve every
+// window, or it would make the SiLU weights smaller than they are (which
+// could lose one).
+static __device__ __forceinline__ int scale_exp(const WinArgs& a, int o, bool& wide) {
+    const floatx4* cm = reinterpret_cast<const floatx4*>(static_cast<const char*>(a.ws) + a.off_cm);
+    float mc = 0.0f, mb = 0.0f, mw = __builtin_inff();
 #pragma unroll
     for (int g = 0; g < kColGroups; ++g) {
-        const floatx2 v = cm[(int64_t)g * a.out + o];
+        const floatx4 v = cm[(int64_t)g * a.out + o];
         mc = __builtin_fmaxf(mc, v[0]);
         mb = __builtin_fmaxf(mb, v[1]);
+        mw = __builtin_fminf(mw, v[2]);
     }
     const int ec = (int)(__float_as_uint(mc) >> 23) - 127, eb = (int)(__float_as_uint(mb) >> 23) - 127;
-    return max(ec, eb - 24);
+    const int e = max(ec, eb - 24);
+    const int ew = (int)(__float_as_uint(mw) >> 23) - 127;  // (128: no window)
+    wide = mw == 0.0f || ew < e - kWindowBits || e > 12 + kBasisExp;
+    return e;
 }
 
 // One workgroup expands one step (block j of a feature pair) of one column tile
 // into step_u 16-byte units: unit (s, f, w, n) holds term s of columns
 // 16 j + 4 (e % 4) + 2 w + e / 4, e = 0 .. 7, of feature f and output n; in fp32
 // then the scaled SiLU weights [f][n].  Coefficients that are not finite become
-// 0 and set the step's flag.
+// 0 and set the step's flag; in fp32 a column whose scale does not serve it sets the
+// flag of all its steps.
 template <int NS>
 __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
     typedef typename Elem<NS>::T T;
@@ -197,8 +240,10 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
     // (256 is a multiple of bn: a thread's output is the same in every turn)
     const int n = threadIdx.x % bn, o = tile * bn + n;
     int ex = 0;
-    if constexpr (NS == 2) ex = o < a.out ? scale_exp(a, o) : 0;
-    int bad = 0;
+    bool wide = false;
+    if constexpr (NS == 2)
+        if (o < a.out) ex = scale_exp(a, o, wide);
+    int bad = wide;
     for (int u = threadIdx.x; u < 4 * bn; u += 256) {
         const int w = u / bn % 2, f = u / (2 * bn);
         u32x4* dst = dst0 + u;
@@ -257,17 +302,17 @@ __global__ __launch_bounds__(256) void expand_kernel(WinArgs a) {
 
 // ----------------------------------------------------------- non-finite terms
 
-// Adds to the workgroup's tile of outputs (already stored) the terms of the
-// non-finite coefficients (flagged steps), with the values and products the
-// dense contraction has (also 0 times an infinite coefficient, NaN).  P: the
-// split's partial sums, or null.
-template <int NS, int K>
+// bf16: adds to the workgroup's tile of outputs (already stored) the terms of the
+// non-finite weights (flagged steps), with the values and products the dense
+// contraction has (also 0 times an infinite weight, NaN).  P: the split's partial
+// sums, or null.
+template <int K>
 __device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* P, int64_t row_beg,
                                               int col_beg, int bm, int t_beg, int t_end,
                                               const int* flag) {
-    typedef typename Elem<NS>::T T;
-    const T* x = static_cast<const T*>(a.x);
-    T* y = static_cast<T*>(a.y);
+    typedef Elem<1> E;
+    const uint16_t* x = static_cast<const uint16_t*>(a.x);
+    uint16_t* y = static_cast<uint16_t*>(a.y);
     for (int u = threadIdx.x; u < bm * a.bn; u += kThreads) {
         const int64_t row = row_beg + u / a.bn;
         const int o = col_beg + u % a.bn;
@@ -275,14 +320,13 @@ __device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* P, int64_
         float add = 0.0f;
         for (int t = t_beg; t < t_end && add == add; ++t) {
             if (flag[t] == 0) continue;
-            // (fp32: the SiLU column, 0, is on its own instruction with its weights as given)
-            const int p = t / a.nbk, c_beg = max(16 * (t % a.nbk), NS == 2 ? 1 : 0);
-            const int c_end = min(16 * (t % a.nbk) + 15, a.nb);
+            const int p = t / a.nbk, c_beg = 16 * (t % a.nbk);
+            const int c_end = min(c_beg + 15, a.nb);
             for (int f = 0; f < 2 && 2 * p + f < a.in; ++f) {
-                const float xv = Elem<NS>::val(x[row * a.in + 2 * p + f]);
+                const float xv = E::val(x[row * a.in + 2 * p + f]);
                 const float lo = coord_lo(xv, a.xlim, a.inv_lo, a.a_frac);
                 for (int c = c_beg; c <= c_end; ++c) {
-                    const float w = Elem<NS>::val(packed_at<T>(a, o, p, f, c));
+                    const float w = E::val(packed_at<uint16_t>(a, o, p, f, c));
                     if (__builtin_fabsf(w) < __builtin_inff()) continue;
                     const float v =
                         __builtin_fmaf(xv, a.inv_h, a.a_int + 1.0f - (float)c) + lo;
@@ -293,7 +337,82 @@ __device__ __forceinline__ void fix_nonfinite(const WinArgs& a, float* P, int64_
         if (add == 0.0f) continue;
         const int64_t at = row * a.out + o;
         if (P != nullptr) P[at] += 2.0f * add;
-        else Elem<NS>::st(y + at, Elem<NS>::val(y[at]) + 2.0f * add);
+        else E::st(y + at, E::val(y[at]) + 2.0f * add);
+    }
+}
+
+// -------------------------------------------- fp32 instruction, every column
+
+// The sums of a wave's two row tiles (rows row[0], row[1] of lane r) and NF column
+// fragments (outputs col[nf] of lane r) over the pairs [p_beg, p_end), every column
+// of their features on the fp32 instruction: acc = y / 2.  The weights come from the
+// packed buffer a block ahead, a fragment's 32 outputs in one contiguous run per
+// lane half.  Whole calls where every workgroup takes this path, against the kernel that
+// reads the packed weights through LDS: 8192 x 128 -> 128, G = 100: 349 us (316), 16384 x
+// 256 -> 64: 140 (124), 4096 x 256 -> 256, G = 20, degree 1: 184 (214), 65536 x 784 -> 256:
+// 4.9 ms (3.2: one fragment at a time generates the basis values four times).
+template <int K, int NF>
+__device__ __forceinline__ void dense_tile(const WinArgs& a, const int64_t (&row)[2],
+                                           const int (&col)[NF], int h, int p_beg, int p_end,
+                                           floatx16 (&acc)[2][NF]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int nf = 0; nf < NF; ++nf)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][nf][q] = 0.0f;
+    const float* x = static_cast<const float*>(a.x);
+    const floatx2* w[NF];
+    floatx2 wn[NF];
+#pragma unroll
+    for (int nf = 0; nf < NF; ++nf) {
+        w[nf] = static_cast<const floatx2*>(a.wp) +
+                (((int64_t)(col[nf] / a.pk_ntile) * a.pk_nblk_pad + (int64_t)p_beg * a.pk_nsb) * 2 +
+                 h) * a.pk_ntile + col[nf] % a.pk_ntile;
+        wn[nf] = *w[nf];
+    }
+    const int step = 2 * a.pk_ntile;
+    int left = (p_end - p_beg) * a.pk_nsb - 1;  // blocks after the one in wn
+    float xn[2];
+    auto load_x = [&](int p) {
+        const int f = 2 * p + h;  // (an odd feature count's phantom: x = 0, zero weights)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) xn[i] = f < a.in ? x[row[i] * a.in + f] : 0.0f;
+    };
+    load_x(p_beg);
+#pragma unroll 1
+    for (int p = p_beg; p < p_end; ++p) {
+        const float xv[2] = {xn[0], xn[1]};
+        load_x(min(p + 1, p_end - 1));
+        float lo[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) lo[i] = coord_lo(xv[i], a.xlim, a.inv_lo, a.a_frac);
+#pragma unroll 1
+        for (int b = 0; b < a.pk_nsb; ++b) {
+            floatx2 wv[NF];
+            const int adv = left > 0 ? step : 0;
+            --left;
+#pragma unroll
+            for (int nf = 0; nf < NF; ++nf) {
+                wv[nf] = wn[nf];
+                w[nf] += adv;
+                wn[nf] = *w[nf];
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float c = (float)(2 * b + j);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float v = half_basis_k<K>(__builtin_fmaf(xv[i], a.inv_h, a.a_int + 1.0f - c) +
+                                              lo[i]);
+                    if (j == 0 && b == 0) v = half_silu(xv[i]);
+#pragma unroll
+                    for (int nf = 0; nf < NF; ++nf)
+                        acc[i][nf] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, wv[nf][j], acc[i][nf],
+                                                                          0, 0, 0);
+                }
+            }
+        }
     }
 }
 
@@ -551,6 +670,11 @@ void window_kernel(WinArgs a) {
         __builtin_amdgcn_sched_barrier(0);
     };
 
+    const int t_end = min((st_beg + nst) * SPB, a.steps);
+    const int* flag = reinterpret_cast<const int*>(static_cast<const char*>(a.ws) + a.off_flag) +
+                      tile * a.steps;
+    int bad = 0;
+
     // ---- prologue: x and weights of stages 0 .. D - 1, the A of stage 0
     uint32_t xq[D][SPB];
     {
@@ -564,16 +688,20 @@ void window_kernel(WinArgs a) {
             constexpr int kk = decltype(k)::value;
             make_part(std::integral_constant<int, kk % 4>{}, gn, x0[kk / 4], kk / 4, 0, own);
         });
+        for (int t = t_beg + tid; t < t_end; t += kThreads) bad |= flag[t];
         wait_stage(std::integral_constant<int, 0>{});
         fence();
     }
+    // (fp32: the flagged steps' workgroup takes its sums by dense_tile alone)
+    bad = __syncthreads_or(bad);
+    const int nst_run = NS == 2 && bad ? 0 : nst;
     u32x4 par;
     int par_pos = 0;
     float par_silu = 0.0f;
     int cj = 0;                   // MB, fp32: block of the step
     int buf = 0, fill = D % NBS;  // LDS buffer of the stage, and of the one D ahead
 #pragma unroll 1
-    for (int st = 0; st < nst; ++st) {
+    for (int st = 0; st < nst_run; ++st) {
         const int e = st & 1;
         uint32_t xn[SPB], xl[SPB];
 #pragma unroll
@@ -657,40 +785,76 @@ void window_kernel(WinArgs a) {
                               (int64_t)blockIdx.z * a.batch * a.out
                         : nullptr;
     T* y = static_cast<T*>(a.y);
+    // one 32 x 32 tile's sums times 2^us
+    auto store = [&](int i, int col, const floatx16& c, int us, int half)
+                     __attribute__((always_inline)) {
+        const int64_t row0 = row_beg + wr * 64 + (i ^ wc) * 32 + 4 * half;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int64_t row = row0 + 8 * (q / 4) + q % 4;
+            if (row < a.batch && col < a.out) {
+                const float v = NS == 2 ? __builtin_ldexpf(c[q], us) : 2.0f * c[q];
+                if (P != nullptr) P[row * a.out + col] = v;
+                else Elem<NS>::st(y + row * a.out + col, v);
+            }
+        }
+    };
+    if constexpr (NS == 2) {
+        float fin = 0.0f;  // (NaN once a sum is not finite)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int nf = 0; nf < NFW; ++nf)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    if constexpr (ACC2) acc[i][nf][q] += acc2[i][nf][q];
+                    fin = __builtin_fmaf(acc[i][nf][q], 0.0f, fin);
+                }
+        if (__builtin_amdgcn_readfirstlane(__syncthreads_or(bad | !(fin == 0.0f)))) {
+            // fragments at a time (two at 256 columns would make the main loop spill)
+            constexpr int NF = NFW == 2 ? 2 : 1;
+#pragma unroll 1
+            for (int n0 = 0; n0 < NFW; n0 += NF) {
+                // (opaque, so that the stores' addresses are not computed ahead for all
+                // turns or for both paths, which would spill)
+                int rr = r, hh = h;
+                asm volatile("" : "+v"(rr), "+v"(hh));
+                int64_t row[2];
+                int col[NF], colc[NF];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    row[i] = min(row_beg + wr * 64 + (i ^ wc) * 32 + rr, a.batch - 1);
+#pragma unroll
+                for (int n = 0; n < NF; ++n) {
+                    col[n] = col_beg + (wc * NFW + n0 + n) * 32 + rr;
+                    colc[n] = min(col[n], a.out - 1);
+                }
+                floatx16 d[2][NF];
+                dense_tile<K, NF>(a, row, colc, hh, p_beg, t_end / a.nbk, d);
+#pragma unroll
+                for (int n = 0; n < NF; ++n) {
+                    store(0, col[n], d[0][n], 1, hh);
+                    store(1, col[n], d[1][n], 1, hh);
+                }
+            }
+            return;
+        }
+    }
 #pragma unroll
     for (int nf = 0; nf < NFW; ++nf) {
         const int col = col_beg + (wc * NFW + nf) * 32 + r;
-        if constexpr (ACC2) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc[i][nf][q] += acc2[i][nf][q];
-        }
         int us = 1;
         if constexpr (NS == 2)
             us = 1 + reinterpret_cast<const int*>(static_cast<const char*>(a.ws) + a.off_us)[col];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int64_t row0 = row_beg + wr * 64 + (i ^ wc) * 32 + 4 * h;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int64_t row = row0 + 8 * (q / 4) + q % 4;
-                if (row < a.batch && col < a.out) {
-                    const float v = NS == 2 ? __builtin_ldexpf(acc[i][nf][q], us)
-                                            : 2.0f * acc[i][nf][q];
-                    if (P != nullptr) P[row * a.out + col] = v;
-                    else Elem<NS>::st(y + row * a.out + col, v);
-                }
-            }
+        store(0, col, acc[0][nf], us, h);
+        store(1, col, acc[1][nf], us, h);
+    }
+    if constexpr (NS == 1) {
+        if (bad) {
+            __syncthreads();  // (the outputs are stored)
+            fix_nonfinite<K>(a, P, row_beg, col_beg, BM, t_beg, t_end, flag);
         }
     }
-    const int* flag = reinterpret_cast<const int*>(static_cast<const char*>(a.ws) + a.off_flag) +
-                      tile * a.steps;
-    const int t_end = min((st_beg + nst) * SPB, a.steps);
-    int bad = 0;
-    for (int t = t_beg + tid; t < t_end; t += kThreads) bad |= flag[t];
-    if (__syncthreads_or(bad))
-        fix_nonfinite<NS, K>(a, P, row_beg, col_beg, BM, t_beg, t_end, flag);
 }
 
 template <int NS, int NFW, bool MB>
@@ -707,7 +871,7 @@ hipError_t launch_k(const WinArgs& a, dim3 grid, hipStream_t s) {
 template <int NS>
 hipError_t launch_ns(const WinGeom& g, const WinArgs& a, hipStream_t s) {
     if constexpr (NS == 2)
-        hipLaunchKernelGGL(colmax_kernel, dim3((unsigned)((a.out + 15) / 16), kColGroups), dim3(256),
+        hipLaunchKernelGGL(colmax_kernel, dim3((unsigned)((a.out + 15) / 16), kColGroups), dim3(kThreads),
                            0, s, a);
     hipLaunchKernelGGL(expand_kernel<NS>, dim3((unsigned)a.steps, (unsigned)g.ntiles), dim3(256), 0,
                        s, a);

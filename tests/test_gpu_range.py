@@ -1,0 +1,100 @@
+"""GPU accuracy of the fp32 kernels whose operands are sums of 16-bit terms, where
+one value of a row, a column or a tile is far larger than the others: every row,
+feature and basis whose result does not hold the large value keeps the fp32
+accuracy it has without it (compared part by part: a norm over the tensor would
+hide it).  Against the float64 oracle at the fp32 tolerance 1e-5, relative to the
+largest value of the part compared."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import F32_LAYER_TOL, say
+from test_gpu_window import _inputs, _planned
+from test_gpu_window import _run as _run_forward
+
+pytestmark = pytest.mark.gpu
+
+F32_MAX = float(np.finfo(np.float32).max)
+
+
+def _rows_close(y, ref):
+    """Every row against its own largest value."""
+    scale = np.abs(ref).max(axis=1, keepdims=True)
+    err = np.abs(y - ref) / np.where(scale > 0, scale, 1.0)
+    assert err.max() <= F32_LAYER_TOL, (float(err.max()), int(err.max(axis=1).argmax()))
+
+
+WINDOW = [(4096, 161, 64, 10, 3), (4096, 140, 140, 30, 3), (8192, 96, 100, 12, 1)]
+
+
+@pytest.mark.parametrize("big", [1e4, 1e6, 1e10, F32_MAX])
+@pytest.mark.parametrize("B,n_in,n_out,G,k", WINDOW)
+def test_forward_one_large_coefficient(B, n_in, n_out, G, k, big):
+    """One large coefficient in every output column: the rows whose input is outside
+    its support.  (Those inside it are right to the large term's own rounding.)"""
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, "f32")
+    C[np.arange(n_out), 3, 2] = np.float32(big)
+    assert _planned(B, n_in, n_out, G, k, "f32")
+    say(f"range forward coefficient {big:g} {n_in}->{n_out} G={G} k={k}")
+    y = _run_forward(x, C, Wb, G, k, "f32")
+    rows = np.r_[0:96, B - 32:B]
+    ref = oracle.layer(x[rows], C, Wb, G, k=k)
+    u = (x[rows, 3].astype(np.float64) + 1) * (G / 2) + k - 2
+    out = (u <= -1e-3) | (u >= k + 1 + 1e-3)
+    assert out.sum() > 20 and (~out).sum() > 5
+    _rows_close(y[rows][out], ref[out])
+    _rows_close(y[rows][~out], ref[~out])
+
+
+@pytest.mark.parametrize("big", [1e6, 1e10, 1e30])
+@pytest.mark.parametrize("B,n_in,n_out,G,k", WINDOW[:2])
+def test_forward_one_large_silu_weight(B, n_in, n_out, G, k, big):
+    """One large SiLU weight in every column, met by a SiLU value of 0 in half the rows."""
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, "f32")
+    Wb[:, 5] = np.float32(big)
+    x[::2, 5] = 0.0
+    say(f"range forward silu weight {big:g} {n_in}->{n_out} G={G}")
+    y = _run_forward(x, C, Wb, G, k, "f32")
+    rows = np.r_[0:64]
+    _rows_close(y[rows], oracle.layer(x[rows], C, Wb, G, k=k))
+
+
+@pytest.mark.parametrize("small", [1e-3, 1e-6, 1e-9, 1e-20])
+@pytest.mark.parametrize("B,n_in,n_out,G,k", WINDOW)
+def test_forward_small_coefficients_beside_normal_ones(B, n_in, n_out, G, k, small):
+    """All features but one with small weights, and rows that meet only those (the
+    one feature off the grid, without a SiLU weight); then only some bases small."""
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, "f32")
+    C[:, 1:] *= np.float32(small)
+    Wb[:, 1:] *= np.float32(small)
+    Wb[:, 0] = 0.0
+    x[::2, 0] = 3.0
+    say(f"range forward small {small:g} {n_in}->{n_out} G={G} k={k}")
+    rows = np.r_[0:64]
+    y = _run_forward(x, C, Wb, G, k, "f32")
+    _rows_close(y[rows], oracle.layer(x[rows], C, Wb, G, k=k))
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, "f32")
+    C[:, :, G // 2:] *= np.float32(small)
+    Wb *= np.float32(small)
+    x[::2] = np.float32(0.5) + np.abs(x[::2]) / 2  # past the large bases
+    x[::2] = np.clip(x[::2], 0.5 + 2.0 * (k + 1) / G if G > 20 else 0.9, 1.0)
+    y = _run_forward(x, C, Wb, G, k, "f32")
+    _rows_close(y[rows], oracle.layer(x[rows], C, Wb, G, k=k))
+
+
+@pytest.mark.parametrize("B,n_in,n_out,G,k", WINDOW)
+@pytest.mark.parametrize("cs,ws,xs", [(0.0, 1.0, 1e30), (0.25, 1e-3, 1e36), (1.0, 1e-3, 1e38),
+                                      (1e12, 1e-20, 1e3), (1e-20, 1.0, 1e20), (1e30, 1.0, 30.0)])
+def test_forward_large_inputs(B, n_in, n_out, G, k, cs, ws, xs):
+    """Inputs far past the grid, where only the SiLU term counts: finite while the
+    layer's sum is, whatever the coefficients' scale."""
+    x, C, Wb = _inputs(B, n_in, n_out, G, k, "f32")
+    C = (C * cs / 0.1).astype(np.float32)
+    Wb = (Wb * ws).astype(np.float32)
+    x[::7] = np.where(np.arange(n_in) % 5 == 0, xs, np.where(np.arange(n_in) % 2, 0.0, -60.0))
+    say(f"range forward inputs {xs:g} coefficients {cs:g} {ws:g} {n_in}->{n_out} G={G}")
+    y = _run_forward(x, C, Wb, G, k, "f32")
+    rows = np.r_[0:70]
+    ref = oracle.layer(x[rows], C, Wb, G, k=k)
+    assert np.abs(ref).max() < 1e38 and np.isfinite(y).all()
+    _rows_close(y[rows], ref)
