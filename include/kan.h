@@ -347,7 +347,10 @@ kan_status kan_layer_plan(const kan_grid* grid, kan_dtype dtype, int64_t batch,
  * basis values are regenerated in registers, never stored.  In fp32 the
  * operands are two fp16 terms each (22 bits, scaled by powers of two), except
  * the weight gradients of batches below 8192 rows and of grids whose padded
- * columns do not divide 256, which use the fp32 matrix instruction.  For layers of at
+ * columns do not divide 256, which use the fp32 matrix instruction, and dx of
+ * features (in pairs up to G = 12) whose terms would not hold 22 bits of the largest of
+ * any four consecutive coefficients, or that have four consecutive coefficients
+ * of 0 for some outputs only: these run on the fp32 instruction too.  For layers of at
  * most 16 outputs from 16384 rows on (when a feature's G + 7 columns, rounded
  * down to even, times its outputs rounded up to a multiple of 4 stay within
  * 256) dx runs instead on the vector ALUs over the SiLU column and the four

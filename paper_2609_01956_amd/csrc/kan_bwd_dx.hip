@@ -22,8 +22,10 @@
 // 512.  dy is scaled per batch row and the weights per K tile and chunk of
 // outputs by the power of two that brings the largest to 2^12.  784 -> 256 at 16384
 // rows: 805 -> 267 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
-// window at its own coordinate; fewer roundings).  Rows with a
-// non-finite dy and tiles with a non-finite weight are computed apart at the end.
+// window at its own coordinate; fewer roundings).  The terms hold 22 bits of the
+// largest weight of every window; a K tile with weights that they cannot hold so
+// (kan_bwd_pack.h) is held in fp32 and taken after the others on the fp32
+// instruction, and rows with a non-finite dy are then computed apart.
 #include "kan_bwd_pack.h"
 
 #include <algorithm>
@@ -84,6 +86,114 @@ __device__ __forceinline__ float slope_at(float v) {
     const float w = 2.0f - a;
     const float b = __builtin_amdgcn_fmed3f(1.0f - a, 0.0f, 1.0f);
     return __builtin_copysignf(__builtin_fmaf(2.0f * b, b, -0.5f * w * w), -v);
+}
+
+// fp32: dx of the features with a tile held in fp32, on the fp32 instruction (their
+// other tiles' weights from the two terms), for the wave's row tile rf.  dy comes from
+// memory again, in fp32, and the weights straight from the workspace, both a group of
+// outputs ahead.  A function of its own, so that the main loop keeps its registers;
+// args: the kernel's, in place.  16384 x 784 -> 256 with every tile so: 1.6 ms, 0.3 ms
+// with none (0.8 ms where the fp32 instruction was the kernel's own).
+template <int RF, bool C16>
+__device__ __attribute__((noinline)) void wide_tiles(const uint32_t* args, int rf) {
+    constexpr int NT = 2;
+    struct Words { uint32_t w[sizeof(Dx2Args) / 4]; } words;
+    static_assert(sizeof(Words) == sizeof(Dx2Args), "whole words");
+#pragma unroll
+    for (size_t i = 0; i < sizeof(Dx2Args) / 4; ++i)
+        words.w[i] = __builtin_amdgcn_readfirstlane(args[i]);
+    const Dx2Args a = __builtin_bit_cast(Dx2Args, words);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int64_t wrow = (int64_t)blockIdx.x * (kNW * 32 * RF) + wave * (32 * RF) +
+                         32 * __builtin_amdgcn_readfirstlane(rf);
+    if (wrow >= a.batch) return;
+    const int64_t row = wrow + r, rowc = min(row, a.batch - 1);
+    const int ch = blockIdx.y, g0 = ch * a.gmax, S = min(a.gmax, a.groups - g0);
+    const int t_begin = blockIdx.z * a.tiles_per_split;
+    const int t_end = min(t_begin + a.tiles_per_split, a.ntiles);
+    const int tpf = C16 ? 1 : a.cp / 32;
+    const uint64_t bytes = (uint64_t)(a.batch - wrow) * a.out * 4;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(static_cast<const float*>(a.dy) + wrow * a.out), (short)0,
+        (int)(bytes < 0xffffffffull ? bytes : 0xffffffffull), kBufferWord3);
+    // dy of the lane half's eight outputs of group s (loads past the tensor give 0)
+    auto load_dy = [&](int s, u32x4 (&d)[2]) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            d[m] = __builtin_bit_cast(
+                u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                           rs, ((uint32_t)r * (uint32_t)a.out +
+                                (uint32_t)((g0 + s) * 16 + 8 * h + 4 * m)) * 4u, 0, 0));
+    };
+#pragma unroll 1
+    for (int t0 = t_begin; t0 < t_end; t0 += tpf) {
+        int flags = 0;
+        for (int t = t0; t < t0 + tpf; ++t) flags |= a.wexp[t * a.nchunk + ch];
+        if (__builtin_amdgcn_readfirstlane(flags >> 16) == 0) continue;
+        const int f = C16 ? 2 * t0 + h : t0 / tpf;
+        const float x = f < a.in ? static_cast<const float*>(a.xt)[(int64_t)f * a.bpad + rowc] : 0.0f;
+        const float lo = coord_lo(x, a.xlim, a.inv_lo, a.a_frac);
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int t = t0; t < t0 + tpf; ++t) {
+            const int we = __builtin_amdgcn_readfirstlane(a.wexp[t * a.nchunk + ch]);
+            const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(
+                a.wtp + ((int64_t)t * a.groups + g0) * (NT * 64), (short)0, S * NT * 1024,
+                kBufferWord3);
+            auto load_wt = [&](int s, int term) {
+                return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     ws, lane * 16, (s * NT + term) * 1024, 0));
+            };
+            u32x4 n0 = load_wt(0, 0), n1 = load_wt(0, 1), dn[2];
+            load_dy(0, dn);
+            floatx16 acc;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
+#pragma unroll 1
+            for (int s = 0; s < S; ++s) {
+                const u32x4 q0 = n0, q1 = n1;
+                u32x4 d[2] = {dn[0], dn[1]};
+                const int sn = min(s + 1, S - 1);
+                n0 = load_wt(sn, 0);
+                n1 = load_wt(sn, 1);
+                load_dy(sn, dn);
+                float w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = __uint_as_float(e < 4 ? q0[e % 4] : q1[e % 4]);
+                if (we >> 16 == 0) {
+                    const f16x8_t h0 = __builtin_bit_cast(f16x8_t, q0);
+                    const f16x8_t h1 = __builtin_bit_cast(f16x8_t, q1);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        w[e] = __builtin_ldexpf((float)h0[e] + (float)h1[e], we - 512 - 12);
+                }
+                if ((g0 + s) * 16 + 16 > a.out) {  // (past the row: the next row's)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if ((g0 + s) * 16 + 8 * h + e >= a.out) d[e / 4][e % 4] = 0u;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                        w[e], __uint_as_float(d[e / 4][e % 4]), acc, 0, 0, 0);
+            }
+            const int c0 = C16 ? 0 : 32 * (t - t0) + 16 * h;
+            float sb = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {  // (a sum counts in its window alone)
+                const float v = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - (float)(c0 + q)) + lo;
+                if (c0 + q > 0 && v >= -2.0f && v < 2.0f)
+                    sb = __builtin_fmaf(acc[q], slope_at(v), sb);
+            }
+            sum += __builtin_fmaf(c0 == 0 ? acc[0] : 0.0f, silu_slope(x), a.inv_h * sb);
+        }
+        if (!C16) sum += __shfl_xor(sum, 32);  // (both lane halves' columns)
+        if (row < a.batch && f < a.in && (C16 || h == 0)) {
+            if (a.dxp != nullptr) a.dxp[((int64_t)ch * a.batch + row) * a.in + f] = sum;
+            else static_cast<float*>(a.dx)[row * a.in + f] = sum;
+        }
+    }
 }
 
 // SM bounds the 16-output groups of a chunk; RF row tiles per wave; TPB K tiles per
@@ -469,13 +579,16 @@ void dx2_kernel(Dx2Args a) {
     if (nst > 0) store_stage(nst - 1);
 
     if constexpr (!BF) {
-        // Rows with a non-finite dy and features of tiles with a non-finite weight: the
-        // same sums in plain fp32, with the zeros and infinities the matrix
-        // instruction would meet.
         int any = 0;
         for (int i = tid; i < BM; i += kThreads) any |= rowbad[i];
         for (int t = t_begin + tid; t < t_end; t += kThreads) any |= a.wexp[t * a.nchunk + ch] >> 16;
         if (__syncthreads_or(any)) {
+#pragma unroll 1
+            for (int rf = 0; rf < RF; ++rf)
+                wide_tiles<RF, C16>((const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr(), rf);
+            // Rows with a non-finite dy: the same sums in plain fp32, with the zeros and
+            // infinities the matrix instruction would meet.
+            __syncthreads();
             const int f_beg = cp16 ? 2 * t_begin : t_begin / tpf;
             const int f_end = min(a.in, cp16 ? 2 * t_end : t_end / tpf);
             const int nf = f_end - f_beg;
@@ -484,11 +597,7 @@ void dx2_kernel(Dx2Args a) {
             for (int64_t u = tid; u < (int64_t)BM * nf; u += kThreads) {
                 const int rl = (int)(u / nf), f = f_beg + (int)(u % nf);
                 const int64_t row = wg_row0 + rl;
-                if (row >= a.batch) continue;
-                bool bad = rowbad[rl] != 0;
-                for (int t = cp16 ? f / 2 : f * tpf; t < (cp16 ? f / 2 + 1 : (f + 1) * tpf); ++t)
-                    bad |= (a.wexp[t * a.nchunk + ch] >> 16) != 0;
-                if (!bad) continue;
+                if (row >= a.batch || rowbad[rl] == 0) continue;
                 const float x = xt[(int64_t)f * a.bpad + row];
                 const float sc = __builtin_amdgcn_fmed3f(
                     __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f) +

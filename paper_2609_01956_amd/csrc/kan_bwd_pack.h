@@ -17,16 +17,30 @@ __device__ __forceinline__ T weight(const Dx2Args& a, int o, int f, int c) {
                   : static_cast<const T*>(a.coef)[row * a.nb + c - 1];
 }
 
+// fp32: a window (four consecutive coefficients of a feature for an output: what one
+// input's derivative meets) whose largest is 2^kPackWindowBits below the tile's
+// scale loses more than the last two bits of its fp32 values.
+constexpr int kPackWindowBits = 15;
+
+// The next lane's value (the wave's last lane: its own).
+__device__ __forceinline__ float next_lane(float v) {
+    const int u = (int)__float_as_uint(v);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(u, u, 0x130, 0xf, 0xf, false));
+}
+
 // One workgroup packs K tile t for output chunk ch (groups g0 .. g0 + S - 1 of 16
 // outputs): [t][g][term][lane (r, h)][e], outputs 16 g + 8 h + e of the K row of A
-// row r.  fp32: scaled per (tile, chunk), wexp[t nchunk + ch] = the exponent
-// (biased by 512; bit 16: a weight was not finite, and taken as 0).
+// row r.  fp32: two fp16 terms of the weights, scaled per (tile, chunk), and
+// wexp[t nchunk + ch] = the exponent, biased by 512.  Bit 16 of it: the tile holds
+// its weights in fp32 instead (outputs 16 g + 8 h + 4 term + 0 .. 3 in a unit), as
+// the terms cannot hold them: a weight is not finite, or some window or SiLU column is
+// too far below the scale, or a window is zero for some outputs only (their
+// gradients are then all that a dx has, however small beside the others').
 template <typename T>
 __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
     constexpr bool BF = sizeof(T) == 2;
     constexpr int NT = BF ? 1 : 2;
     __shared__ __align__(16) uint16_t buf[NT][32][32][8];
-    __shared__ float redm[256];
     const int tid = threadIdx.x;
     const int g0 = ch * a.gmax, S = min(a.gmax, a.groups - g0);
     const int kl = tid & 31, e = tid >> 5;  // local K row, output within eight
@@ -57,42 +71,115 @@ __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
             if (!ok || 16 * g0 + 8 * i + e >= a.out || i >= 2 * S) v[i] = T(0);
     }
     int ex = 0;
+    bool wide = false;
     if constexpr (!BF) {
-        float m = 0.0f;
+        __shared__ floatx2 redm[4];
+        __shared__ int zeros[38], others[38], silu[32];  // (windows: per first K row; see edges)
+        if (tid < 38) zeros[tid] = others[tid] = 0;
+        if (tid < 32) silu[tid] = 0;
+        __syncthreads();
+        float m = 0.0f, mw = __builtin_inff();
         bool bad = false;
+        // the windows that begin at the thread's column: the largest and the least of
+        // their maxima's bits less 1 (an empty window is the largest then)
+        uint32_t hi = 0u, lo = 0xffffffffu;
+        const int outs = min((a.out - 16 * g0 - e + 7) / 8, 2 * S);  // the thread's
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
             const float av = __builtin_fabsf(v[i]);
-            const bool fin = av < __builtin_inff();
-            bad |= !fin;
-            v[i] = fin ? v[i] : 0.0f;
-            m = __builtin_fmaxf(m, fin ? av : 0.0f);
+            bad |= !(av < __builtin_inff());
+            m = __builtin_fmaxf(m, av);
+            // (past the thread's last output: its first again)
+            const float w1 = i < outs ? av : __builtin_fabsf(v[0]);
+            const float w2 = __builtin_fmaxf(w1, next_lane(w1));
+            const float w3 = __builtin_fmaxf(w1, next_lane(w2));
+            const uint32_t w4 = __float_as_uint(__builtin_fmaxf(w1, next_lane(w3))) - 1u;
+            hi = max(hi, w4);
+            lo = min(lo, w4);
         }
-        redm[tid] = m;
-        const int anybad = __syncthreads_or(bad);
-        for (int k = 128; k >= 1; k >>= 1) {
-            if (tid < k) redm[tid] = __builtin_fmaxf(redm[tid], redm[tid + k]);
-            __syncthreads();
+        if (f < a.in && c >= 1 && c + 3 <= a.nb && kl + 3 < 32 && outs > 0) {
+            if (hi == 0xffffffffu) zeros[kl] = 1;
+            if (lo != 0xffffffffu) {
+                others[kl] = 1;
+                mw = __uint_as_float(lo + 1u);
+            }
         }
-        ex = (int)(__float_as_uint(redm[0]) >> 23) - 127;
-        if (tid == 0) a.wexp[t * a.nchunk + ch] = (ex + 512) | (anybad ? 1 << 16 : 0);
-    }
+        if (c == 0 && f < a.in) atomicMax(&silu[kl], (int)__float_as_uint(m));
+        // features of several tiles: the windows over the tile's first and last edge,
+        // an output per thread
+        const int f0 = 32 * t / a.cp, cs = 32 * t % a.cp, o = 16 * g0 + tid;
+        if (a.cp > 16 && tid < 16 * S && o < a.out) {
+            const T* w = static_cast<const T*>(a.coef) + ((int64_t)o * a.in + f0) * a.nb - 1;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        if constexpr (BF) {
-            buf[0][i][r][e] = v[i];
-        } else {
-            const float x = __builtin_ldexpf(v[i], 12 - ex);
-            const _Float16 h0 = (_Float16)x;
-            buf[0][i][r][e] = __builtin_bit_cast(uint16_t, h0);
-            buf[NT - 1][i][r][e] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)h0));
+            for (int edge = 0; edge < 2; ++edge) {
+                const int at = cs + 32 * edge;  // windows that begin 3 .. 1 columns before it
+                float n[6];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const int cc = at - 3 + k;
+                    n[k] = cc >= 1 && cc <= a.nb ? __builtin_fabsf(w[cc]) : 0.0f;
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    if (at - 3 + k < 1 || at + k > a.nb) continue;
+                    const float m4 = __builtin_fmaxf(__builtin_fmaxf(n[k], n[k + 1]),
+                                                     __builtin_fmaxf(n[k + 2], n[k + 3]));
+                    (m4 > 0.0f ? others : zeros)[32 + 3 * edge + k] = 1;
+                    mw = m4 > 0.0f ? __builtin_fminf(mw, m4) : mw;
+                }
+            }
+        }
+        if (bad) m = __builtin_inff();
+#pragma unroll
+        for (int k = 1; k < 64; k *= 2) {
+            m = __builtin_fmaxf(m, __shfl_xor(m, k));
+            mw = __builtin_fminf(mw, __shfl_xor(mw, k));
+        }
+        if (tid % 64 == 0) redm[tid / 64] = floatx2{m, mw};
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            m = __builtin_fmaxf(m, redm[k][0]);
+            mw = __builtin_fminf(mw, redm[k][1]);
+        }
+        auto exponent = [](float q) -> int { return (int)(__float_as_uint(q) >> 23) - 127; };
+        ex = exponent(m);
+        bool w = !(m < __builtin_inff()) ||
+                 exponent(mw) < ex - kPackWindowBits;  // (infinity: no window)
+        if (tid < 38) w |= (zeros[tid] & others[tid]) != 0;
+        if (tid < 32)
+            w |= silu[tid] != 0 && exponent(__uint_as_float((uint32_t)silu[tid])) < ex - kPackWindowBits;
+        wide = __syncthreads_or(w);
+        if (tid == 0) a.wexp[t * a.nchunk + ch] = wide ? 1 << 16 : ex + 512;
+    }
+    if (!BF && wide) {
+        float* raw = reinterpret_cast<float*>(&buf[0][0][0][0]);  // [output octet][A row][e]
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            if constexpr (!BF) raw[(i * 32 + r) * 8 + e] = v[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            if constexpr (BF) {
+                buf[0][i][r][e] = v[i];
+            } else {
+                const float x = __builtin_ldexpf(v[i], 12 - ex);
+                const _Float16 h0 = (_Float16)x;
+                buf[0][i][r][e] = __builtin_bit_cast(uint16_t, h0);
+                buf[NT - 1][i][r][e] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)h0));
+            }
         }
     }
     __syncthreads();
     u32x4* dst = a.wtp + ((int64_t)t * a.groups + g0) * (NT * 64);
     for (int u = tid; u < S * NT * 64; u += 256) {
         const int lane = u % 64, term = u / 64 % NT, g = u / (64 * NT);
-        dst[u] = *reinterpret_cast<const u32x4*>(&buf[term][2 * g + lane / 32][lane % 32][0]);
+        const int at = 2 * g + lane / 32;
+        if (!BF && wide)
+            dst[u] = reinterpret_cast<const u32x4*>(&buf[0][0][0][0])[(at * 32 + lane % 32) * 2 + term];
+        else
+            dst[u] = *reinterpret_cast<const u32x4*>(&buf[term][at][lane % 32][0]);
     }
 }
 

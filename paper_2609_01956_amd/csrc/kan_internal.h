@@ -324,7 +324,7 @@ struct Dx2Args {
     const void* coef;
     const void* bw;
     u32x4* wtp;        // packed weights [ntiles][groups][terms][64 lanes]
-    int* wexp;         // fp32: scale exponents [ntiles][nchunk]
+    int* wexp;         // fp32: scale exponents and flags [ntiles][nchunk] (kan_bwd_pack.h)
     void* dx;
     float* dxp;        // per-chunk partials when the outputs take several chunks (else null)
     int64_t batch, bpad;

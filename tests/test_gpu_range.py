@@ -8,7 +8,9 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_common import F32_LAYER_TOL, say
+from gpu_common import F32_LAYER_TOL, normwise, say
+from test_gpu_backward import _case
+from test_gpu_backward import _run as _run_backward
 from test_gpu_window import _inputs, _planned
 from test_gpu_window import _run as _run_forward
 
@@ -98,3 +100,64 @@ def test_forward_large_inputs(B, n_in, n_out, G, k, cs, ws, xs):
     ref = oracle.layer(x[rows], C, Wb, G, k=k)
     assert np.abs(ref).max() < 1e38 and np.isfinite(y).all()
     _rows_close(y[rows], ref)
+
+
+BACK = [(300, 9, 40, 10), (257, 6, 10, 10), (260, 5, 300, 10), (200, 5, 130, 30), (150, 3, 20, 60)]
+
+
+@pytest.mark.parametrize("big", [1e6, 1e10, 1e30])
+@pytest.mark.parametrize("B,n_in,n_out,G", BACK)
+def test_dx_one_large_weight(B, n_in, n_out, G, big):
+    """One large coefficient, or SiLU weight: dx of the other features, and of its own
+    where its derivative is 0 there."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=11, dtype_name="f32")
+    say(f"range dx weight {big:g} {n_in}->{n_out} G={G}")
+    C1 = C.copy()
+    C1[n_out // 2, 1, 2] = np.float32(big)
+    got = _run_backward(x, C1, Wb, dy, G, "f32", need_dw=False)[0]
+    ref = oracle.layer_backward(x, C1, Wb, dy, G)[0]
+    u = (x[:, 1].astype(np.float64) + 1) * (G / 2) + 3 - 2
+    out = (u <= -1e-3) | (u >= 4 + 1e-3)
+    assert out.sum() > 20 and (~out).sum() > 3
+    for f in range(n_in):
+        if f != 1:
+            assert normwise(got[:, f], ref[:, f]) <= F32_LAYER_TOL, f
+    assert normwise(got[out, 1], ref[out, 1]) <= F32_LAYER_TOL
+    assert normwise(got[~out, 1], ref[~out, 1]) <= F32_LAYER_TOL
+    W1 = Wb.copy()
+    W1[n_out // 3, 2] = np.float32(big)
+    got = _run_backward(x, C, W1, dy, G, "f32", need_dw=False)[0]
+    ref = oracle.layer_backward(x, C, W1, dy, G)[0]
+    for f in range(n_in):
+        assert normwise(got[:, f], ref[:, f]) <= F32_LAYER_TOL, f
+
+
+@pytest.mark.parametrize("small", [1e-6, 1e-12])
+@pytest.mark.parametrize("B,n_in,n_out,G", BACK)
+def test_dx_pruned_and_small_edges(B, n_in, n_out, G, small):
+    """One output's gradient far larger than the others', and features whose edges to
+    that output are zero, or small: their dx is made of the small gradients.  Then
+    one feature of small weights beside ones of normal weights."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=12, dtype_name="f32")
+    o1 = n_out // 2
+    dy[:, np.arange(n_out) != o1] *= np.float32(small)
+    say(f"range dx edges {small:g} {n_in}->{n_out} G={G}")
+    for edge in (0.0, small):
+        C1, W1 = C.copy(), Wb.copy()
+        C1[o1, ::2] *= np.float32(edge)
+        W1[o1, ::2] *= np.float32(edge)
+        got = _run_backward(x, C1, W1, dy, G, "f32", need_dw=False)[0]
+        ref = oracle.layer_backward(x, C1, W1, dy, G)[0]
+        for f in range(n_in):
+            assert normwise(got[:, f], ref[:, f]) <= F32_LAYER_TOL, (edge, f)
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=13, dtype_name="f32")
+    C[:, 2], Wb[:, 2] = C[:, 2] * np.float32(small), Wb[:, 2] * np.float32(small)
+    C[:, 1, : G // 2] *= np.float32(small)
+    Wb[:, 1] *= np.float32(small)
+    got = _run_backward(x, C, Wb, dy, G, "f32", need_dw=False)[0]
+    ref = oracle.layer_backward(x, C, Wb, dy, G)[0]
+    for f in range(n_in):
+        assert normwise(got[:, f], ref[:, f]) <= F32_LAYER_TOL, f
+    low = (x[:, 1] > -1 + 1e-3) & (x[:, 1] < -1 + 2.0 / G * (G // 2 - 3) - 1e-3)
+    if low.sum() > 3:
+        assert normwise(got[low, 1], ref[low, 1]) <= F32_LAYER_TOL
