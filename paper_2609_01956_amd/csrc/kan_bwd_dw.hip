@@ -15,7 +15,7 @@
 // the largest of the workgroup's rows to 2^12 (from the maxima that the
 // transposition leaves per 64 rows), basis values by 2^12.  An output with a
 // non-finite dy, or a SiLU row with an infinite value, has a non-finite gradient
-// whatever the other rows hold: those are computed apart at the end.
+// whatever the other rows hold: those are summed again at the end (exact_tile).
 //
 // Per chunk of 32 batch rows the workgroup stages dy (transposed) and the A
 // operand in LDS, double-buffered.  A is built once per workgroup: a thread owns
@@ -99,6 +99,61 @@ __global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restr
 }
 
 // -------------------------------------------------------------------- kernel
+
+// fp32: elements of a wave's tile (32 K rows from kt, 32 outputs from o0; bit q of
+// mask: the lane's accumulator q) summed again on the fp32 instruction, straight from
+// the transposed operands, 64 batch rows at a time: the blocks where a dy or an x of
+// the tile is not finite.  A function of its own, so that the main loop keeps its
+// registers; args: the kernel's, in place.
+__device__ __attribute__((noinline)) void exact_tile(const uint32_t* args, int kt, int o0,
+                                                     uint32_t mask) {
+    struct Words { uint32_t w[sizeof(Dw2Args) / 4]; } words;
+    static_assert(sizeof(Words) == sizeof(Dw2Args), "whole words");
+#pragma unroll
+    for (size_t i = 0; i < sizeof(Dw2Args) / 4; ++i)
+        words.w[i] = __builtin_amdgcn_readfirstlane(args[i]);
+    const Dw2Args a = __builtin_bit_cast(Dw2Args, words);
+    kt = __builtin_amdgcn_readfirstlane(kt);
+    o0 = __builtin_amdgcn_readfirstlane(o0);
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int f = min((kt + r) / a.cp, a.in - 1), c = (kt + r) % a.cp;  // the lane's K row
+    const float* xr = static_cast<const float*>(a.xt) + (int64_t)f * a.bpad + 32 * h;
+    const float* dr = static_cast<const float*>(a.dyt) + (int64_t)(o0 + r) * a.bpad + 32 * h;
+    // the lane's maximum per block: an output's, or a K row's feature's
+    const bool has = h != 0 || o0 + r < a.out32;
+    const float* mx = h != 0 ? a.xmax + f : a.dymax + min(o0 + r, a.out32 - 1);
+    const int mw = h != 0 ? a.in32 : a.out32;
+    const int64_t b_begin = (int64_t)blockIdx.y * a.rows_per_split;
+    const int64_t b_end = min(b_begin + a.rows_per_split, a.bpad);
+    floatx16 acc;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
+#pragma unroll 1
+    for (int64_t b0 = b_begin; b0 < b_end; b0 += 64) {
+        const bool bad = has && __float_as_uint(mx[b0 / 64 * mw]) >> 31 != 0;
+        if (__ballot(bad) == 0) continue;
+#pragma unroll 2
+        for (int i = 0; i < 32; i += 4) {
+            const floatx4 x4 = *reinterpret_cast<const floatx4*>(xr + b0 + i);
+            const floatx4 d4 = *reinterpret_cast<const floatx4*>(dr + b0 + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = half_basis(__builtin_fmaf(x4[e], a.inv_h, a.a_int + 1.0f - (float)c) +
+                                           coord_lo(x4[e], a.xlim, a.inv_lo, a.a_frac));
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(c == 0 ? half_silu_w(x4[e]) : v, d4[e],
+                                                           acc, 0, 0, 0);
+            }
+        }
+        uint32_t open = mask;  // (a NaN stays one)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) open &= ~(acc[q] != acc[q] ? 1u << q : 0u);
+        if (__ballot(open != 0) == 0) break;
+    }
+    float* P = a.P + ((int64_t)blockIdx.y * a.out32 + o0 + r) * a.kr + kt + 4 * h;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        if ((mask >> q & 1) != 0) P[8 * (q / 4) + q % 4] = acc[q];
+}
 
 // FULL: cp = 16, so every thread owns a (row, feature) of each chunk.
 template <typename T, int OH, int NFW, bool FULL>
@@ -368,7 +423,14 @@ void dw_split_kernel(Dw2Args a) {
     }
     if (ck < nchunks) chunk(0, dq[0], xq[1], prev[1], std::false_type{});
     if (own && nanx) nanf[fl] = 1;
-    __syncthreads();
+    bool fix = false;  // (fp32) some element is to be summed again
+    if constexpr (BF) {
+        __syncthreads();
+    } else {
+        int any = 0;
+        for (int i = tid; i < OT + 16; i += kThreads) any |= (i < OT ? exd[i] : exs[i - OT]) >> 16;
+        fix = __syncthreads_or(any) != 0;
+    }
 
     // acc[rt][nf][q] = (scaled dW^T / 2)[K row kt0 + lr][output], lr = 32 (kg RF + rt) +
     // 8 (q / 4) + 4 h + q % 4.  A feature with a NaN input: its basis gradients
@@ -381,6 +443,7 @@ void dw_split_kernel(Dw2Args a) {
             const int ol = (oh * NFW + nf) * 32 + r;
             const int o = ot0 + ol;
             int ed = 0;
+            uint32_t again = 0;  // elements to be summed again
             if constexpr (!BF) ed = (exd[ol] & 0xffff) - 512 - 12;
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
@@ -399,44 +462,20 @@ void dw_split_kernel(Dw2Args a) {
                     }
                     v[e] = isn && (c != 0 || e != 0) ? __builtin_nanf("") : t;
                 }
-                if (o < a.out32 && kt0 + lr < a.kr)
+                if (o < a.out32 && kt0 + lr < a.kr) {
                     *reinterpret_cast<floatx4*>(P + (int64_t)o * a.kr + kt0 + lr) = v;
-            }
-        }
-    }
-    if constexpr (!BF) {
-        // outputs with a non-finite dy, SiLU rows with a non-finite value: the sum
-        // over the rows that hold one (with the zeros of the basis, whose product
-        // with an infinity is NaN)
-        int any = 0;
-        for (int i = tid; i < OT + 16; i += kThreads) any |= (i < OT ? exd[i] : exs[i - OT]) >> 16;
-        if (__syncthreads_or(any)) {
-            for (int ol = 0; ol < OT; ++ol) {
-                const int o = ot0 + ol;
-                if (o >= a.out32) break;
-                const bool od = (exd[ol] >> 16) != 0;
-                for (int lr = tid; lr < KT && kt0 + lr < a.kr; lr += kThreads) {
-                    const int f = lr / a.cp, c = lr - f * a.cp;
-                    const bool fs = c == 0 && (exs[f] >> 16) != 0;
-                    if ((!od && !fs) || F0 + f >= a.in || (c != 0 && nanf[f])) continue;
-                    float s = 0.0f;
-                    for (int64_t b = b_begin; b < b_end && s == s; ++b) {
-                        const float dv = dyt[(int64_t)o * a.bpad + b];
-                        const float x = xt[(int64_t)(F0 + f) * a.bpad + b];
-                        float v;
-                        if (c == 0) {
-                            v = half_silu_w(x);
-                        } else {
-                            v = half_basis(__builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - (float)c) +
-                                           coord_lo(x, a.xlim, a.inv_lo, a.a_frac));
-                        }
-                        if (!(__builtin_fabsf(dv) < __builtin_inff()) ||
-                            !(__builtin_fabsf(v) < __builtin_inff()))
-                            s += v * dv;
+                    if (!BF && fix && F0 + f < a.in) {
+                        // an output's non-finite dy reaches every K row (0 times infinity
+                        // is NaN), a feature's non-finite x its SiLU row
+                        const bool od = exd[BF ? 0 : ol] >> 16 != 0, fs = exs[BF ? 0 : f] >> 16 != 0;
+                        if (c == 0 && (od || fs)) again |= 1u << (4 * m);
+                        if (od && !isn) again |= (c == 0 ? 14u : 15u) << (4 * m);
                     }
-                    if (s != 0.0f) P[(int64_t)o * a.kr + kt0 + lr] = s;
                 }
             }
+            if (!BF && __ballot(again != 0) != 0)
+                exact_tile((const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr(),
+                           kt0 + 32 * (kg * RF + rt), ot0 + (oh * NFW + nf) * 32, again);
         }
     }
 }

@@ -11,7 +11,8 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_common import normwise, say
+from gpu_common import device, normwise, say, torch
+from paper_2609_01956_amd import binding as kb
 from test_gpu_backward import _case, _check, _run
 
 pytestmark = pytest.mark.gpu
@@ -100,3 +101,36 @@ def test_backward_f32_non_finite(n_out, G):
     assert normwise(dx[~bad], clean[0][~bad]) <= 1e-5
     inside = (u > 0.01) & (u < 1.9) & (np.arange(B) < S) & (dy2[:, 5] != 0)
     assert not np.isfinite(dx[inside, 3]).any()
+
+
+def test_backward_f32_non_finite_late_row():
+    """Infinite gradients in one late row of a batch split (3328 rows): infinities where the basis holds the row, NaN (0 times infinity)
+    elsewhere, the outputs without one bitwise as before, and about the same time (the
+    flagged outputs are summed again over the 64-row blocks that hold a non-finite
+    value, not over every row)."""
+    B, n_in, n_out, G, row = 16384, 784, 256, 10, 6600
+    g = torch.Generator(device=device()).manual_seed(3)
+    x = torch.rand(B, n_in, device=device(), generator=g) * 2 - 1
+    C = torch.randn(n_out, n_in, G + 3, device=device(), generator=g) * 0.1
+    Wb = torch.randn(n_out, n_in, device=device(), generator=g)
+    dy = torch.randn(B, n_out, device=device(), generator=g)
+    bad = dy.clone()
+    bad[row, ::2] = float("inf")
+    times = {}
+    say("backward non-finite late row 16384 x 784 -> 256")
+    for name, d in (("clean", dy), ("bad", bad), ("clean", dy), ("bad", bad)):
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        out = kb.layer_backward(x, C, Wb, d, G, need_dx=False)
+        end.record()
+        torch.cuda.synchronize()
+        times[name] = (start.elapsed_time(end), out)
+    (t0, (_, cC, cW)), (t1, (_, dC, dW)) = times["clean"], times["bad"]
+    assert torch.equal(dC[1::2], cC[1::2]) and torch.equal(dW[1::2], cW[1::2])
+    assert torch.equal(torch.isposinf(dW[::2]), (x[row] > 0).expand(n_out // 2, -1))
+    assert torch.equal(torch.isneginf(dW[::2]), (x[row] < 0).expand(n_out // 2, -1))
+    u = (x[row].double()[:, None] + 1) * (G / 2) + 3 - torch.arange(G + 3, device=device())
+    inside, edge = (u > 1e-3) & (u < 4 - 1e-3), (u.abs() <= 1e-3) | ((u - 4).abs() <= 1e-3)
+    assert torch.isposinf(dC[::2])[:, inside].all()
+    assert torch.isnan(dC[::2])[:, ~(inside | edge)].all()
+    assert t1 < 4 * t0, (t0, t1)
