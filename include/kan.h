@@ -350,7 +350,11 @@ kan_status kan_layer_plan(const kan_grid* grid, kan_dtype dtype, int64_t batch,
  * columns do not divide 256, which use the fp32 matrix instruction, and dx of
  * features (in pairs up to G = 12) whose terms would not hold 22 bits of the largest of
  * any four consecutive coefficients, or that have four consecutive coefficients
- * of 0 for some outputs only: these run on the fp32 instruction too.  For layers of at
+ * of 0 for some outputs only: these run on the fp32 instruction too.  So do single
+ * weight gradients made of values far below the largest: the terms hold 21 bits
+ * of a dy within 2^-29 of its output's largest (of the rows of a batch split), and of
+ * a SiLU value likewise, and a sum in which the rounding of smaller ones could
+ * reach 2^-17 is taken again.  For layers of at
  * most 16 outputs from 16384 rows on (when a feature's G + 7 columns, rounded
  * down to even, times its outputs rounded up to a multiple of 4 stay within
  * 256) dx runs instead on the vector ALUs over the SiLU column and the four
@@ -375,8 +379,8 @@ kan_status kan_layer_backward(const kan_grid* grid, kan_dtype dtype, int64_t bat
 /*
  * kan_layer_backward_workspace_bytes -- size in bytes of the workspace
  * kan_layer_backward needs for this grid, dtype, batch and shape (the packed
- * weights of the dx contraction, x and dy transposed, in fp32 their maxima per
- * 64 rows, and the fp32 partial weight gradients of the batch splits).  Writes *bytes.  Returns KAN_OK,
+ * weights of the dx contraction, x and dy transposed, in fp32 the
+ * range of their values per 64 rows, and the fp32 partial weight gradients of the batch splits).  Writes *bytes.  Returns KAN_OK,
  * KAN_ERR_INVALID_ARG (bytes == NULL, bad grid or sizes, batch < 0) or
  * KAN_ERR_UNSUPPORTED.
  */

@@ -896,8 +896,8 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
                                dim3((unsigned)((g.bpad + 63) / 64), (unsigned)((drows + 63) / 64)),
                                dim3(256), 0, s, x, xt, a.batch, a.in, g.bpad, drows, vec);
         } else if (g.dw2 && a.dcoef != nullptr) {
-            e = launch_transpose_max(x, xt, reinterpret_cast<float*>(ws + g.off_xm), a.batch, a.in,
-                                     g.bpad, s);
+            e = launch_transpose_range(x, xt, reinterpret_cast<floatx2*>(ws + g.off_xr), true, a.batch,
+                                       a.in, g.bpad, s);
             if (e != hipSuccess) return e;
         } else {
             hipLaunchKernelGGL((transpose_kernel<T, false>),
@@ -955,9 +955,10 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
                                    dim3(256), 0, s, static_cast<const T*>(a.dy), dyt, a.batch,
                                    a.out, g.bpad, g.out32, vec);
             } else if (g.dw2) {
-                e = launch_transpose_max(reinterpret_cast<const float*>(a.dy), reinterpret_cast<float*>(dyt),
-                                         reinterpret_cast<float*>(ws + g.off_dm), a.batch, a.out,
-                                         g.bpad, s);
+                e = launch_transpose_range(reinterpret_cast<const float*>(a.dy),
+                                           reinterpret_cast<float*>(dyt),
+                                           reinterpret_cast<floatx2*>(ws + g.off_dr), false,
+                                           a.batch, a.out, g.bpad, s);
                 if (e != hipSuccess) return e;
             } else {
                 hipLaunchKernelGGL((transpose_kernel<T, true>),
@@ -970,8 +971,8 @@ hipError_t backward_t(const BwdGeom& g, const BwdArgs& a, hipStream_t s) {
                 Dw2Args d;
                 d.xt = xt;
                 d.dyt = dyt;
-                d.xmax = reinterpret_cast<const float*>(ws + g.off_xm);
-                d.dymax = reinterpret_cast<const float*>(ws + g.off_dm);
+                d.xrange = reinterpret_cast<const floatx2*>(ws + g.off_xr);
+                d.dyrange = reinterpret_cast<const floatx2*>(ws + g.off_dr);
                 d.P = P;
                 d.bpad = g.bpad;
                 d.in = a.in;
@@ -1040,7 +1041,7 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     g->kt = 256;
     g->ktiles = (g->kr + g->kt - 1) / g->kt;
     // whole features per 256 K rows: the kernel of kan_bwd_dw.hip, whose fp32 form
-    // takes at most 128 outputs per workgroup (and keeps maxima per 64 rows)
+    // takes at most 128 outputs per workgroup (and keeps ranges per 64 rows)
     // (fp32 from 8192 rows: below, its sums are short and the fp32 instruction's
     // kernel as exact and, with few workgroups, as fast: 1024 x 2 -> 5 59 us per
     // training step against 64)
@@ -1107,10 +1108,10 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     off = align256(off + (size_t)(g->dw2 ? g->otiles * ot : g->out32) * (size_t)g->bpad * es);
     g->off_xt = off;
     off = align256(off + (size_t)((in + 31) / 32 * 32) * (size_t)g->bpad * es);
-    g->off_xm = off;
-    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)((in + 31) / 32 * 32) * 4);
-    g->off_dm = off;
-    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)g->out32 * 4);
+    g->off_xr = off;
+    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)((in + 31) / 32 * 32) * 8);
+    g->off_dr = off;
+    if (rq == 64) off = align256(off + (size_t)(g->bpad / 64) * (size_t)g->out32 * 8);
     g->off_p = off;
     off = align256(off + (size_t)(g->split > 0 ? g->split : 1) * g->out32 * (size_t)g->kr * 4);
     g->off_dxp = off;

@@ -12,10 +12,15 @@
 // 256 at 16384 rows: 794 -> 312 us; relative error against float64 6.2e-7 ->
 // 4.0e-7).  dy is
 // scaled per output and SiLU values per feature by the power of two that brings
-// the largest of the workgroup's rows to 2^12 (from the maxima that the
-// transposition leaves per 64 rows), basis values by 2^12.  An output with a
-// non-finite dy, or a SiLU row with an infinite value, has a non-finite gradient
-// whatever the other rows hold: those are summed again at the end (exact_tile).
+// the largest of the workgroup's rows to 2^14 (from the maxima that the
+// transposition leaves per 64 rows), basis values by 2^12, and second terms by
+// 2^11 more: their products have accumulators of their own, and so an operand is
+// within 2^-36 or 2^-23 of its value.  Where an output's dy or a feature's SiLU values
+// range over more than 2^29 (the transposition leaves the least, too), a sum can be
+// made of values alone that the terms hold badly; the sums that are then below
+// what these errors can add up to, times 2^17, are taken again at the end
+// (exact_tile), and so are those of an output with a non-finite dy and of a SiLU row
+// with an infinite value.
 //
 // Per chunk of 32 batch rows the workgroup stages dy (transposed) and the A
 // operand in LDS, double-buffered.  A is built once per workgroup: a thread owns
@@ -31,7 +36,10 @@ namespace kan {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kBasisExp = 12;
+constexpr int kBasisExp = 12, kDyExp = 14;
+constexpr int kTermExp = 11;     // second terms: their own scale
+constexpr float kTermScale = 1 << kTermExp;
+constexpr int kSpreadBits = 29;  // exponents within which two terms hold 21 bits and more
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
@@ -43,7 +51,7 @@ __device__ __forceinline__ float half_silu_w(float x) {
     return x * __builtin_amdgcn_rcpf(__builtin_fmaf(__expf(-x), 2.0f, 2.0f));
 }
 
-// Exponent of a maximum (of finite values): scaling by 2^(12 - e) brings it to [2^12, 2^13).
+// Exponent of a maximum (of finite values): scaling by 2^(14 - e) brings it to [2^14, 2^15).
 __device__ __forceinline__ int max_exp(float m) {
     return (int)((__float_as_uint(m) >> 23) & 0xffu) - 127;
 }
@@ -53,17 +61,19 @@ __device__ __forceinline__ int max_exp(float m) {
 // dst[c][b] = src[b][c], zero-padded to ceil(cols / 32) * 32 rows and rpad (a
 // multiple of 64) columns, in tiles of 64 rows by 32 columns; and per tile the
 // largest finite |value| of each column, with the sign bit set if a value is not
-// finite: vmax[b / 64][c], c < ceil(cols / 32) * 32.
-__global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restrict__ src,
-                                                            float* __restrict__ dst,
-                                                            float* __restrict__ vmax,
-                                                            int64_t rows, int cols, int64_t rpad) {
+// finite, and the least nonzero |value|, or at most that of |silu(value)| / 2 (infinity if none):
+// range[b / 64][c], c < ceil(cols / 32) * 32.
+template <bool SILU>
+__global__ __launch_bounds__(256) void transpose_range_kernel(const float* __restrict__ src,
+                                                              float* __restrict__ dst,
+                                                              floatx2* __restrict__ range,
+                                                              int64_t rows, int cols, int64_t rpad) {
     __shared__ float tile[64][33];
-    __shared__ float red[8][33];
+    __shared__ float red[8][33], redl[8][33];
     const int64_t b0 = (int64_t)blockIdx.x * 64;
     const int c0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    float m = 0.0f;
+    float m = 0.0f, lo = __builtin_inff(), neg = 0.0f;
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -74,7 +84,17 @@ __global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restr
         const bool fin = av < __builtin_inff();
         m = __builtin_fmaxf(m, fin ? av : 0.0f);
         bad |= !fin;
+        lo = av > 0.0f ? __builtin_fminf(lo, av) : lo;  // (a NaN isn't)
+        if (SILU) neg = __builtin_fminf(neg, v);
     }
+    if (SILU && lo < __builtin_inff()) {
+        // least |silu|: of the value nearest 0, at its negative, or of the lowest (to
+        // -85, below which it is soon 0)
+        const float l0 = half_silu_w(-__builtin_fminf(lo, 85.0f));
+        const float l1 = half_silu_w(__builtin_fmaxf(neg, -85.0f));
+        lo = __builtin_fminf(-l0, neg < 0.0f ? -l1 : -l0);
+    }
+    redl[ty][tx] = lo;
     red[ty][tx] = bad ? -m : m;
     if (bad && m == 0.0f) red[ty][tx] = -0.0f;
     __syncthreads();
@@ -92,9 +112,10 @@ __global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restr
             const float v = red[k][threadIdx.x];
             mx = __builtin_fmaxf(mx, __builtin_fabsf(v));
             s |= __float_as_uint(v) & 0x80000000u;
+            lo = __builtin_fminf(lo, redl[k][threadIdx.x]);
         }
-        vmax[(int64_t)blockIdx.x * (gridDim.y * 32) + c0 + threadIdx.x] =
-            __uint_as_float(__float_as_uint(mx) | s);
+        range[(int64_t)blockIdx.x * (gridDim.y * 32) + c0 + threadIdx.x] =
+            floatx2{__uint_as_float(__float_as_uint(mx) | s), lo};
     }
 }
 
@@ -103,10 +124,13 @@ __global__ __launch_bounds__(256) void transpose_max_kernel(const float* __restr
 // fp32: elements of a wave's tile (32 K rows from kt, 32 outputs from o0; bit q of
 // mask: the lane's accumulator q) summed again on the fp32 instruction, straight from
 // the transposed operands, 64 batch rows at a time: the blocks where a dy or an x of
-// the tile is not finite.  A function of its own, so that the main loop keeps its
-// registers; args: the kernel's, in place.
+// the tile is not finite, and those with a row in the support of one of the K rows of
+// small (bit r: K row kt + r).  A function of its own, so that the main loop keeps its
+// registers; args: the kernel's, in place.  dW of 16384 x 784 -> 256: 0.38 ms per call
+// without such elements, 1.4 ms where they are all (one row of gradients of 1e10
+// beside others of 1; 0.8 ms where the fp32 instruction was the kernel's own).
 __device__ __attribute__((noinline)) void exact_tile(const uint32_t* args, int kt, int o0,
-                                                     uint32_t mask) {
+                                                     uint32_t mask, uint32_t small) {
     struct Words { uint32_t w[sizeof(Dw2Args) / 4]; } words;
     static_assert(sizeof(Words) == sizeof(Dw2Args), "whole words");
 #pragma unroll
@@ -115,44 +139,108 @@ __device__ __attribute__((noinline)) void exact_tile(const uint32_t* args, int k
     const Dw2Args a = __builtin_bit_cast(Dw2Args, words);
     kt = __builtin_amdgcn_readfirstlane(kt);
     o0 = __builtin_amdgcn_readfirstlane(o0);
+    small = __builtin_amdgcn_readfirstlane(small);
     const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
     const int f = min((kt + r) / a.cp, a.in - 1), c = (kt + r) % a.cp;  // the lane's K row
     const float* xr = static_cast<const float*>(a.xt) + (int64_t)f * a.bpad + 32 * h;
     const float* dr = static_cast<const float*>(a.dyt) + (int64_t)(o0 + r) * a.bpad + 32 * h;
-    // the lane's maximum per block: an output's, or a K row's feature's
+    // the lane's range per block: an output's, or a K row's feature's
     const bool has = h != 0 || o0 + r < a.out32;
-    const float* mx = h != 0 ? a.xmax + f : a.dymax + min(o0 + r, a.out32 - 1);
-    const int mw = h != 0 ? a.in32 : a.out32;
+    const floatx2* rng = h != 0 ? a.xrange + f : a.dyrange + min(o0 + r, a.out32 - 1);
+    const int rw = h != 0 ? a.in32 : a.out32;
+    // the tile's features (two of 16 columns, or 32 columns from c0 of one) and K rows
+    // of small
+    const int f0 = kt / a.cp, c0 = kt % a.cp, f1 = a.cp == 16 ? min(f0 + 1, a.in - 1) : f0;
+    const float* x0 = static_cast<const float*>(a.xt) + (int64_t)f0 * a.bpad + lane;
+    const float* x1 = static_cast<const float*>(a.xt) + (int64_t)f1 * a.bpad + lane;
+    const uint32_t small0 = a.cp == 16 ? small & 0xffffu : small;
+    const uint32_t small1 = a.cp == 16 ? small >> 16 : 0u;
+    const bool every = c0 == 0 && ((small0 | small1) & 1u) != 0;  // a SiLU row: every block
+    auto meets = [&](float x, uint32_t cols) -> bool {
+        const float sv = __builtin_fmaf(x, a.inv_h, a.a_int + 1.0f) +
+                         coord_lo(x, a.xlim, a.inv_lo, a.a_frac);
+        // window columns first .. first + 3, and one more on each side for sv's rounding
+        const int first = (int)__builtin_amdgcn_fmed3f(__builtin_floorf(sv) - 1.0f, -8.0f,
+                                                       (float)(a.cp + 8)) - c0;
+        const uint64_t win = first < -8 || first > 32 ? 0 : 0x3full << (first + 8) >> 1;
+        return ((uint32_t)(win >> 8) & cols) != 0;
+    };
     const int64_t b_begin = (int64_t)blockIdx.y * a.rows_per_split;
     const int64_t b_end = min(b_begin + a.rows_per_split, a.bpad);
+    auto value = [&](float x, int col) -> float {  // of K row col of x's feature
+        const float v = half_basis(__builtin_fmaf(x, a.inv_h, a.a_int + 1.0f - (float)col) +
+                                   coord_lo(x, a.xlim, a.inv_lo, a.a_frac));
+        return col == 0 ? half_silu_w(x) : v;
+    };
+    float* P = a.P + ((int64_t)blockIdx.y * a.out32 + o0) * a.kr + kt;
+    // A few elements (sums that cancel): one after the other, a row per lane.  (Softmax
+    // gradients, 16384 x 784 -> 256, some elements in all: dW 588 -> 412 us)
+    int count = __builtin_popcount(mask);
+#pragma unroll
+    for (int k = 1; k < 64; k *= 2) count += __shfl_xor(count, k);
+    if (__builtin_amdgcn_readfirstlane(count) <= 8) {
+#pragma unroll 1
+        for (uint64_t who = __ballot(mask != 0); who != 0; who = __ballot(mask != 0)) {
+            const int src = __ffsll((unsigned long long)who) - 1;
+            const int q = __builtin_amdgcn_readlane(__ffs((int)mask) - 1, src);
+            const int kr = 8 * (q / 4) + 4 * (src / 32) + q % 4, o = src % 32;
+            const int col = (kt + kr) % a.cp;
+            const float* xs = static_cast<const float*>(a.xt) + (int64_t)((kt + kr) / a.cp) * a.bpad;
+            const float* ds = static_cast<const float*>(a.dyt) + (int64_t)(o0 + o) * a.bpad;
+            float sum = 0.0f;
+#pragma unroll 8
+            for (int64_t b = b_begin + lane; b < b_end; b += 64)
+                sum = __builtin_fmaf(value(xs[b], col), ds[b], sum);
+#pragma unroll
+            for (int k = 1; k < 64; k *= 2) sum += __shfl_xor(sum, k);
+            if (lane == src) P[(int64_t)o * a.kr + kr] = sum;
+            if (lane == src) mask &= mask - 1;
+        }
+        return;
+    }
     floatx16 acc;
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
+    bool done = false;
 #pragma unroll 1
-    for (int64_t b0 = b_begin; b0 < b_end; b0 += 64) {
-        const bool bad = has && __float_as_uint(mx[b0 / 64 * mw]) >> 31 != 0;
-        if (__ballot(bad) == 0) continue;
-#pragma unroll 2
-        for (int i = 0; i < 32; i += 4) {
-            const floatx4 x4 = *reinterpret_cast<const floatx4*>(xr + b0 + i);
-            const floatx4 d4 = *reinterpret_cast<const floatx4*>(dr + b0 + i);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = half_basis(__builtin_fmaf(x4[e], a.inv_h, a.a_int + 1.0f - (float)c) +
-                                           coord_lo(x4[e], a.xlim, a.inv_lo, a.a_frac));
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(c == 0 ? half_silu_w(x4[e]) : v, d4[e],
-                                                           acc, 0, 0, 0);
+    for (int64_t bb = b_begin; bb < b_end && !done; bb += 16 * 64) {
+        const int n = (int)min((int64_t)16, (b_end - bb) / 64);
+        uint32_t blocks = 0;
+        if (small == 0) {
+#pragma unroll 8
+            for (int j = 0; j < n; ++j) {
+                const bool in = has && __float_as_uint(rng[(bb / 64 + j) * rw][0]) >> 31 != 0;
+                blocks |= (uint32_t)(__ballot(in) != 0) << j;
+            }
+        } else {
+#pragma unroll 8
+            for (int j = 0; j < n; ++j) {
+                bool in = every || (has && __float_as_uint(rng[(bb / 64 + j) * rw][0]) >> 31 != 0);
+                in |= meets(x0[bb + 64 * j], small0) || meets(x1[bb + 64 * j], small1);
+                blocks |= (uint32_t)(__ballot(in) != 0) << j;
             }
         }
-        uint32_t open = mask;  // (a NaN stays one)
+#pragma unroll 1
+        for (; blocks != 0; blocks &= blocks - 1) {
+            const int64_t b0 = bb + 64 * (__ffs((int)blocks) - 1);
+#pragma unroll 2
+            for (int i = 0; i < 32; i += 4) {
+                const floatx4 x4 = *reinterpret_cast<const floatx4*>(xr + b0 + i);
+                const floatx4 d4 = *reinterpret_cast<const floatx4*>(dr + b0 + i);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) open &= ~(acc[q] != acc[q] ? 1u << q : 0u);
-        if (__ballot(open != 0) == 0) break;
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(value(x4[e], c), d4[e], acc, 0, 0, 0);
+            }
+            uint32_t open = mask;  // (a NaN stays one)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) open &= ~(acc[q] != acc[q] ? 1u << q : 0u);
+            done = __ballot(open != 0) == 0;
+            if (done) break;
+        }
     }
-    float* P = a.P + ((int64_t)blockIdx.y * a.out32 + o0 + r) * a.kr + kt + 4 * h;
 #pragma unroll
     for (int q = 0; q < 16; ++q)
-        if ((mask >> q & 1) != 0) P[8 * (q / 4) + q % 4] = acc[q];
+        if ((mask >> q & 1) != 0) P[(int64_t)r * a.kr + 4 * h + 8 * (q / 4) + q % 4] = acc[q];
 }
 
 // FULL: cp = 16, so every thread owns a (row, feature) of each chunk.
@@ -173,7 +261,8 @@ void dw_split_kernel(Dw2Args a) {
     __shared__ u32x4 dys[2][NT][OT * 4];
     __shared__ u32x4 as[2][NT][KT * AROW / 16];
     __shared__ int nanf[16];
-    __shared__ int exd[BF ? 1 : OT], exs[BF ? 1 : 16];  // scale exponents; bit 16: non-finite
+    // scale exponents; bit 16: non-finite, bit 17: a spread past kSpreadBits
+    __shared__ int exd[BF ? 1 : OT], exs[BF ? 1 : 16];
 
     const T* __restrict__ xt = static_cast<const T*>(a.xt);
     const T* __restrict__ dyt = static_cast<const T*>(a.dyt);
@@ -190,21 +279,24 @@ void dw_split_kernel(Dw2Args a) {
     for (int i = tid; i < 2 * NT * KT * AROW / 16; i += kThreads)
         (&as[0][0][0])[i] = u32x4{0u, 0u, 0u, 0u};
     if constexpr (!BF) {
-        // maxima over the split's rows
+        // ranges over the split's rows
         const int64_t m0 = b_begin / 64, m1 = (b_end + 63) / 64;
         for (int i = tid; i < OT + 16; i += kThreads) {
             const bool isx = i >= OT;
             const int c = isx ? F0 + i - OT : ot0 + i;
             const int w = isx ? a.in32 : a.out32;
-            const float* src = isx ? a.xmax : a.dymax;
-            float m = 0.0f;
+            const floatx2* src = isx ? a.xrange : a.dyrange;
+            float m = 0.0f, lo = __builtin_inff();
             uint32_t s = 0;
             if (c < w)
+#pragma unroll 8
                 for (int64_t k = m0; k < m1; ++k) {
-                    const float v = src[k * w + c];
-                    m = __builtin_fmaxf(m, __builtin_fabsf(v));
-                    s |= __float_as_uint(v) >> 31;
+                    const floatx2 v = src[k * w + c];
+                    m = __builtin_fmaxf(m, __builtin_fabsf(v[0]));
+                    s |= __float_as_uint(v[0]) >> 31;
+                    lo = __builtin_fminf(lo, v[1]);
                 }
+            if (max_exp(lo) < max_exp(m) - kSpreadBits) s |= 2u;
             // (low half: the exponent, biased by 512)
             const int e = (max_exp(m) + 512) | (int)(s << 16);
             if (isx) exs[i - OT] = e;
@@ -222,7 +314,7 @@ void dw_split_kernel(Dw2Args a) {
     const uint32_t abase = (uint32_t)(min(fl, nfeat - 1) * a.cp * AROW + bl * 2);
     const float cmax = (float)(a.cp - 4);
     int sscale = 0;
-    if constexpr (!BF) sscale = 12 - ((exs[min(fl, nfeat - 1)] & 0xffff) - 512);
+    if constexpr (!BF) sscale = kDyExp - ((exs[min(fl, nfeat - 1)] & 0xffff) - 512);
     // dy units of the thread: outputs ol + k kThreads / UR, 16-byte load w of each
     // output's 32 values (the transposed dy has rows up to the last tile's end:
     // what those past out32 hold is not used)
@@ -273,15 +365,15 @@ void dw_split_kernel(Dw2Args a) {
                     *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&dys[buf][0][0]) + dput + k * (KO * 64)) =
                         d[k];
                 } else {
-                    const int ds = 12 + 512 - (exd[ol0 + k * KO] & 0xffff);
+                    const int ds = kDyExp + kTermExp + 512 - (exd[ol0 + k * KO] & 0xffff);
                     f16x4_t t0, t1;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         // (a non-finite dy becomes a finite one: its output is computed apart)
                         const float v = __builtin_amdgcn_fmed3f(
-                            __builtin_ldexpf(__uint_as_float(d[k][e]), ds), -60000.0f, 60000.0f);
-                        t0[e] = (_Float16)v;
-                        t1[e] = (_Float16)(v - (float)t0[e]);
+                            __builtin_ldexpf(__uint_as_float(d[k][e]), ds), -0x1p26f, 0x1p26f);
+                        t0[e] = (_Float16)(v * (1.0f / kTermScale));
+                        t1[e] = (_Float16)__builtin_fmaf((float)t0[e], -kTermScale, v);
                     }
                     *reinterpret_cast<u32x2_t*>(reinterpret_cast<char*>(&dys[buf][0][0]) + dput + k * (KO * 64)) =
                         __builtin_bit_cast(u32x2_t, t0);
@@ -326,15 +418,18 @@ void dw_split_kernel(Dw2Args a) {
                     st16(buf, 0, gn.adr + 2 * AROW, (uint16_t)w23);
                     st16(buf, 0, gn.adr + 3 * AROW, (uint16_t)(w23 >> 16));
                 } else {
-                    auto two = [&](uint32_t adr, float v) {
-                        const _Float16 t = (_Float16)v;
+                    auto two = [&](uint32_t adr, float v, float scale) {
+                        const _Float16 t = (_Float16)(v * scale);
                         st16(buf, 0, adr, __builtin_bit_cast(uint16_t, t));
-                        st16(buf, 1, adr, __builtin_bit_cast(uint16_t, (_Float16)(v - (float)t)));
+                        st16(buf, 1, adr,
+                             __builtin_bit_cast(uint16_t, (_Float16)__builtin_fmaf(
+                                                              (float)t, -kTermScale,
+                                                              v * (scale * kTermScale))));
                     };
-                    two(abase, __builtin_ldexpf(gn.sl, sscale));
+                    two(abase, __builtin_ldexpf(gn.sl, sscale), 1.0f);
 #pragma unroll
                     for (int m = 0; m < 4; ++m)
-                        two(gn.adr + m * AROW, gn.bv[m] * (float)(1 << kBasisExp));
+                        two(gn.adr + m * AROW, gn.bv[m], (float)(1 << kBasisExp));
                 }
             }
         }
@@ -431,6 +526,10 @@ void dw_split_kernel(Dw2Args a) {
         for (int i = tid; i < OT + 16; i += kThreads) any |= (i < OT ? exd[i] : exs[i - OT]) >> 16;
         fix = __syncthreads_or(any) != 0;
     }
+    // Bounds of the error of a sum by the terms' 2^-36 (scaled as the sum: basis
+    // values are at most 2^12 / 3, the others less than 2^15), times 2^17.
+    const float rows = (float)(b_end - b_begin);
+    const float tiny = rows * 0x1p-8f, tiny_silu = rows * 0x1p-3f;
 
     // acc[rt][nf][q] = (scaled dW^T / 2)[K row kt0 + lr][output], lr = 32 (kg RF + rt) +
     // 8 (q / 4) + 4 h + q % 4.  A feature with a NaN input: its basis gradients
@@ -443,8 +542,8 @@ void dw_split_kernel(Dw2Args a) {
             const int ol = (oh * NFW + nf) * 32 + r;
             const int o = ot0 + ol;
             int ed = 0;
-            uint32_t again = 0;  // elements to be summed again
-            if constexpr (!BF) ed = (exd[ol] & 0xffff) - 512 - 12;
+            uint32_t again = 0, small = 0;  // elements to be summed again, K rows of small ones
+            if constexpr (!BF) ed = (exd[ol] & 0xffff) - 512 - kDyExp;
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 const int lr = 32 * (kg * RF + rt) + 8 * m + 4 * h;
@@ -452,12 +551,16 @@ void dw_split_kernel(Dw2Args a) {
                 const int c = lr - f * (FULL ? 16 : a.cp);  // (a multiple of 4)
                 const bool isn = nanf[f] != 0;
                 floatx4 v;
+                uint32_t low = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float t = acc[rt][nf][4 * m + e];
                     if constexpr (!BF) {
-                        t += acc2[BF ? 0 : rt][BF ? 0 : nf][4 * m + e];
-                        const int ea = e == 0 && c == 0 ? (exs[f] & 0xffff) - 512 - 12 : -kBasisExp;
+                        t = __builtin_fmaf(acc2[BF ? 0 : rt][BF ? 0 : nf][4 * m + e],
+                                           1.0f / kTermScale, t);
+                        const bool si = e == 0 && c == 0;
+                        if (__builtin_fabsf(t) < (si ? tiny_silu : tiny)) low |= 1u << e;
+                        const int ea = si ? (exs[f] & 0xffff) - 512 - kDyExp : -kBasisExp;
                         t = __builtin_ldexpf(t, ed + ea);
                     }
                     v[e] = isn && (c != 0 || e != 0) ? __builtin_nanf("") : t;
@@ -467,15 +570,25 @@ void dw_split_kernel(Dw2Args a) {
                     if (!BF && fix && F0 + f < a.in) {
                         // an output's non-finite dy reaches every K row (0 times infinity
                         // is NaN), a feature's non-finite x its SiLU row
-                        const bool od = exd[BF ? 0 : ol] >> 16 != 0, fs = exs[BF ? 0 : f] >> 16 != 0;
-                        if (c == 0 && (od || fs)) again |= 1u << (4 * m);
-                        if (od && !isn) again |= (c == 0 ? 14u : 15u) << (4 * m);
+                        const int fo = exd[BF ? 0 : ol] >> 16, fx = c == 0 ? exs[BF ? 0 : f] >> 16 : 0;
+                        uint32_t bad = ((fo & 1) != 0 ? 15u : 0u) | (fx & 1);
+                        uint32_t few = low & (((fo & 2) != 0 ? 15u : 0u) | fx >> 1);
+                        // (not the padding past nb, nor what is NaN by its feature)
+                        const uint32_t keep = isn ? (c == 0 ? 1u : 0u)
+                                                  : (1u << min(4, max(0, a.nb + 1 - c))) - 1u;
+                        bad &= keep;
+                        few &= keep;
+                        again |= (bad | few) << (4 * m);
+                        small |= few << (8 * m + 4 * h);
                     }
                 }
             }
-            if (!BF && __ballot(again != 0) != 0)
+            if (!BF && __ballot(again != 0) != 0) {
+#pragma unroll
+                for (int k = 1; k < 64; k *= 2) small |= (uint32_t)__shfl_xor((int)small, k);
                 exact_tile((const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr(),
-                           kt0 + 32 * (kg * RF + rt), ot0 + (oh * NFW + nf) * 32, again);
+                           kt0 + 32 * (kg * RF + rt), ot0 + (oh * NFW + nf) * 32, again, small);
+            }
         }
     }
 }
@@ -501,11 +614,15 @@ hipError_t launch_t(const BwdGeom& g, const Dw2Args& a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_transpose_max(const float* src, float* dst, float* vmax, int64_t rows, int cols,
-                                int64_t rpad, hipStream_t s) {
-    hipLaunchKernelGGL(transpose_max_kernel,
-                       dim3((unsigned)(rpad / 64), (unsigned)((cols + 31) / 32)), dim3(256), 0, s,
-                       src, dst, vmax, rows, cols, rpad);
+hipError_t launch_transpose_range(const float* src, float* dst, floatx2* range, bool silu,
+                                  int64_t rows, int cols, int64_t rpad, hipStream_t s) {
+    const dim3 grid((unsigned)(rpad / 64), (unsigned)((cols + 31) / 32));
+    if (silu)
+        hipLaunchKernelGGL(transpose_range_kernel<true>, grid, dim3(256), 0, s, src, dst, range,
+                           rows, cols, rpad);
+    else
+        hipLaunchKernelGGL(transpose_range_kernel<false>, grid, dim3(256), 0, s, src, dst, range,
+                           rows, cols, rpad);
     return hipGetLastError();
 }
 

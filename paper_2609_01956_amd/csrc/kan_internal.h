@@ -281,7 +281,7 @@ struct BwdGeom {
     int split;      // dW: batch splits (partials summed by the reduce kernel)
     int rows_per_split;  // multiple of 32
     int64_t bpad;   // batch rounded up to 32 (columns of the transposed dy)
-    size_t off_wt, off_we, off_dyt, off_xt, off_xm, off_dm, off_p, off_dxp, bytes;  // workspace layout
+    size_t off_wt, off_we, off_dyt, off_xt, off_xr, off_dr, off_p, off_dxp, bytes;  // workspace layout
 };
 
 // Returns false when the sizes do not fit the kernels' index types.
@@ -306,16 +306,17 @@ struct BwdArgs {
 struct Dw2Args {
     const void* xt;      // x transposed: [in32][bpad]
     const void* dyt;     // dy transposed: [out32][bpad]
-    const float* xmax;   // fp32: maxima per 64 rows [bpad / 64][in32] (launch_transpose_max)
-    const float* dymax;  // fp32: [bpad / 64][out32]
+    const floatx2* xrange;   // fp32: ranges per 64 rows [bpad / 64][in32] (launch_transpose_range)
+    const floatx2* dyrange;  // fp32: [bpad / 64][out32]
     float* P;            // [split][out32][kr] partial sums of dW^T / 2
     int64_t bpad;
     int in, in32, out32, nb, cp, kr, rows_per_split;
     float inv_h, inv_lo, xlim, a_int, a_frac;
 };
 hipError_t launch_dw_split(bool bf16, const BwdGeom& g, const Dw2Args& a, hipStream_t s);
-hipError_t launch_transpose_max(const float* src, float* dst, float* vmax, int64_t rows, int cols,
-                                int64_t rpad, hipStream_t s);
+// silu: the least value of a range is (at most) that of |silu(src)| / 2.
+hipError_t launch_transpose_range(const float* src, float* dst, floatx2* range, bool silu,
+                                  int64_t rows, int cols, int64_t rpad, hipStream_t s);
 
 // Input gradient on the matrix cores (kan_bwd_dx.hip).
 struct Dx2Args {

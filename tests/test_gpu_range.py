@@ -161,3 +161,75 @@ def test_dx_pruned_and_small_edges(B, n_in, n_out, G, small):
     low = (x[:, 1] > -1 + 1e-3) & (x[:, 1] < -1 + 2.0 / G * (G // 2 - 3) - 1e-3)
     if low.sum() > 3:
         assert normwise(got[low, 1], ref[low, 1]) <= F32_LAYER_TOL
+
+
+DW = [(8192, 9, 40, 10), (8300, 5, 130, 30), (8200, 3, 20, 60), (20000, 33, 10, 12), (8257, 7, 300, 8)]
+
+
+def _columns_close(x, C, Wb, dy, G):
+    """Every column of the weight gradients (a feature's basis, or its SiLU weight)
+    against its own largest value over the outputs, and every output of it where all
+    of its own terms have one sign (else its sum may cancel)."""
+    _, dC, dW = _run_backward(x, C, Wb, dy, G, "f32", need_dx=False)
+    _, rC, rW = oracle.layer_backward(x, C, Wb, dy, G)
+    got, ref = np.concatenate([dC, dW[:, :, None]], 2), np.concatenate([rC, rW[:, :, None]], 2)
+    scale = np.abs(ref).max(axis=0, keepdims=True)
+    if (dy >= 0).all():
+        scale = np.repeat(scale, ref.shape[0], 0)
+        scale[..., :-1] = np.abs(rC)
+    err = np.abs(got - ref) / np.where(scale > 0, scale, 1.0)
+    assert err.max() <= F32_LAYER_TOL, (float(err.max()), np.unravel_index(err.argmax(), err.shape))
+
+
+# (the SiLU weight's gradient, up to 1.5 times the large one, stays finite in fp32)
+@pytest.mark.parametrize("big", [1e4, 1e6, 1e10, 1e15, F32_MAX / 4])
+@pytest.mark.parametrize("B,n_in,n_out,G", DW)
+def test_dw_one_large_gradient(B, n_in, n_out, G, big):
+    """One row of large gradients, for all outputs and for every third."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=21, dtype_name="f32")
+    for step in (1, 3):
+        d = dy.copy()
+        d[B // 2 + 5, ::step] = np.float32(big)
+        say(f"range dw gradient {big:g} step {step} B={B} {n_in}->{n_out} G={G}")
+        _columns_close(x, C, Wb, d, G)
+
+
+@pytest.mark.parametrize("small", [1e-3, 1e-6, 1e-9, 1e-12, 1e-20])
+@pytest.mark.parametrize("B,n_in,n_out,G", DW)
+def test_dw_columns_of_small_gradients(B, n_in, n_out, G, small):
+    """Bases that only rows of small gradients meet: many rows, then three; with
+    gradients of both signs and of one."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=22, dtype_name="f32", off=0.0)
+    rng = np.random.default_rng(5)
+    for rows in (np.arange(B) % 2 == 0, np.isin(np.arange(B), [7, B // 2, B - 2])):
+        x1, d = x.copy(), dy.copy()
+        d[rows] *= np.float32(small)
+        # odd features: the rows of small gradients in the upper half, the others below
+        x1[:, 1::2] = -np.abs(x1[:, 1::2])
+        x1[np.ix_(rows, np.arange(n_in) % 2 == 1)] *= -1
+        say(f"range dw small {small:g} rows {int(rows.sum())} B={B} {n_in}->{n_out} G={G}")
+        _columns_close(x1, C, Wb, d, G)
+        _columns_close(x1, C, Wb, np.abs(d), G)
+    # gradients over a wide range in every row, as a softmax leaves them
+    d = np.exp(-rng.uniform(0, -np.log(small), dy.shape)).astype(np.float32)
+    _columns_close(x, C, Wb, d, G)
+
+
+@pytest.mark.parametrize("xs", [1e4, 1e8, 1e12])
+@pytest.mark.parametrize("B,n_in,n_out,G", DW[:3])
+def test_dw_large_input_without_gradient(B, n_in, n_out, G, xs):
+    """Inputs far past the grid in rows that some outputs have no gradient in, and a
+    feature of tiny inputs beside them."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=23, dtype_name="f32")
+    x[11, 1] = xs
+    x[12:, 2] *= np.float32(1 / xs)
+    x[13:, 0] = np.where(np.arange(B - 13) % 2, 0.0, -40.0)
+    dy[11:13, ::2] = 0.0
+    dy[:13, 1::4] = 0.0
+    say(f"range dw input {xs:g} B={B} {n_in}->{n_out} G={G}")
+    _, dC, dW = _run_backward(x, C, Wb, dy, G, "f32", need_dx=False)
+    _, rC, rW = oracle.layer_backward(x, C, Wb, dy, G)
+    for o in (slice(0, None, 2), slice(1, None, 4), slice(3, None, 4)):
+        for f in range(n_in):
+            assert normwise(dW[o, f], rW[o, f]) <= F32_LAYER_TOL, f
+            assert normwise(dC[o, f], rC[o, f]) <= F32_LAYER_TOL, f
