@@ -47,18 +47,6 @@ __device__ __forceinline__ float silu_slope(float x) {
     return s * __builtin_fmaf(x, 1.0f - s, 1.0f);
 }
 
-// 16-byte units straight from memory into LDS (lane l: byte voff + soff of the
-// resource to LDS byte lds + 16 l).  In asm so that the compiler does not make
-// every LDS read wait for it; the caller waits for vmcnt before the stage is used.
-__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory");
-}
-
 // ------------------------------------------------------------------- packing
 
 template <typename T>

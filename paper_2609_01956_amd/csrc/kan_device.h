@@ -152,6 +152,20 @@ template <> struct Storage<uint16_t> {
     static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
+// 16-byte units straight from memory into LDS: lane l of the wave moves the
+// unit at byte voff + soff of the resource to LDS byte lds + 16 l.  (Written in
+// asm: with the builtin the compiler, unable to tell the stage being filled
+// from the one being read, waits for the move before every LDS read.  It has no
+// register result; the caller waits for vmcnt before the stage is used.)
+__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0 .. N - 1.
 template <int I, int N>
 struct StaticFor {

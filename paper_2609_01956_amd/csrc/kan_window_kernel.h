@@ -84,20 +84,6 @@ __device__ __forceinline__ float half_basis_k(float v) {
     else return 0.5f * basis_deg<K>(v);
 }
 
-// 16-byte units straight from memory into LDS: lane l of the wave moves the
-// unit at byte voff + soff of the resource to LDS byte lds + 16 l.  (Written in
-// asm: with the builtin the compiler, unable to tell the stage being filled
-// from the one being read, waits for the move before every LDS read.  It has no
-// register result; the caller waits for vmcnt before the stage is used.)
-__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory");
-}
-
 template <int NS> struct Elem;
 template <> struct Elem<2> {
     typedef float T;

@@ -9,6 +9,7 @@ import re
 import pytest
 
 from paper_2609_01956_amd import binding as kb
+from paper_2609_01956_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -449,3 +450,16 @@ def test_packed_forward_workspace_host_checks():
     assert call(X - 16, need) == bad                  # over x
     assert call(P + 64, need) == bad                  # over the packed weights
     assert call(Y - 16, need) == bad                  # over y
+
+
+def test_inline_asm_names_m0_where_it_writes_it():
+    """Inline assembly that writes m0 says so: the compiler may keep values of its own
+    there between the blocks."""
+    found = 0
+    for name in sorted(os.listdir(build.CSRC)):
+        text = open(os.path.join(build.CSRC, name)).read()
+        for block in re.findall(r"asm\s+volatile\s*\((.*?)\);", text, re.S):
+            if re.search(r"\bm0\s*,", block):
+                found += 1
+                assert '"m0"' in block, (name, block)
+    assert found > 0
