@@ -277,9 +277,12 @@ kan_status kan_layer_forward_packed_full_workspace_bytes(const kan_grid* grid, k
                                                          int32_t out_features, size_t* bytes);
 
 /*
- * kan_layer_plan -- the workgroup shape that kan_layer_forward_packed (and
- * kan_layer_forward) launches for a layer of this grid, dtype, shape and
- * batch.  Host only: no HIP call, nothing enqueued.  For testing and tuning.
+ * kan_layer_plan -- the workgroup shape with which the kernels on the packed weights
+ * run a layer of this grid, dtype, shape and batch: what kan_layer_forward_packed (and
+ * kan_layer_forward) launches with a forced shape, without a workspace, or with one
+ * that is too small for the window kernel.  Large layers that this kernel takes
+ * (kan_layer_forward_packed_full_workspace_bytes) run on it instead where the workspace
+ * holds its weights, which no plan reports.  Host only: no HIP call, nothing enqueued.  For testing and tuning.
  *
  *   shape    NULL for the library's own choice, or a forced {rf, wk, nw, cs}
  *            as accepted by kan_layer_forward_packed (validated here the same
@@ -428,8 +431,11 @@ kan_status kan_layer_forward_span_workspace_bytes(const kan_grid* grid, kan_dtyp
  * packed weights go to a fixed scratch array of KAN_NOALLOC_SCRATCH_BYTES
  * bytes that the library holds in device memory on every GPU it runs on,
  * until the process ends, followed (from the next 256-byte boundary) by the
- * partial sums of a split contraction when they fit there (else the layer
- * runs unsplit); nothing is allocated or freed by the call.
+ * window kernel's expanded weights and partial sums for the layers that run on it
+ * (kan_layer_forward_packed_full_workspace_bytes), or the partial sums of a split
+ * contraction, when they fit there; else the layer runs unsplit on the packed
+ * weights, so an fp32 layer's last bits depend on its size here as they do on the
+ * workspace there.  Nothing is allocated or freed by the call.
  *
  *   x, coef, base_w, y   as kan_layer_forward (caller-owned device memory)
  *

@@ -434,7 +434,8 @@ kan_status kan_layer_forward(const kan_grid* grid, kan_dtype dtype, int64_t batc
     const size_t es = dtype_size(dtype);
     const uint64_t ub = (uint64_t)batch;
     const size_t ws = geom.packed_bytes;
-    // (the whole workspace: past the packed weights it may hold partial sums)
+    // (the whole workspace: past the packed weights it may hold expanded weights and
+    // partial sums)
     if (overlap(workspace, workspace_bytes, x, ub * (size_t)in_features * es) ||
         overlap(workspace, workspace_bytes, coef, (size_t)out_features * in_features * gc.nb * es) ||
         overlap(workspace, workspace_bytes, base_w, (size_t)out_features * in_features * es) ||
@@ -472,8 +473,9 @@ kan_status kan_layer_forward_noalloc(const kan_grid* grid, kan_dtype dtype, int6
     st = kan_layer_pack(grid, dtype, in_features, out_features, coef, base_w, ws,
                         geom.packed_bytes, stream);
     if (st != KAN_OK) return st;
-    // the scratch past the packed weights holds the K split's partial sums
-    // when they fit (else the layer runs unsplit)
+    // the scratch past the packed weights holds the window kernel's weights and
+    // partial sums, or else the K split's partial sums, where they fit (else the
+    // layer runs unsplit on the packed weights)
     const size_t off = align256(geom.packed_bytes);
     void* rest = ws_bytes > off ? static_cast<char*>(ws) + off : nullptr;
     const size_t rest_bytes = ws_bytes > off ? ws_bytes - off : 0;

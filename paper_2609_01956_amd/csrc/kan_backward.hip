@@ -68,7 +68,6 @@ template <> struct B<float> {
     static __device__ __forceinline__ void st2(float* p, float v0, float v1) {
         *reinterpret_cast<floatx2*>(p) = floatx2{v0, v1};
     }
-    static constexpr int E = 4;   // elements per 16-byte unit
 };
 template <> struct B<uint16_t> {
     static __device__ __forceinline__ float ld(const uint16_t* p) { return bf16_to_f32(*p); }
@@ -76,7 +75,6 @@ template <> struct B<uint16_t> {
     static __device__ __forceinline__ void st2(uint16_t* p, float v0, float v1) {
         *reinterpret_cast<uint32_t*>(p) = pack2_bf16(v0, v1);
     }
-    static constexpr int E = 8;
 };
 
 // -------------------------------------------------------------- transposes
@@ -1042,9 +1040,12 @@ bool bwd_geom(int nb, bool bf16, int64_t batch, int in, int out, BwdGeom* g) {
     g->ktiles = (g->kr + g->kt - 1) / g->kt;
     // whole features per 256 K rows: the kernel of kan_bwd_dw.hip, whose fp32 form
     // takes at most 128 outputs per workgroup (and keeps ranges per 64 rows)
-    // (fp32 from 8192 rows: below, its sums are short and the fp32 instruction's
-    // kernel as exact and, with few workgroups, as fast: 1024 x 2 -> 5 59 us per
-    // training step against 64)
+    // (fp32 from 8192 rows: the fp32 instruction's kernel shares one launch that prepares
+    // small layers' operands, which this one, with its ranges, cannot: 1024 x 2 -> 5
+    // 59 us per training step against 64.  That is all it gains: dW alone, this kernel
+    // against the other's, takes 114 us against 240 for 4096 x 784 -> 256, 188 against
+    // 438 at 8128 rows, 34 against 47 for 4096 x 128 -> 128 and 20 against 21-22 for 2 -> 5
+    // at 1024 to 4096 rows; at 16384 rows 339 against 844, 52 against 97, 26 against 28.)
     g->dw2 = g->cp <= 256 && 256 % g->cp == 0 && (bf16 || batch >= 8192);
     const int wide = (g->out32 + g->oh * g->nfw * 32 - 1) / (g->oh * g->nfw * 32);
     if (g->dw2 && !bf16 && g->nfw == 4) g->nfw = 2;

@@ -296,7 +296,11 @@ BasisLaunch plan_basis(int64_t n, int nb, int k, int es, const void* phi) {
     BasisLaunch L;
     // The many-run kernel: bf16, short runs (at most 16 values per input) and enough
     // of them (65536 x 784, G = 10: 260 us against 340; 65536 x 256: 70 against 79;
-    // with eight runs 16384 x 256, 16384 runs: 20 against 18.6;
+    // with eight runs 16384 x 256, 16384 runs: 20 against 18.6; with the runs that
+    // basis_runs gives now, this kernel against the one-run kernel at G = 10: 16384 runs
+    // 19.4 against 19.0, 32768 35.5 against 38, 49152 51.5 against 57, and at G = 5 16.6
+    // against 18.4, 29.7 against 34.2, 43 against 50, so the line lies too high by a
+    // factor of two to four;
     // longer runs, 60000 x 300, G = 25: 187 against 172; fp32 runs of the same bytes,
     // 65536 x 300, G = 5: 115 against 99), with room for the window, and an aligned
     // output (every run then starts on 16 bytes).

@@ -9,8 +9,8 @@
 // first leaves, rounded again: 22 bits and a sign), three products (the fourth
 // is below 2^-22 of the first), exact in fp32, fp32 accumulation: 96 cycles per
 // 16 rows of a 32 x 32 tile where the fp32 matrix instruction takes 512 (784 ->
-// 256 at 16384 rows: 794 -> 312 us; relative error against float64 6.2e-7 ->
-// 4.0e-7).  dy is
+// 256 at 16384 rows, the weight gradients alone: 844 -> 339 us a call; relative error
+// against float64 6.2e-7 -> 4.0e-7).  dy is
 // scaled per output and SiLU values per feature by the power of two that brings
 // the largest of the workgroup's rows to 2^14 (from the maxima that the
 // transposition leaves per 64 rows), basis values by 2^12, and second terms by

@@ -14,14 +14,14 @@
 //
 // bf16: one bf16 operand each, two row tiles per wave, so that every A fragment
 // read from LDS feeds two MFMAs (with one, the reads alone fill the LDS's
-// bandwidth at the matrix cores' rate).  784 -> 256 at 65536 rows: 496 -> 375 us
+// bandwidth at the matrix cores' rate).  784 -> 256 at 65536 rows: 496 -> 377 us
 // (two row tiles and columns selected in registers 420, A fragments read four
-// groups ahead 375).
+// groups ahead 377).
 // fp32: both operands as two fp16 terms (kan_bwd_dw.hip) and three products:
 // 96 cycles per 16 outputs of a 32 x 32 tile where the fp32 instruction takes
 // 512.  dy is scaled per batch row and the weights per K tile and chunk of
 // outputs by the power of two that brings the largest to 2^12.  784 -> 256 at 16384
-// rows: 805 -> 267 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
+// rows: 805 -> 277 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
 // window at its own coordinate; fewer roundings).  The terms hold 22 bits of the
 // largest weight of every window; a K tile with weights that they cannot hold so
 // (kan_bwd_pack.h) is held in fp32 and taken after the others on the fp32

@@ -203,8 +203,8 @@ hipError_t launch_narrow(const LayerGeom& g, const LayerArgs& a, hipStream_t s);
 // --------------------------------------------- window kernel (kan_window_kernel.h)
 //
 // The fused forward on the structured-sparse matrix instruction for degrees 1 ..
-// 3 and any grid: fp32 as two fp16 terms per operand, bf16 where a feature
-// does not take two blocks of eight columns.  It runs on weights expanded from
+// 3 and any grid: fp32 as two fp16 terms per operand, bf16 where a feature of a
+// cubic layer does not take two blocks of eight columns.  It runs on weights expanded from
 // the packed buffer into the caller's workspace.
 struct WinGeom {
     int nfw;        // 32-column fragments per wave (64 nfw columns per tile)
@@ -351,7 +351,7 @@ struct SpanGeom {
     int fs, fpf;     // feature splits (partials summed when > 1), features per split
     int cs;          // fp32: LDS stride of one weight column in floats (tile width, padded)
     int64_t rblocks; // row blocks of 256 nr / ng rows
-    size_t off_w, off_p, bytes;  // workspace: transposed weights (four bytes each), partial sums
+    size_t off_w, off_p, bytes;  // workspace: transposed weights (four bytes each; bf16 uses two), partial sums
 };
 bool span_geom(int nb, int64_t batch, int in, int out, SpanGeom* g);
 

@@ -1,7 +1,8 @@
 // kan_window_kernel.h -- fused KAN-layer forward (eq. kan_forward) on the
 // structured-sparse matrix instruction for any grid and degrees 1 .. 3: fp32
-// layers as two fp16 terms per operand, and bf16 layers whose features take
-// other than two blocks of eight columns.
+// layers as two fp16 terms per operand, and bf16 layers (cubic ones only where a
+// feature takes other than two blocks of eight columns; those have a kernel of their
+// own).
 //
 // Of a feature's basis columns only the k + 1 <= 4 whose support holds x can be
 // nonzero (eq. bounded), and they are consecutive.  A feature's columns
@@ -26,8 +27,8 @@
 // the fp32 instruction over all columns takes 1024, and fewer roundings of the
 // accumulator, which set the layer's error: relative error (2-norm) against
 // float64 at 65536 x 784 -> 256, G = 10: 8.7e-7, with the fp32 instruction 1.1e-6;
-// 8192 x 128 -> 128, G = 100: 1.8e-7 both.  Times at these sizes: 3198 -> 634 us
-// and 316 -> 80 us.  Coefficients are scaled per output column by the power of two
+// 8192 x 128 -> 128, G = 100: 1.8e-7 both.  Times of a call at these sizes: 3198 ->
+// 658 us and 312 -> 76 us.  Coefficients are scaled per output column by the power of two
 // that brings the column's largest to [2^12, 2^13), and basis values by 2^12; a
 // column's coefficients then have an absolute error of 2^-37 of its largest.  That
 // is 2^-22 or less of the largest of any k + 1 consecutive coefficients of a
