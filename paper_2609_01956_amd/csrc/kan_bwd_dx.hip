@@ -21,7 +21,7 @@
 // 96 cycles per 16 outputs of a 32 x 32 tile where the fp32 instruction takes
 // 512.  dy is scaled per batch row and the weights per K tile and chunk of
 // outputs by the power of two that brings the largest to 2^12.  784 -> 256 at 16384
-// rows: 805 -> 277 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
+// rows: 805 -> 277-300 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
 // window at its own coordinate; fewer roundings).  The terms hold 22 bits of the
 // largest weight of every window; a K tile with weights that they cannot hold so
 // (kan_bwd_pack.h) is held in fp32 and taken after the others on the fp32

@@ -28,7 +28,7 @@
 // accumulator, which set the layer's error: relative error (2-norm) against
 // float64 at 65536 x 784 -> 256, G = 10: 8.7e-7, with the fp32 instruction 1.1e-6;
 // 8192 x 128 -> 128, G = 100: 1.8e-7 both.  Times of a call at these sizes: 3198 ->
-// 658 us and 312 -> 76 us.  Coefficients are scaled per output column by the power of two
+// 674 us and 312 -> 76 us.  Coefficients are scaled per output column by the power of two
 // that brings the column's largest to [2^12, 2^13), and basis values by 2^12; a
 // column's coefficients then have an absolute error of 2^-37 of its largest.  That
 // is 2^-22 or less of the largest of any k + 1 consecutive coefficients of a
