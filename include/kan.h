@@ -352,8 +352,8 @@ kan_status kan_layer_plan(const kan_grid* grid, kan_dtype dtype, int64_t batch,
  * the weight gradients of batches below 8192 rows and of grids whose padded
  * columns do not divide 256, which use the fp32 matrix instruction, and dx of
  * features (in pairs up to G = 12) whose terms would not hold 22 bits of the largest of
- * any four consecutive coefficients, or that have four consecutive coefficients
- * of 0 for some outputs only: these run on the fp32 instruction too.  So do single
+ * any four consecutive coefficients or 20 bits of a sum of SiLU weights, or that have
+ * four consecutive coefficients or a SiLU weight of 0 for some outputs only: these run on the fp32 instruction too.  So do single
  * weight gradients made of values far below the largest: the terms hold 21 bits
  * of a dy within 2^-29 of its output's largest (of the rows of a batch split), and of
  * a SiLU value likewise, and a sum in which the rounding of smaller ones could

@@ -19,13 +19,13 @@
 // groups ahead 377).
 // fp32: both operands as two fp16 terms (kan_bwd_dw.hip) and three products:
 // 96 cycles per 16 outputs of a 32 x 32 tile where the fp32 instruction takes
-// 512.  dy is scaled per batch row and the weights per K tile and chunk of
-// outputs by the power of two that brings the largest to 2^12.  784 -> 256 at 16384
-// rows: 805 -> 277-300 us, relative error (2-norm) against float64 5e-7 -> 1.6e-7 (the
-// window at its own coordinate; fewer roundings).  The terms hold 22 bits of the
-// largest weight of every window; a K tile with weights that they cannot hold so
-// (kan_bwd_pack.h) is held in fp32 and taken after the others on the fp32
-// instruction, and rows with a non-finite dy are then computed apart.
+// 512.  dy is scaled per batch row and the weights per K tile and chunk of outputs
+// (coefficients and SiLU weights each by their own) by the power of two that brings the
+// largest to 2^14.  784 -> 256 at 16384 rows: 805 -> 277-300 us, relative error (2-norm)
+// against float64 5e-7 -> 1.6e-7 (the window at its own coordinate; fewer roundings).
+// The terms hold 22 bits of the largest weight of every window; a K tile with weights
+// that they cannot hold so (kan_bwd_pack.h) is held in fp32 and taken after the others
+// on the fp32 instruction, and rows with a non-finite dy are then computed apart.
 #include "kan_bwd_pack.h"
 
 #include <algorithm>
@@ -80,8 +80,9 @@ __device__ __forceinline__ float slope_at(float v) {
 // other tiles' weights from the two terms), for the wave's row tile rf.  dy comes from
 // memory again, in fp32, and the weights straight from the workspace, both a group of
 // outputs ahead.  A function of its own, so that the main loop keeps its registers;
-// args: the kernel's, in place.  16384 x 784 -> 256 with every tile so: 1.6 ms, 0.3 ms
-// with none (0.8 ms where the fp32 instruction was the kernel's own).
+// args: the kernel's, in place.  16384 x 784 -> 256 with every tile so: 1.29 ms a call,
+// 0.29 ms with none (0.8 ms where the fp32 instruction was the kernel's own), 0.30 ms
+// with one.
 template <int RF, bool C16>
 __device__ __attribute__((noinline)) void wide_tiles(const uint32_t* args, int rf) {
     constexpr int NT = 2;
@@ -115,10 +116,16 @@ __device__ __attribute__((noinline)) void wide_tiles(const uint32_t* args, int r
                                 (uint32_t)((g0 + s) * 16 + 8 * h + 4 * m)) * 4u, 0, 0));
     };
 #pragma unroll 1
-    for (int t0 = t_begin; t0 < t_end; t0 += tpf) {
-        int flags = 0;
-        for (int t = t0; t < t0 + tpf; ++t) flags |= a.wexp[t * a.nchunk + ch];
-        if (__builtin_amdgcn_readfirstlane(flags >> 16) == 0) continue;
+    for (int next = t_begin; next < t_end;) {
+        // the first feature with such a tile, 64 tiles at a look
+        const int tl = next + lane;
+        const uint64_t wide = __ballot(tl < t_end && (a.wexp[min(tl, t_end - 1) * a.nchunk + ch] & kPackWide) != 0);
+        if (wide == 0) {
+            next += 64;
+            continue;
+        }
+        const int t0 = (next + __ffsll((unsigned long long)wide) - 1) / tpf * tpf;
+        next = t0 + tpf;
         const int f = C16 ? 2 * t0 + h : t0 / tpf;
         const float x = f < a.in ? static_cast<const float*>(a.xt)[(int64_t)f * a.bpad + rowc] : 0.0f;
         const float lo = coord_lo(x, a.xlim, a.inv_lo, a.a_frac);
@@ -126,6 +133,8 @@ __device__ __attribute__((noinline)) void wide_tiles(const uint32_t* args, int r
 #pragma unroll 1
         for (int t = t0; t < t0 + tpf; ++t) {
             const int we = __builtin_amdgcn_readfirstlane(a.wexp[t * a.nchunk + ch]);
+            // (a feature of several tiles: its SiLU column is the first A row of its first)
+            const int wx = (r == 0 && t == t0 ? pack_es(we) : pack_ex(we)) - kPackExp;
             const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(
                 a.wtp + ((int64_t)t * a.groups + g0) * (NT * 64), (short)0, S * NT * 1024,
                 kBufferWord3);
@@ -149,12 +158,12 @@ __device__ __attribute__((noinline)) void wide_tiles(const uint32_t* args, int r
                 float w[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) w[e] = __uint_as_float(e < 4 ? q0[e % 4] : q1[e % 4]);
-                if (we >> 16 == 0) {
+                if ((we & kPackWide) == 0) {
                     const f16x8_t h0 = __builtin_bit_cast(f16x8_t, q0);
                     const f16x8_t h1 = __builtin_bit_cast(f16x8_t, q1);
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        w[e] = __builtin_ldexpf((float)h0[e] + (float)h1[e], we - 512 - 12);
+                        w[e] = __builtin_ldexpf((float)h0[e] + (float)h1[e], wx);
                 }
                 if ((g0 + s) * 16 + 16 > a.out) {  // (past the row: the next row's)
 #pragma unroll
@@ -348,13 +357,13 @@ void dx2_kernel(Dx2Args a) {
             bad |= __shfl_xor((int)bad, 32) != 0;
             if (h == 0) rowbad[wave * 32 * RF + 32 * rf + r] = bad;
             const int ex = (int)(__float_as_uint(m) >> 23) - 127;
-            esc[rf] = ex - 12;
+            esc[rf] = ex - kPackExp;
 #pragma unroll
             for (int s = 0; s < SM; ++s) {
                 f16x8_t t0, t1;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float x = __builtin_amdgcn_fmed3f(__builtin_ldexpf(v[s][e], 12 - ex),
+                    const float x = __builtin_amdgcn_fmed3f(__builtin_ldexpf(v[s][e], kPackExp - ex),
                                                             -60000.0f, 60000.0f);
                     t0[e] = (_Float16)x;
                     t1[e] = (_Float16)(x - (float)t0[e]);
@@ -496,8 +505,7 @@ void dx2_kernel(Dx2Args a) {
             const int f = cp16 ? fu + h : fu;
             const int c0 = cp16 ? 0 : 32 * t - fu * a.cp + 16 * h;
             int we = 0;
-            if constexpr (!BF)
-                we = (a.wexp[min(t, a.ntiles - 1) * a.nchunk + ch] & 0xffff) - 512 - 12;
+            if constexpr (!BF) we = a.wexp[min(t, a.ntiles - 1) * a.nchunk + ch];
 #pragma unroll
             for (int rf = 0; rf < RF; ++rf) {
                 float xv;
@@ -545,8 +553,13 @@ void dx2_kernel(Dx2Args a) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) sb = __builtin_fmaf(gw[q], d[q], sb);
                 }
-                float v = __builtin_fmaf(c0 == 0 ? acc[rf][0] : 0.0f, silu_slope(xv), a.inv_h * sb);
-                if constexpr (!BF) v = __builtin_ldexpf(v, we + esc[rf]);
+                const float s0 = c0 == 0 ? acc[rf][0] : 0.0f;
+                float v;
+                if constexpr (BF)
+                    v = __builtin_fmaf(s0, silu_slope(xv), a.inv_h * sb);
+                else
+                    v = __builtin_ldexpf(s0 * silu_slope(xv), pack_es(we) - kPackExp + esc[rf]) +
+                        __builtin_ldexpf(a.inv_h * sb, pack_ex(we) - kPackExp + esc[rf]);
                 if (!cp16) {
                     // features of several tiles: the running sum, complete (both
                     // lane halves added) at the feature's last tile
@@ -569,14 +582,16 @@ void dx2_kernel(Dx2Args a) {
     if constexpr (!BF) {
         int any = 0;
         for (int i = tid; i < BM; i += kThreads) any |= rowbad[i];
-        for (int t = t_begin + tid; t < t_end; t += kThreads) any |= a.wexp[t * a.nchunk + ch] >> 16;
+        for (int t = t_begin + tid; t < t_end; t += kThreads) any |= a.wexp[t * a.nchunk + ch] & kPackWide;
         if (__syncthreads_or(any)) {
 #pragma unroll 1
             for (int rf = 0; rf < RF; ++rf)
                 wide_tiles<RF, C16>((const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr(), rf);
             // Rows with a non-finite dy: the same sums in plain fp32, with the zeros and
             // infinities the matrix instruction would meet.
-            __syncthreads();
+            int rows = 0;
+            for (int i = tid; i < BM; i += kThreads) rows |= rowbad[i];
+            if (!__syncthreads_or(rows)) return;
             const int f_beg = cp16 ? 2 * t_begin : t_begin / tpf;
             const int f_end = min(a.in, cp16 ? 2 * t_end : t_end / tpf);
             const int nf = f_end - f_beg;

@@ -20,7 +20,19 @@ __device__ __forceinline__ T weight(const Dx2Args& a, int o, int f, int c) {
 // fp32: a window (four consecutive coefficients of a feature for an output: what one
 // input's derivative meets) whose largest is 2^kPackWindowBits below the tile's
 // scale loses more than the last two bits of its fp32 values.
-constexpr int kPackWindowBits = 15;
+constexpr int kPackWindowBits = 17;
+// SiLU weights have a scale of their own.  One that is that far below it: what the terms
+// lose of the other outputs' gradients, where it alone meets the largest, is then past
+// 2^-17 of the sum (past the grid there is nothing else).  (A window's bits would be met
+// by chance in many tiles: its largest of four is not.)
+constexpr int kPackSiluBits = 22;
+constexpr int kPackExp = 14;  // the largest of a scale's weights, and dy of a row: [2^14, 2^15)
+// The word of a tile: the exponents of the coefficients' and the SiLU weights' scales,
+// or that the tile's weights are held in fp32.
+constexpr int kPackWide = 1 << 24;
+__device__ __forceinline__ int pack_word(int ex, int es) { return (ex + 512) | (es + 512) << 12; }
+__device__ __forceinline__ int pack_ex(int w) { return (w & 0xfff) - 512; }
+__device__ __forceinline__ int pack_es(int w) { return (w >> 12 & 0xfff) - 512; }
 
 // The next lane's value (the wave's last lane: its own).
 __device__ __forceinline__ float next_lane(float v) {
@@ -30,12 +42,13 @@ __device__ __forceinline__ float next_lane(float v) {
 
 // One workgroup packs K tile t for output chunk ch (groups g0 .. g0 + S - 1 of 16
 // outputs): [t][g][term][lane (r, h)][e], outputs 16 g + 8 h + e of the K row of A
-// row r.  fp32: two fp16 terms of the weights, scaled per (tile, chunk), and
-// wexp[t nchunk + ch] = the exponent, biased by 512.  Bit 16 of it: the tile holds
-// its weights in fp32 instead (outputs 16 g + 8 h + 4 term + 0 .. 3 in a unit), as
-// the terms cannot hold them: a weight is not finite, or some window or SiLU column is
-// too far below the scale, or a window is zero for some outputs only (their
-// gradients are then all that a dx has, however small beside the others').
+// row r.  fp32: two fp16 terms of the weights, scaled per (tile, chunk), coefficients and
+// SiLU weights each by their own, and wexp[t nchunk + ch] = pack_word, or kPackWide: the
+// tile holds its weights in fp32 instead (outputs 16 g + 8 h + 4 term + 0 .. 3 in a
+// unit), as the terms cannot hold them: a weight is not finite, or some window, SiLU
+// column or SiLU weight is too far below its scale, or a window or SiLU weight is zero for
+// some outputs only (the others' gradients are then all that a dx has, however small
+// beside those outputs').
 template <typename T>
 __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
     constexpr bool BF = sizeof(T) == 2;
@@ -70,10 +83,11 @@ __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
         for (int i = 8 * ib; i < 8 * ib + 8; ++i)
             if (!ok || 16 * g0 + 8 * i + e >= a.out || i >= 2 * S) v[i] = T(0);
     }
-    int ex = 0;
+    int ex = 0, es = 0;
     bool wide = false;
     if constexpr (!BF) {
         __shared__ floatx2 redm[4];
+        __shared__ floatx2 reds[4];
         __shared__ int zeros[38], others[38], silu[32];  // (windows: per first K row; see edges)
         if (tid < 38) zeros[tid] = others[tid] = 0;
         if (tid < 32) silu[tid] = 0;
@@ -93,15 +107,17 @@ __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
             const float w1 = i < outs ? av : __builtin_fabsf(v[0]);
             const float w2 = __builtin_fmaxf(w1, next_lane(w1));
             const float w3 = __builtin_fmaxf(w1, next_lane(w2));
-            const uint32_t w4 = __float_as_uint(__builtin_fmaxf(w1, next_lane(w3))) - 1u;
+            // (a SiLU weight is a window of its own)
+            const uint32_t w4 = __float_as_uint(c == 0 ? w1 : __builtin_fmaxf(w1, next_lane(w3))) - 1u;
             hi = max(hi, w4);
             lo = min(lo, w4);
         }
-        if (f < a.in && c >= 1 && c + 3 <= a.nb && kl + 3 < 32 && outs > 0) {
+        float ms = __builtin_inff();  // the least SiLU weight
+        if (f < a.in && (c == 0 || (c + 3 <= a.nb && kl + 3 < 32)) && outs > 0) {
             if (hi == 0xffffffffu) zeros[kl] = 1;
             if (lo != 0xffffffffu) {
                 others[kl] = 1;
-                mw = __uint_as_float(lo + 1u);
+                (c == 0 ? ms : mw) = __uint_as_float(lo + 1u);
             }
         }
         if (c == 0 && f < a.in) atomicMax(&silu[kl], (int)__float_as_uint(m));
@@ -130,27 +146,35 @@ __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
             }
         }
         if (bad) m = __builtin_inff();
+        float msl = c == 0 ? m : 0.0f;  // the largest SiLU weight
+        m = c == 0 ? 0.0f : m;
 #pragma unroll
         for (int k = 1; k < 64; k *= 2) {
             m = __builtin_fmaxf(m, __shfl_xor(m, k));
+            msl = __builtin_fmaxf(msl, __shfl_xor(msl, k));
             mw = __builtin_fminf(mw, __shfl_xor(mw, k));
+            ms = __builtin_fminf(ms, __shfl_xor(ms, k));
         }
-        if (tid % 64 == 0) redm[tid / 64] = floatx2{m, mw};
+        if (tid % 64 == 0) redm[tid / 64] = floatx2{m, mw}, reds[tid / 64] = floatx2{msl, ms};
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             m = __builtin_fmaxf(m, redm[k][0]);
             mw = __builtin_fminf(mw, redm[k][1]);
+            msl = __builtin_fmaxf(msl, reds[k][0]);
+            ms = __builtin_fminf(ms, reds[k][1]);
         }
         auto exponent = [](float q) -> int { return (int)(__float_as_uint(q) >> 23) - 127; };
         ex = exponent(m);
-        bool w = !(m < __builtin_inff()) ||
-                 exponent(mw) < ex - kPackWindowBits;  // (infinity: no window)
+        es = exponent(msl);
+        bool w = !(m < __builtin_inff()) || !(msl < __builtin_inff()) ||
+                 exponent(mw) < ex - kPackWindowBits ||  // (infinity: no window)
+                 exponent(ms) < es - kPackSiluBits;
         if (tid < 38) w |= (zeros[tid] & others[tid]) != 0;
         if (tid < 32)
-            w |= silu[tid] != 0 && exponent(__uint_as_float((uint32_t)silu[tid])) < ex - kPackWindowBits;
+            w |= silu[tid] != 0 && exponent(__uint_as_float((uint32_t)silu[tid])) < es - kPackWindowBits;
         wide = __syncthreads_or(w);
-        if (tid == 0) a.wexp[t * a.nchunk + ch] = wide ? 1 << 16 : ex + 512;
+        if (tid == 0) a.wexp[t * a.nchunk + ch] = wide ? kPackWide : pack_word(ex, es);
     }
     if (!BF && wide) {
         float* raw = reinterpret_cast<float*>(&buf[0][0][0][0]);  // [output octet][A row][e]
@@ -164,7 +188,7 @@ __device__ __forceinline__ void pack_dx2(const Dx2Args& a, int t, int ch) {
             if constexpr (BF) {
                 buf[0][i][r][e] = v[i];
             } else {
-                const float x = __builtin_ldexpf(v[i], 12 - ex);
+                const float x = __builtin_ldexpf(v[i], kPackExp - (c == 0 ? es : ex));
                 const _Float16 h0 = (_Float16)x;
                 buf[0][i][r][e] = __builtin_bit_cast(uint16_t, h0);
                 buf[NT - 1][i][r][e] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)h0));

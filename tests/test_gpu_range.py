@@ -233,3 +233,21 @@ def test_dw_large_input_without_gradient(B, n_in, n_out, G, xs):
         for f in range(n_in):
             assert normwise(dW[o, f], rW[o, f]) <= F32_LAYER_TOL, f
             assert normwise(dC[o, f], rC[o, f]) <= F32_LAYER_TOL, f
+
+
+@pytest.mark.parametrize("edge", [0.0, 1e-9, 1e-30])
+@pytest.mark.parametrize("B,n_in,n_out,G", BACK)
+def test_dx_silu_weights_past_the_grid(B, n_in, n_out, G, edge):
+    """Inputs past the grid, where only the SiLU weights count: those of the output with
+    the large gradient are zero or small for some features, whose coefficients are not."""
+    x, C, Wb, dy = _case(B, n_in, n_out, G, seed=14, dtype_name="f32")
+    x[::2] = np.where(x[::2] > 0, 3.0, -2.5) + x[::2]
+    o1 = n_out // 2
+    dy[:, np.arange(n_out) != o1] *= np.float32(1e-12)
+    Wb[o1, ::2] *= np.float32(edge)
+    say(f"range dx silu edges {edge:g} {n_in}->{n_out} G={G}")
+    got = _run_backward(x, C, Wb, dy, G, "f32", need_dw=False)[0]
+    ref = oracle.layer_backward(x, C, Wb, dy, G)[0]
+    for f in range(n_in):
+        assert normwise(got[::2, f], ref[::2, f]) <= F32_LAYER_TOL, f
+        assert normwise(got[1::2, f], ref[1::2, f]) <= F32_LAYER_TOL, f
